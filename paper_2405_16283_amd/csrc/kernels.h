@@ -35,7 +35,7 @@ enum LaunchClass {
   LC_RMS_STAT,
   LC_RMS_APPLY,
   LC_ROPE,
-  LC_ATTN_F32,       // attention block on the vector ALUs (fp32 storage, or shapes the MFMA kernel does not take)
+  LC_ATTN_F32,       // attention block with fp32 products (fp32 storage, or shapes the bf16 kernel does not take)
   LC_ATTN_BF16,      // MFMA attention block
   LC_ATTN_COMBINE,
   LC_SILU_MUL,
@@ -43,7 +43,7 @@ enum LaunchClass {
   LC_SILU_BWD,
   LC_RMS_BWD_STAT,
   LC_RMS_BWD_APPLY,
-  LC_ATTN_BWD,       // attention backward on the vector ALUs (statistics, dQ, dK, dV)
+  LC_ATTN_BWD,       // attention backward with fp32 products (statistics, dQ, dK, dV)
   LC_ATTN_BWD_BF16,  // MFMA attention backward: statistics; the next three values are its dQ, dK and dV forms
   LC_ATTN_BWD_BF16_DQ,
   LC_ATTN_BWD_BF16_DK,
@@ -115,5 +115,9 @@ int32_t blocks_for(int cls, const OpDesc& d, const int32_t* aux);
 // type and (for attention) the head size.  max_blocks = largest nblocks in the batch.
 hipError_t launch_batch(int cls, int dtype, int head_dim, const DeviceTables& t, const Batch& b,
                         int32_t max_blocks, hipStream_t stream);
+
+// LC_ATTN_F32 (reverse == false) and LC_ATTN_BWD: attn_f32.hip.
+hipError_t launch_attn_f32(bool reverse, int dtype, int head_dim, const DeviceTables& t, const Batch& b, int32_t max_blocks,
+                           hipStream_t stream);
 
 }  // namespace tn

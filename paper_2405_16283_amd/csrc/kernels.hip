@@ -6,6 +6,7 @@
 // (Appendix A); here every vertex kind has its own kernel, written for 64-wide wavefronts and
 // the MFMA units.  All kernels are grouped (see kernels.h) and deterministic: fixed summation
 // order, no atomics, so any dispatch order gives the same bits.
+#include "device.h"
 #include "kernels.h"
 
 #include <climits>
@@ -14,27 +15,6 @@
 
 namespace tn {
 namespace {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef unsigned short bf16_t;  // storage of a bf16 value
-
-__device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float((uint32_t)b << 16); }
-// round to nearest, ties to even: the hardware conversion of gfx950 (v_cvt_pk_bf16_f32)
-__device__ __forceinline__ bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
-// two values at once, the first in the low half
-__device__ __forceinline__ uint32_t f2bf2(float a, float b) {
-  typedef float f32x2_t __attribute__((ext_vector_type(2)));
-  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t));
-}
-template <typename T> __device__ __forceinline__ float ld(const T* p);
-template <> __device__ __forceinline__ float ld<float>(const float* p) { return *p; }
-template <> __device__ __forceinline__ float ld<bf16_t>(const bf16_t* p) { return bf2f(*p); }
-template <typename T> __device__ __forceinline__ void st(T* p, float v);
-template <> __device__ __forceinline__ void st<float>(float* p, float v) { *p = v; }
-template <> __device__ __forceinline__ void st<bf16_t>(bf16_t* p, float v) { *p = f2bf(v); }
 
 // ---------------------------------------------------------------------------------------------
 // elementwise: add, silu*mul
@@ -1080,171 +1060,6 @@ __global__ void __launch_bounds__(64 * NW, TI == 2 ? 2 : 1) gemm_bf16_nt256_kern
 }
 
 // ---------------------------------------------------------------------------------------------
-// attention block on the vector ALUs: one thread per (query row, head), online softmax over
-// the key rows in ascending order.  Serves fp32 graphs and shapes the MFMA kernel does not take.
-// aux: [rows per Q tile, rows per K/V tile, columns per tile, q rows, kv rows]
-// ---------------------------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ const T* tile_elem(void* const* tiles, int nc, int t_rows, int t_cols, int row, int col) {
-  const int rt = row / t_rows, ct = col / t_cols;
-  return (const T*)tiles[rt * nc + ct] + (size_t)(row - rt * t_rows) * t_cols + (col - ct * t_cols);
-}
-
-// The same for a grid of transposed tiles: tile (rt, ct) holds [its columns, its rows]; the last
-// row tile may be shorter, which changes its pitch.
-template <typename T>
-__device__ __forceinline__ const T* tile_elem_t(void* const* tiles, int nc, int t_rows, int t_cols, int total_rows,
-                                                int row, int col) {
-  const int rt = row / t_rows, ct = col / t_cols;
-  const int pitch = min(t_rows, total_rows - rt * t_rows);
-  return (const T*)tiles[rt * nc + ct] + (size_t)(col - ct * t_cols) * pitch + (row - rt * t_rows);
-}
-
-template <typename T, int HD>
-__global__ void __launch_bounds__(64) attn_generic_kernel(DeviceTables t, Batch b) {
-  const OpDesc& d = t.descs[b.at(blockIdx.y)];
-  if ((int)blockIdx.x >= d.nblocks) return;
-  const int* ax = t.aux + d.aux0;
-  const int tq = ax[0], tk = ax[1], tc = ax[2], q_rows = ax[3], kv_rows = ax[4];
-  const int nc = d.p.n_col_tiles, gw = nc * tc;
-  const int hpg = gw / HD;
-  const int qblocks = (q_rows + 63) / 64;
-  const int h = blockIdx.x / qblocks, row = (blockIdx.x % qblocks) * 64 + threadIdx.x;
-  if (row >= q_rows) return;
-  void* const* Qt = t.ptrs + d.ptr0;
-  void* const* Kt = Qt + d.p.n_q_tiles * nc;
-  void* const* Vt = Kt + d.p.n_kv_tiles * nc;
-  float q[HD], o[HD];
-#pragma unroll
-  for (int c = 0; c < HD; ++c) {
-    q[c] = ld(tile_elem<T>(Qt, nc, tq, tc, row, h * HD + c)) * d.p.scale;
-    o[c] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  const int qpos = d.p.q_pos0 + row;
-  for (int j = 0; j < kv_rows; ++j) {
-    if (d.p.causal && d.p.k_pos0 + j > qpos) break;
-    float s = 0.f;
-#pragma unroll
-    for (int c = 0; c < HD; ++c) s = fmaf(q[c], ld(tile_elem<T>(Kt, nc, tk, tc, j, h * HD + c)), s);
-    const float mn = fmaxf(m, s);
-    const float alpha = __expf(m - mn), p = __expf(s - mn);
-    l = l * alpha + p;
-#pragma unroll
-    for (int c = 0; c < HD; ++c) {
-      const float v = d.p.v_trans ? ld(tile_elem_t<T>(Vt, nc, tk, tc, kv_rows, j, h * HD + c))
-                                  : ld(tile_elem<T>(Vt, nc, tk, tc, j, h * HD + c));
-      o[c] = o[c] * alpha + p * v;
-    }
-    m = mn;
-  }
-  float* out = (float*)d.out + (size_t)row * d.cols;
-#pragma unroll
-  for (int c = 0; c < HD; ++c) out[h * HD + c] = o[c];
-  out[gw + h] = m;
-  out[gw + hpg + h] = l;
-}
-
-// ---------------------------------------------------------------------------------------------
-// attention backward on the vector ALUs.  Modes 0 (statistics) and 1 (dQ): one thread per (query
-// row, head), keys ascending.  Modes 2 (dK) and 3 (dV): one thread per (key row, head), queries
-// ascending.  Scores are recomputed from Q and K; p = exp(scale q.k - lse).
-// aux: [rows per Q tile, rows per K/V tile, columns per tile, q rows, kv rows]
-// ---------------------------------------------------------------------------------------------
-template <typename T, int HD>
-__global__ void __launch_bounds__(64) attn_bwd_kernel(DeviceTables t, Batch b) {
-  const OpDesc& d = t.descs[b.at(blockIdx.y)];
-  if ((int)blockIdx.x >= d.nblocks) return;
-  const int* ax = t.aux + d.aux0;
-  const int tq = ax[0], tk = ax[1], tc = ax[2], q_rows = ax[3], kv_rows = ax[4];
-  const int nc = d.p.n_col_tiles, gw = nc * tc, hpg = gw / HD, mode = d.p.mode;
-  const int nq = d.p.n_q_tiles, nkv = d.p.n_kv_tiles;
-  void* const* Qt = t.ptrs + d.ptr0;
-  void* const* Kt = Qt + nq * nc;
-  void* const* Vt = Kt + nkv * nc;
-  void* const* Dt = Vt + nkv * nc;   // dO tiles
-  void* const* St = Dt + nq * nc;    // statistics, one tensor per Q row tile (modes 1..3)
-  const int my_rows = mode <= 1 ? q_rows : kv_rows;
-  const int rblocks = (my_rows + 63) / 64;
-  const int h = blockIdx.x / rblocks, row = (blockIdx.x % rblocks) * 64 + threadIdx.x;
-  if (row >= my_rows) return;
-  const float scale = d.p.scale;
-  auto vel = [&](int j, int c) -> float {  // V[j, h*HD + c]
-    return d.p.v_trans ? ld(tile_elem_t<T>(Vt, nc, tk, tc, kv_rows, j, h * HD + c))
-                       : ld(tile_elem<T>(Vt, nc, tk, tc, j, h * HD + c));
-  };
-  auto stat = [&](int r, int which) -> float {  // which 0: lse, 1: D
-    const int rt = r / tq;
-    const float* s = (const float*)St[rt];
-    return s[(size_t)(r - rt * tq) * (2 * hpg) + which * hpg + h];
-  };
-  if (mode <= 1) {
-    const int qpos = d.p.q_pos0 + row;
-    float acc[HD];
-#pragma unroll
-    for (int c = 0; c < HD; ++c) acc[c] = 0.f;
-    float m = -INFINITY, l = 0.f, dsum = 0.f;  // mode 0: running maximum, sum of exp, sum of exp * dp
-    const float lse = mode == 1 ? stat(row, 0) : 0.f, D = mode == 1 ? stat(row, 1) : 0.f;
-    for (int j = 0; j < kv_rows; ++j) {
-      if (d.p.causal && d.p.k_pos0 + j > qpos) break;
-      float s = 0.f, dp = 0.f;
-#pragma unroll 8
-      for (int c = 0; c < HD; ++c) {
-        s = fmaf(ld(tile_elem<T>(Qt, nc, tq, tc, row, h * HD + c)), ld(tile_elem<T>(Kt, nc, tk, tc, j, h * HD + c)), s);
-        dp = fmaf(ld(tile_elem<T>(Dt, nc, tq, tc, row, h * HD + c)), vel(j, c), dp);
-      }
-      s *= scale;
-      if (mode == 0) {
-        const float mn = fmaxf(m, s);
-        const float alpha = __expf(m - mn), p = __expf(s - mn);
-        l = l * alpha + p;
-        dsum = dsum * alpha + p * dp;
-        m = mn;
-      } else {
-        const float ds = __expf(s - lse) * (dp - D) * scale;
-#pragma unroll 8
-        for (int c = 0; c < HD; ++c) acc[c] = fmaf(ds, ld(tile_elem<T>(Kt, nc, tk, tc, j, h * HD + c)), acc[c]);
-      }
-    }
-    if (mode == 0) {
-      float* out = (float*)d.out + (size_t)row * (2 * hpg);
-      out[h] = m + __logf(l);
-      out[hpg + h] = dsum / l;
-    } else {
-      T* out = (T*)d.out + (size_t)row * gw + h * HD;
-#pragma unroll 8
-      for (int c = 0; c < HD; ++c) st(out + c, acc[c]);
-    }
-  } else {
-    const int kpos = d.p.k_pos0 + row;
-    float acc[HD];
-#pragma unroll
-    for (int c = 0; c < HD; ++c) acc[c] = 0.f;
-    for (int r = 0; r < q_rows; ++r) {
-      if (d.p.causal && kpos > d.p.q_pos0 + r) continue;
-      float s = 0.f, dp = 0.f;
-#pragma unroll 8
-      for (int c = 0; c < HD; ++c) {
-        s = fmaf(ld(tile_elem<T>(Qt, nc, tq, tc, r, h * HD + c)), ld(tile_elem<T>(Kt, nc, tk, tc, row, h * HD + c)), s);
-        if (mode == 2) dp = fmaf(ld(tile_elem<T>(Dt, nc, tq, tc, r, h * HD + c)), vel(row, c), dp);
-      }
-      const float p = __expf(s * scale - stat(r, 0));
-      if (mode == 2) {
-        const float ds = p * (dp - stat(r, 1)) * scale;
-#pragma unroll 8
-        for (int c = 0; c < HD; ++c) acc[c] = fmaf(ds, ld(tile_elem<T>(Qt, nc, tq, tc, r, h * HD + c)), acc[c]);
-      } else {
-#pragma unroll 8
-        for (int c = 0; c < HD; ++c) acc[c] = fmaf(p, ld(tile_elem<T>(Dt, nc, tq, tc, r, h * HD + c)), acc[c]);
-      }
-    }
-    T* out = (T*)d.out + (size_t)row * gw + h * HD;
-#pragma unroll 8
-    for (int c = 0; c < HD; ++c) st(out + c, acc[c]);
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
 // MFMA attention backward (bf16 storage, V given as plain [keys, columns] tiles).
 //
 // Modes 0 (statistics) and 1 (dQ): one workgroup = one head x 128 queries, a wavefront owns 32
@@ -1939,28 +1754,8 @@ hipError_t launch_batch(int cls, int dtype, int head_dim, const DeviceTables& t,
     case LC_ATTN_BWD_BF16_DK: TN_LAUNCH_ATTN_BWD(2); break;
     case LC_ATTN_BWD_BF16_DV: TN_LAUNCH_ATTN_BWD(3); break;
 #undef TN_LAUNCH_ATTN_BWD
-    case LC_ATTN_BWD:
-      if (head_dim == 64) {
-        if (bf) hipLaunchKernelGGL((attn_bwd_kernel<bf16_t, 64>), grid, dim3(64), 0, s, t, b);
-        else hipLaunchKernelGGL((attn_bwd_kernel<float, 64>), grid, dim3(64), 0, s, t, b);
-      } else if (head_dim == 128) {
-        if (bf) hipLaunchKernelGGL((attn_bwd_kernel<bf16_t, 128>), grid, dim3(64), 0, s, t, b);
-        else hipLaunchKernelGGL((attn_bwd_kernel<float, 128>), grid, dim3(64), 0, s, t, b);
-      } else {
-        return hipErrorInvalidValue;
-      }
-      break;
-    case LC_ATTN_F32:
-      if (head_dim == 64) {
-        if (bf) hipLaunchKernelGGL((attn_generic_kernel<bf16_t, 64>), grid, dim3(64), 0, s, t, b);
-        else hipLaunchKernelGGL((attn_generic_kernel<float, 64>), grid, dim3(64), 0, s, t, b);
-      } else if (head_dim == 128) {
-        if (bf) hipLaunchKernelGGL((attn_generic_kernel<bf16_t, 128>), grid, dim3(64), 0, s, t, b);
-        else hipLaunchKernelGGL((attn_generic_kernel<float, 128>), grid, dim3(64), 0, s, t, b);
-      } else {
-        return hipErrorInvalidValue;
-      }
-      break;
+    case LC_ATTN_BWD: return launch_attn_f32(true, dtype, head_dim, t, b, max_blocks, s);
+    case LC_ATTN_F32: return launch_attn_f32(false, dtype, head_dim, t, b, max_blocks, s);
     case LC_ATTN_BF16:
       if (head_dim == 64) {
         hipLaunchKernelGGL(attn_bf16_kernel<64>, grid, wg, 4 * 64 * 64 * 2, s, t, b);

@@ -1,0 +1,109 @@
+"""The attention kernels with fp32 products (fp32 graphs, and bf16 tilings the bf16 kernels do not take),
+at the edges of their 64-row chunks and 16-row wavefronts and over every layout of the tile grid,
+against float64.  Tolerances: the repository's 1e-4 for fp32 results (sums of at most a few hundred
+fp32 products, measured 1e-6), 2e-2 where the result is stored as bf16 (half an ulp is 2^-9 of a value)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import llama_ref as R
+from oracle import tiled as T
+from paper_2405_16283_amd import binding as B
+
+from test_gpu_attention_block import _compare, _ranges
+from test_gpu_backward_ops import TOL, Graph
+
+pytestmark = pytest.mark.gpu
+
+
+def _grid(g, full, ranges, tc, transpose=False):
+    vs, wide = [], np.zeros(full.shape)
+    for r0, r1 in ranges:
+        for c0 in range(0, full.shape[1], tc):
+            v, w = g.inp(full[r0:r1, c0:c0 + tc].T if transpose else full[r0:r1, c0:c0 + tc])
+            vs.append(v)
+            wide[r0:r1, c0:c0 + tc] = w.T if transpose else w
+    return vs, wide
+
+
+FORWARD = [
+    # dtype, hd, hpg, tc, q_rows, kv_rows, tq, tk, q_pos0, k_pos0, causal, v_trans
+    ("f32", 64, 2, 128, 128, 128, 64, 64, 0, 0, 1, 1),      # two full chunks
+    ("f32", 128, 1, 128, 65, 129, 128, 128, 64, 0, 1, 1),   # one row, one key past a chunk
+    ("f32", 64, 1, 64, 15, 17, 64, 64, 2, 0, 1, 0),         # less than a wavefront's rows; V as plain tiles
+    ("f32", 128, 1, 32, 70, 90, 32, 32, 20, 0, 1, 1),       # a head across four column tiles
+    ("f32", 64, 1, 64, 100, 75, 100, 1, 0, 0, 0, 1),        # single-row key tiles
+    ("f32", 64, 1, 64, 48, 200, 48, 96, 80, 100, 1, 1),     # tiles that straddle chunks; rows that see nothing
+    ("bf16", 128, 2, 256, 130, 203, 128, 256, 73, 0, 1, 0),  # bf16, plain V
+    ("bf16", 64, 1, 64, 33, 77, 64, 48, 44, 0, 1, 1),       # bf16, key tiles of 48 rows, odd last tile
+]
+
+
+@pytest.mark.parametrize("case", FORWARD)
+def test_attention_block(case):
+    dtype, hd, hpg, tc, q_rows, kv_rows, tq, tk, q_pos0, k_pos0, causal, v_trans = case
+    print(f"[case] attn_block {case}", flush=True)
+    rng = np.random.default_rng(q_rows)
+    g = Graph(dtype)
+    gw = hpg * hd
+    qt, kt = _ranges(q_rows, tq), _ranges(kv_rows, tk)
+    q, Q = _grid(g, rng.standard_normal((q_rows, gw)), qt, tc)
+    k, K = _grid(g, rng.standard_normal((kv_rows, gw)), kt, tc)
+    v, V = _grid(g, rng.standard_normal((kv_rows, gw)), kt, tc, bool(v_trans))
+    p = dict(n_q_tiles=len(qt), n_kv_tiles=len(kt), n_col_tiles=gw // tc, head_dim=hd, q_pos0=q_pos0, k_pos0=k_pos0,
+             causal=causal, scale=1.0 / np.sqrt(hd), v_trans=v_trans)
+    blk = g.op(B.TN_OP_ATTN_BLOCK, q + k + v, q_rows, gw + 2 * hpg, f32=True, **p)
+    (got,) = g.run([blk])
+    ref = T._eval_vertex("attn_block", dict(p, n_q_tiles=1, n_kv_tiles=1, n_col_tiles=1, v_trans=0), [Q, K, V])
+    _compare(got, ref, gw, hd, hpg)
+
+
+BACKWARD = [
+    # dtype, hd, tc, q_rows, kv_rows, tq, tk, q_pos0, v_trans
+    ("f32", 64, 64, 160, 160, 64, 64, 0, 0),
+    ("f32", 128, 128, 65, 129, 65, 129, 64, 0),
+    ("f32", 64, 64, 17, 63, 17, 40, 46, 1),     # key tiles of 40 rows, V transposed
+    ("f32", 128, 32, 33, 70, 32, 32, 37, 0),    # a head across four column tiles
+    ("bf16", 128, 128, 131, 131, 128, 128, 0, 0),
+]
+
+
+@pytest.mark.parametrize("case", BACKWARD)
+def test_attention_reverse(case):
+    dtype, hd, tc, q_rows, kv_rows, tq, tk, q_pos0, v_trans = case
+    print(f"[case] attn_bwd {case}", flush=True)
+    rng = np.random.default_rng(kv_rows)
+    g = Graph(dtype)
+    hpg, scale = (2 if tc >= hd else 1), 1.0 / np.sqrt(hd)
+    gw = hpg * hd
+    qt, kt = _ranges(q_rows, tq), _ranges(kv_rows, tk)
+    q, Q = _grid(g, rng.standard_normal((q_rows, gw)), qt, tc)
+    k, K = _grid(g, rng.standard_normal((kv_rows, gw)), kt, tc)
+    v, V = _grid(g, rng.standard_normal((kv_rows, gw)), kt, tc, bool(v_trans))
+    do, DO = _grid(g, rng.standard_normal((q_rows, gw)), qt, tc)
+    nc = gw // tc
+    p = dict(n_q_tiles=len(qt), n_kv_tiles=len(kt), n_col_tiles=nc, head_dim=hd, q_pos0=q_pos0, k_pos0=0, causal=1, scale=scale,
+             v_trans=v_trans)
+    stats = []
+    for i, (r0, r1) in enumerate(qt):
+        ins = q[i * nc:(i + 1) * nc] + k + v + do[i * nc:(i + 1) * nc]
+        stats.append(g.op(B.TN_OP_ATTN_BWD, ins, r1 - r0, 2 * hpg, f32=True, mode=0, **dict(p, n_q_tiles=1, q_pos0=q_pos0 + r0)))
+    base = q + k + v + do + stats
+    outs = [g.op(B.TN_OP_ATTN_BWD, base, rows, gw, mode=m, **p) for m, rows in ((1, q_rows), (2, kv_rows), (3, kv_rows))]
+    got = g.run(stats + outs)
+    tq_, tk_, tv_ = (torch.tensor(a, requires_grad=True) for a in (Q, K, V))
+    mask = torch.arange(kv_rows)[None, :] > (q_pos0 + torch.arange(q_rows))[:, None]
+    loss, lse, dd = 0.0, [], []
+    for h in range(hpg):
+        sl = slice(h * hd, (h + 1) * hd)
+        s = (tq_[:, sl] @ tk_[:, sl].T * scale).masked_fill(mask, float("-inf"))
+        o = torch.softmax(s, dim=-1) @ tv_[:, sl]
+        loss = loss + (o * torch.tensor(DO[:, sl])).sum()
+        lse.append(torch.logsumexp(s, dim=-1).detach().numpy())
+        dd.append((o.detach().numpy() * DO[:, sl]).sum(axis=1))
+    loss.backward()
+    st = np.concatenate(got[:len(qt)], axis=0)
+    errs = [R.rel_err(st[:, :hpg], np.stack(lse, 1)), R.rel_err(st[:, hpg:], np.stack(dd, 1))]
+    errs += [R.rel_err(a, t.grad.numpy()) for a, t in zip(got[-3:], (tq_, tk_, tv_))]
+    print("  lse, D, dQ, dK, dV:", ", ".join(f"{e:.1e}" for e in errs), flush=True)
+    assert max(errs) < TOL[dtype]
