@@ -61,5 +61,20 @@ __device__ __forceinline__ const T* tile_elem_t(void* const* tiles, int nc, int 
   return (const T*)tiles[rt * nc + ct] + (size_t)(col - ct * t_cols) * pitch + (row - rt * t_rows);
 }
 
+// Workgroups are handed to the 8 XCDs round-robin in launch order, and each XCD has its own L2.
+// This turns the launch position into a position in which each XCD gets a contiguous run of
+// (vertex, tile) pairs, so that the workgroups sharing an L2 work on neighbouring tiles -- the
+// tiles of one vertex and of vertices with the same A row block -- instead of every XCD
+// streaming every operand.
+__device__ __forceinline__ void xcd_remap(int& bx, int& by) {
+  const int gx = gridDim.x, total = gx * gridDim.y;
+  const int n = blockIdx.x + gx * blockIdx.y;
+  const int xcd = n & 7, slot = n >> 3;
+  const int q = total >> 3, r = total & 7;
+  const int v = xcd * q + min(xcd, r) + slot;
+  by = v / gx;
+  bx = v - by * gx;
+}
+
 }  // namespace
 }  // namespace tn

@@ -29,7 +29,7 @@ struct OpDesc {
 
 // Launch classes: vertices of one class can share a launch.
 enum LaunchClass {
-  LC_GEMM_F32 = 0,   // generic fp32-accumulate GEMM on the vector ALUs, any layout, fp32 or bf16 storage
+  LC_GEMM_F32 = 0,   // GEMM with fp32 products, any layout, fp32 or bf16 storage
   LC_GEMM_BF16_NT,   // MFMA bf16 GEMM, B tiles stored [cols, K], 128x128 tile per workgroup
   LC_GEMM_BF16_NT256,  // the same for output tiles of at least 256x256: 256x256 per workgroup
   LC_RMS_STAT,
@@ -115,6 +115,10 @@ int32_t blocks_for(int cls, const OpDesc& d, const int32_t* aux);
 // type and (for attention) the head size.  max_blocks = largest nblocks in the batch.
 hipError_t launch_batch(int cls, int dtype, int head_dim, const DeviceTables& t, const Batch& b,
                         int32_t max_blocks, hipStream_t stream);
+
+// LC_GEMM_F32: gemm_f32.hip.
+constexpr int kGemmF32Tile = 32;  // output rows and columns per workgroup
+hipError_t launch_gemm_f32(int dtype, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t stream);
 
 // LC_ATTN_F32 (reverse == false) and LC_ATTN_BWD: attn_f32.hip.
 hipError_t launch_attn_f32(bool reverse, int dtype, int head_dim, const DeviceTables& t, const Batch& b, int32_t max_blocks,

@@ -498,85 +498,6 @@ __global__ void __launch_bounds__(256) transpose_kernel(DeviceTables t, Batch b)
 }
 
 // ---------------------------------------------------------------------------------------------
-// generic GEMM on the vector ALUs (fp32 accumulate): 64x64 output tile per workgroup
-// ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256) gemm_generic_kernel(DeviceTables t, Batch b) {
-  const OpDesc& d = t.descs[b.at(blockIdx.y)];
-  if ((int)blockIdx.x >= d.nblocks) return;
-  __shared__ float As[16][68];
-  __shared__ float Bs[16][68];
-  const int M = d.rows, N = d.cols, nk = d.p.nk;
-  const int tn_ = (N + 63) / 64;
-  const int m0 = (blockIdx.x / tn_) * 64, n0 = (blockIdx.x % tn_) * 64;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  float acc[4][4] = {};
-  float gate[4][4];  // mode 2: the first of the two products, while the second is formed
-  for (int pass = 0; pass < (d.p.mode == 2 ? 2 : 1); ++pass) {
-  if (pass == 1) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { gate[i][j] = acc[i][j]; acc[i][j] = 0.f; }
-  }
-  for (int kt = 0; kt < nk; ++kt) {
-    const T* A = (const T*)t.ptrs[d.ptr0 + kt];
-    const T* B = (const T*)t.ptrs[d.ptr0 + (1 + pass) * nk + kt];
-    const int K = t.aux[d.aux0 + kt];
-    for (int k0 = 0; k0 < K; k0 += 16) {
-      {
-        const int r = threadIdx.x / 4, kk = (threadIdx.x % 4) * 4;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int gr = m0 + r, gk = k0 + kk + i;
-          As[kk + i][r] = (gr < M && gk < K) ? ld(d.p.trans_a ? A + (size_t)gk * M + gr : A + (size_t)gr * K + gk) : 0.f;
-        }
-        if (d.trans_b) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int gc = n0 + r, gk = k0 + kk + i;
-            Bs[kk + i][r] = (gc < N && gk < K) ? ld(B + (size_t)gc * K + gk) : 0.f;
-          }
-        } else {
-          const int kr = threadIdx.x / 16, cc = (threadIdx.x % 16) * 4;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int gc = n0 + cc + i, gk = k0 + kr;
-            Bs[kr][cc + i] = (gc < N && gk < K) ? ld(B + (size_t)gk * N + gc) : 0.f;
-          }
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        float a[4], bb[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { a[i] = As[k][ty * 4 + i]; bb[i] = Bs[k][tx * 4 + i]; }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], bb[j], acc[i][j]);
-      }
-      __syncthreads();
-    }
-  }
-  }
-  T* Cp = (T*)d.out;
-  const T* R = d.p.mode == 1 ? (const T*)t.ptrs[d.ptr0 + 2 * nk] : nullptr;  // the residual operand
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = m0 + ty * 4 + i, c = n0 + tx * 4 + j;
-      if (r >= M || c >= N) continue;
-      float v = acc[i][j];
-      if (d.p.mode == 1) v += ld(R + (size_t)r * N + c);
-      if (d.p.mode == 2) v = gate[i][j] / (1.f + __expf(-gate[i][j])) * v;
-      st(d.p.trans_c ? Cp + (size_t)c * M + r : Cp + (size_t)r * N + c, v);
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
 // MFMA bf16 GEMM, C[M,N] = sum_k A_k[M,K_k] * B_k[N,K_k]^T, fp32 accumulate, bf16 store.
 // 128x128 output tile per workgroup of 4 wavefronts (2x2, 64x64 each = 2x2 MFMA 32x32 tiles),
 // K step 64 staged through LDS.  Rows are padded by 8 elements so that the 16-byte fragment
@@ -801,22 +722,7 @@ __device__ __forceinline__ int sload_int(const int* addr) {
   return v;
 }
 
-// Workgroups are handed to the 8 XCDs round-robin in launch order, and each XCD has its own L2.
-// This turns the launch position into a position in which each XCD gets a contiguous run of
-// (vertex, tile) pairs, so that the workgroups sharing an L2 work on neighbouring tiles -- the
-// tiles of one vertex and of vertices with the same A row block -- instead of every XCD
-// streaming every operand.
-__device__ __forceinline__ void xcd_remap(int& bx, int& by) {
-  const int gx = gridDim.x, total = gx * gridDim.y;
-  const int n = blockIdx.x + gx * blockIdx.y;
-  const int xcd = n & 7, slot = n >> 3;
-  const int q = total >> 3, r = total & 7;
-  const int v = xcd * q + min(xcd, r) + slot;
-  by = v / gx;
-  bx = v - by * gx;
-}
-
-// The same idea for kernels whose workgroups of one vertex share operands (the query blocks of an
+// The idea of xcd_remap for kernels whose workgroups of one vertex share operands (the query blocks of an
 // attention head all read that head's keys and values): vertex by goes to XCD by % 8 as a whole,
 // and vertices that differ in cost (blocks on and off the diagonal) stay spread over the XCDs.
 __device__ __forceinline__ void xcd_remap_rows(int& bx, int& by) {
@@ -1619,7 +1525,7 @@ static inline int32_t cdiv(int64_t a, int64_t b) { return (int32_t)((a + b - 1) 
 
 int32_t blocks_for(int cls, const OpDesc& d, const int32_t* aux) {
   switch (cls) {
-    case LC_GEMM_F32: return cdiv(d.rows, 64) * cdiv(d.cols, 64);
+    case LC_GEMM_F32: return cdiv(d.rows, kGemmF32Tile) * cdiv(d.cols, kGemmF32Tile);
     case LC_GEMM_BF16_NT: return cdiv(d.rows, GB_M) * cdiv(d.cols, GB_N);
     case LC_GEMM_BF16_NT256: return cdiv(d.rows, 256) * cdiv(d.cols, d.p.mode == 2 ? 128 : 256);
     case LC_RMS_STAT: return cdiv(d.rows, 4);
@@ -1701,7 +1607,7 @@ hipError_t launch_batch(int cls, int dtype, int head_dim, const DeviceTables& t,
     else hipLaunchKernelGGL(kernel<float>, grid, wg, 0, s, t, b);               \
   } while (0)
   switch (cls) {
-    case LC_GEMM_F32: TN_LAUNCH_T(gemm_generic_kernel); break;
+    case LC_GEMM_F32: return launch_gemm_f32(dtype, t, b, max_blocks, s);
     case LC_GEMM_BF16_NT: hipLaunchKernelGGL(gemm_bf16_nt_kernel, grid, wg, 0, s, t, b); break;
     case LC_GEMM_BF16_NT256: {
       static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_bf16_nt256_kernel<TN_GEMM_WAVES, 4>,

@@ -1,0 +1,52 @@
+"""Tile products of the kernels made for small tiles, at the edges of their 32x32 workgroups, of their pieces
+along K and of the shares of their four wavefronts, over every layout of the GEMM vertex, against float64.
+Tolerance: products summed in fp32 differ from float64 by less than K 2^-24 of the sum of their magnitudes, and for
+random operands by far less than K 2^-24 of the result in the 2-norm; a bf16 result adds half a unit of 2^-8."""
+import numpy as np
+import pytest
+
+from oracle import llama_ref as R
+from oracle import tiled as T
+from paper_2405_16283_amd import binding as B
+
+from test_gpu_backward_ops import Graph
+
+pytestmark = pytest.mark.gpu
+
+
+def _product(dtype, m, n, ks, ta=0, tb=1, tc=0, mode=0):
+    print(f"[case] gemm {dtype} {m}x{n} K {ks} trans {ta}{tb}{tc} mode {mode}", flush=True)
+    rng = np.random.default_rng(m * 1000 + n + sum(ks))
+    g = Graph(dtype)
+    scale = 1.0 / np.sqrt(sum(ks))
+    a = [g.inp(rng.standard_normal((k, m) if ta else (m, k))) for k in ks]
+    b = [[g.inp(rng.standard_normal((n, k) if tb else (k, n)) * scale) for k in ks] for _ in range(2 if mode == 2 else 1)]
+    extra = [g.inp(rng.standard_normal((m, n)))] if mode == 1 else []
+    ins = a + sum(b, []) + extra
+    p = dict(nk=len(ks), trans_a=ta, trans_b=tb, trans_c=tc, mode=mode)
+    v = g.op(B.TN_OP_GEMM, [i[0] for i in ins], n if tc else m, m if tc else n, **p)
+    (got,) = g.run([v])
+    wide = [i[1].T if ta and q < len(ks) else i[1] for q, i in enumerate(ins)]  # the oracle holds A plain
+    ref = T._eval_vertex("gemm", p, wide)
+    err = R.rel_err(got, ref)
+    bound = sum(ks) * 2.0 ** -24 + (2.0 ** -8 if dtype == "bf16" else 0.0)
+    print(f"  rel err {err:.2e} (bound {bound:.1e})", flush=True)
+    assert np.isfinite(got).all() and err < bound
+
+
+F32 = [
+    ((1, 1, [1]), {}), ((32, 32, [32]), {}), ((33, 31, [36, 4]), {}), ((64, 64, [64, 64, 64, 64]), {}),
+    ((40, 72, [96, 128, 20]), {}), ((31, 65, [35, 7]), {}),         # rows along K not aligned to four elements
+    ((256, 192, [256, 256]), {}), ((70, 45, [672]), {}),            # 21 pieces: five and six per wavefront
+    ((16, 64, [33, 64]), dict(ta=1)), ((50, 34, [64, 40]), dict(ta=1, tb=0)), ((35, 66, [70]), dict(tb=0)),
+    ((64, 37, [64, 32]), dict(tc=1)), ((37, 64, [416]), dict(ta=1, tb=0, tc=1)),
+    ((33, 40, [64, 16]), dict(mode=1)), ((40, 33, [224]), dict(mode=2)),
+]
+
+
+@pytest.mark.parametrize("shape,kw", F32)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_any_layout_with_fp32_products(dtype, shape, kw):
+    if dtype == "bf16" and kw.get("tb", 1) and not kw.get("ta", 0) and all(k % 8 == 0 for k in shape[2]):
+        pytest.skip("taken by the bf16 kernels")
+    _product(dtype, *shape, **kw)
