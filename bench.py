@@ -434,7 +434,7 @@ def main():
         subs.append("c2_capped40")
 
     rec, cfg, full, y = run_case(head_name, args.steps, args.warmup, headline=True)
-    gemm_kernel = "gemm_bf16_nt256_kernel" if cfg.dtype == "bf16" else "gemm_f32_kernel"
+    gemm_kernel = "gemm_bf16_nt256_kernel" if cfg.dtype == "bf16" else "gemm_small_kernel"
     config_keys = ("workload", "gpu_cap_bytes", "distinct_layers", "kv_outputs", "outputs", "serial_order", "memgraph", "exec")
     top_keys = config_keys + ("host_link", "mfma", "gpu_idle_frac", "tokens_per_s", "ms_per_step", "steps", "warmup")
     line = {

@@ -42,6 +42,7 @@ struct VInfo {
   int16_t group = -1;  // index of its (cls, dtype, head_dim, depth) combination: vertices of one group can share a launch
   int32_t desc = -1;
   int32_t nblocks = 0;
+  int32_t row_key = -1;  // single-row products: vertices with one key multiply the same B tiles
   int64_t lock = -1;  // increments: the vertex whose output they add to; one of them runs at a time
   double flops = 0, bytes = 0;
 };
@@ -212,6 +213,7 @@ tn_status build_tables(tn_executor& ex) {
   std::vector<int32_t> aux;
   std::vector<double> theta;
   std::map<std::pair<int32_t, uint32_t>, int32_t> theta_at;
+  std::map<std::vector<int64_t>, int32_t> row_keys;  // single-row products: B operands and mode -> key
   ex.info.assign(nv, VInfo{});
   auto addr = [&](int64_t m, uint64_t need, void** out) -> tn_status {
     const MVertex& o = mg.v[m];
@@ -247,7 +249,7 @@ tn_status build_tables(tn_executor& ex) {
     switch (x.op_kind) {
       case TN_OP_GEMM: {
         if (x.p.trans_c) std::swap(d.rows, d.cols);  // the kernels work on the logical [rows, cols] product
-        bool mfma = d.dtype == TN_BF16 && d.trans_b && !x.p.trans_a, k32 = true;
+        bool mfma = d.dtype == TN_BF16 && d.trans_b && (!x.p.trans_a || d.rows == 1), k32 = true, k4 = true;
         double K = 0;
         for (int k = 0; k < x.p.nk; ++k) {
           const int32_t kk = x.p.trans_a ? odesc(k).rows : odesc(k).cols;
@@ -255,12 +257,26 @@ tn_status build_tables(tn_executor& ex) {
           K += kk;
           if (kk % 8) mfma = false;
           if (kk % 32) k32 = false;
+          if (kk % 4) k4 = false;
         }
         const bool big = k32 && d.rows >= 256 && d.cols >= 256;
         // the fused forms (mode 1: + residual, mode 2: gated pair) exist in the 256-tile kernel, which clamps its
         // loads and guards its stores for any shape, and in the generic one, which the thinnest products take
         const bool fused_mfma = x.p.mode != 0 && k32 && d.rows >= 64;
-        vi.cls = !mfma ? LC_GEMM_F32 : (big || fused_mfma) ? LC_GEMM_BF16_NT256 : x.p.mode != 0 ? LC_GEMM_F32 : LC_GEMM_BF16_NT;
+        // Small outputs leave a 128x128 workgroup mostly empty and alone with its walk along K.  Measured at K of 4096,
+        // 32x32 tiles against 128x128 ones: 32 products of 512x16, 28 against 59 us, two of them 15 against 56; 8 of
+        // 16x512 with K of 16384, 53 against 223; 64x64 with K of 512, 64 of them, 5.7 against 13.  From 128x128 up the
+        // larger tile's reuse wins once a launch holds more than 64 (256 of them: 120 against 43).
+        const bool small = std::min(d.rows, d.cols) <= 32 || (int64_t)d.rows * d.cols <= 64 * 128;
+        vi.cls = !mfma ? LC_GEMM_F32 : (big || fused_mfma) ? LC_GEMM_BF16_NT256 : (small || x.p.mode != 0) ? LC_GEMM_BF16_SMALL : LC_GEMM_BF16_NT;
+        // Single rows against the same B tiles are formed together (32 rows against 24 tiles of 512 with K of 4096: 486
+        // us one by one, B coming from the caches for every one of them).
+        if (d.rows == 1 && d.trans_b && (d.dtype == TN_BF16 ? mfma : k4)) {
+          vi.cls = LC_GEMM_ROWS;
+          std::vector<int64_t> key(x.operands.begin() + x.p.nk, x.operands.begin() + (x.p.mode == 2 ? 3 : 2) * x.p.nk);
+          key.push_back(x.p.mode);
+          vi.row_key = row_keys.emplace(std::move(key), (int32_t)row_keys.size()).first->second;
+        }
         vi.flops = (x.p.mode == 2 ? 4.0 : 2.0) * d.rows * d.cols * K;
         // Products of very different depth do not share a launch.  The workgroups of a launch that run at the same
         // time read the same operand panels at the same moment only as long as they walk along K in step, and that
@@ -538,6 +554,8 @@ bool device_visible_host(tn_executor& ex, const void* p, uint64_t bytes, bool* o
 int family_of(int cls) {
   switch (cls) {
     case LC_GEMM_F32:
+    case LC_GEMM_BF16_SMALL:
+    case LC_GEMM_ROWS:
     case LC_GEMM_BF16_NT:
     case LC_GEMM_BF16_NT256: return 0;
     case LC_ATTN_F32:
@@ -898,6 +916,8 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   int xring[2] = {0, 0};
   const int xdepth = std::max(1, std::min<int>(opt.transfer_depth > 0 ? opt.transfer_depth : 3, kMaxQueueDepth));
   std::vector<int64_t> same, xverts, sort_b, stage_verts;
+  std::vector<RowVertex> row_list;
+  row_list.reserve(max_batch);
   std::vector<uint64_t> stage_sizes, stage_run, stage_tmp_s;
   std::vector<size_t> stage_ord;
   std::vector<int64_t> stage_tmp_v;
@@ -1285,7 +1305,14 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
         max_blocks *= 4;
         n_blocks *= 4;
       }
-      if (e == hipSuccess) e = launch_batch(launch_cls, lead.dtype, lead.head_dim, tables, batch, max_blocks, stream);
+      if (e == hipSuccess && lead.cls == LC_GEMM_ROWS) {
+        row_list.clear();
+        for (int64_t m : same) row_list.push_back({ex->info[m].row_key, (uint32_t)ex->info[m].desc});
+        std::sort(row_list.begin(), row_list.end(), [](const RowVertex& a, const RowVertex& b) { return a.key < b.key; });
+        e = launch_gemm_rows(lead.dtype, tables, batch.base, row_list.data(), batch.n, max_blocks, stream);
+      } else if (e == hipSuccess) {
+        e = launch_batch(launch_cls, lead.dtype, lead.head_dim, tables, batch, max_blocks, stream);
+      }
       // a timed launch completes with its second stamp: one event record less between two kernels
       if (grp.prof >= 0) grp.done = ex->prof_events[grp.prof + 1];
       if (e == hipSuccess) e = hipEventRecord(grp.done, stream);

@@ -30,6 +30,8 @@ struct OpDesc {
 // Launch classes: vertices of one class can share a launch.
 enum LaunchClass {
   LC_GEMM_F32 = 0,   // GEMM with fp32 products, any layout, fp32 or bf16 storage
+  LC_GEMM_BF16_SMALL,  // MFMA bf16 GEMM for small or thin products, B tiles stored [cols, K], 32x32 tile per workgroup
+  LC_GEMM_ROWS,      // single-row products, either type (see launch_gemm_rows)
   LC_GEMM_BF16_NT,   // MFMA bf16 GEMM, B tiles stored [cols, K], 128x128 tile per workgroup
   LC_GEMM_BF16_NT256,  // the same for output tiles of at least 256x256: 256x256 per workgroup
   LC_RMS_STAT,
@@ -116,9 +118,19 @@ int32_t blocks_for(int cls, const OpDesc& d, const int32_t* aux);
 hipError_t launch_batch(int cls, int dtype, int head_dim, const DeviceTables& t, const Batch& b,
                         int32_t max_blocks, hipStream_t stream);
 
-// LC_GEMM_F32: gemm_f32.hip.
-constexpr int kGemmF32Tile = 32;  // output rows and columns per workgroup
-hipError_t launch_gemm_f32(int dtype, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t stream);
+// LC_GEMM_F32 and LC_GEMM_BF16_SMALL: gemm_small.hip.
+constexpr int kGemmSmallTile = 32;  // output rows and columns per workgroup
+hipError_t launch_gemm_small(bool bf16_products, int dtype, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t stream);
+
+// LC_GEMM_ROWS: products of a single row whose B tiles are stored [cols, K], with rows along K aligned to 16 bytes.
+// Vertices with one key multiply the same B tiles; those that stand next to each other in the list are formed
+// together, B read once.  (A row's bits do not depend on its company.)  base: the smallest descriptor index of the list.
+struct RowVertex {
+  int32_t key;
+  uint32_t desc;
+};
+hipError_t launch_gemm_rows(int dtype, const DeviceTables& t, uint32_t base, const RowVertex* rows, int n, int32_t max_blocks,
+                            hipStream_t stream);
 
 // LC_ATTN_F32 (reverse == false) and LC_ATTN_BWD: attn_f32.hip.
 hipError_t launch_attn_f32(bool reverse, int dtype, int head_dim, const DeviceTables& t, const Batch& b, int32_t max_blocks,

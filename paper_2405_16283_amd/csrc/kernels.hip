@@ -1525,7 +1525,9 @@ static inline int32_t cdiv(int64_t a, int64_t b) { return (int32_t)((a + b - 1) 
 
 int32_t blocks_for(int cls, const OpDesc& d, const int32_t* aux) {
   switch (cls) {
-    case LC_GEMM_F32: return cdiv(d.rows, kGemmF32Tile) * cdiv(d.cols, kGemmF32Tile);
+    case LC_GEMM_F32:
+    case LC_GEMM_BF16_SMALL: return cdiv(d.rows, kGemmSmallTile) * cdiv(d.cols, kGemmSmallTile);
+    case LC_GEMM_ROWS: return cdiv(d.cols, kGemmSmallTile);
     case LC_GEMM_BF16_NT: return cdiv(d.rows, GB_M) * cdiv(d.cols, GB_N);
     case LC_GEMM_BF16_NT256: return cdiv(d.rows, 256) * cdiv(d.cols, d.p.mode == 2 ? 128 : 256);
     case LC_RMS_STAT: return cdiv(d.rows, 4);
@@ -1607,7 +1609,8 @@ hipError_t launch_batch(int cls, int dtype, int head_dim, const DeviceTables& t,
     else hipLaunchKernelGGL(kernel<float>, grid, wg, 0, s, t, b);               \
   } while (0)
   switch (cls) {
-    case LC_GEMM_F32: return launch_gemm_f32(dtype, t, b, max_blocks, s);
+    case LC_GEMM_F32:
+    case LC_GEMM_BF16_SMALL: return launch_gemm_small(cls == LC_GEMM_BF16_SMALL, dtype, t, b, max_blocks, s);
     case LC_GEMM_BF16_NT: hipLaunchKernelGGL(gemm_bf16_nt_kernel, grid, wg, 0, s, t, b); break;
     case LC_GEMM_BF16_NT256: {
       static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_bf16_nt256_kernel<TN_GEMM_WAVES, 4>,

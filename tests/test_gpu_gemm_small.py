@@ -50,3 +50,38 @@ def test_any_layout_with_fp32_products(dtype, shape, kw):
     if dtype == "bf16" and kw.get("tb", 1) and not kw.get("ta", 0) and all(k % 8 == 0 for k in shape[2]):
         pytest.skip("taken by the bf16 kernels")
     _product(dtype, *shape, **kw)
+
+
+BF16 = [
+    ((16, 512, [512, 512]), {}), ((512, 16, [256, 8]), {}), ((33, 31, [64, 24]), {}), ((64, 128, [200]), {}),
+    ((20, 300, [1344]), {}), ((70, 30, [64, 64]), dict(tc=1)), ((65, 64, [136]), dict(mode=1)), ((40, 100, [72]), dict(mode=2)),
+]
+
+
+@pytest.mark.parametrize("shape,kw", BF16)
+def test_small_and_thin_bf16_products(shape, kw):
+    _product("bf16", *shape, **kw)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,n,ks,mode", [(1, 64, [64], 0), (33, 100, [512, 512, 40], 0), (32, 34, [64] * 9, 1),
+                                            (70, 48, [128, 8], 2), (5, 256, [1024, 1024], 0)])
+def test_single_rows_formed_together(dtype, rows, n, ks, mode):
+    """`rows` single-row vertices, all but the last against one set of B tiles (70: three groups), the last against its own."""
+    print(f"[case] rows {dtype} {rows} n {n} K {ks} mode {mode}", flush=True)
+    rng = np.random.default_rng(rows + n)
+    g = Graph(dtype)
+    sets = 2 if mode == 2 else 1
+    b = [[g.inp(rng.standard_normal((n, k)) / np.sqrt(sum(ks))) for _ in range(sets) for k in ks] for _ in range(2)]
+    p = dict(nk=len(ks), trans_b=1, mode=mode)
+    outs, refs = [], []
+    for r in range(rows):
+        own = b[1 if r + 1 == rows and rows > 1 else 0]
+        ins = [g.inp(rng.standard_normal((1, k))) for k in ks] + own + ([g.inp(rng.standard_normal((1, n)))] if mode == 1 else [])
+        outs.append(g.op(B.TN_OP_GEMM, [i[0] for i in ins], 1, n, **p))
+        refs.append(T._eval_vertex("gemm", p, [i[1] for i in ins]))
+    got = np.concatenate(g.run(outs))
+    err = R.rel_err(got, np.concatenate(refs))
+    bound = sum(ks) * 2.0 ** -24 + (2.0 ** -8 if dtype == "bf16" else 0.0)
+    print(f"  rel err {err:.2e} (bound {bound:.1e})", flush=True)
+    assert np.isfinite(got).all() and err < bound
