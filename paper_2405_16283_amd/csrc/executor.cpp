@@ -720,13 +720,51 @@ tn_status tn_executor_place_inputs(tn_executor* ex, const void* const* host_inpu
   if (ex->poisoned) return fail(TN_ERR_HIP, "executor is poisoned by an earlier HIP error");
   const MemGraph& mg = *ex->mg;
   hipStream_t s = ex->slots[ex->n_compute].stream;
+  // Sources in memory of this GPU are copied by grouped launches (a copy call per tile spends 2.5 us on each: 2.0 ms for
+  // the 784 weight tiles of a 7B-shaped layer, against 0.2 ms); everything else is left to the runtime, which
+  // is told to find out where it lies.
+  int dev = -1;
+  TN_HIP(hipGetDevice(&dev));
+  hipPointerAttribute_t own{};
+  if (hipPointerGetAttributes(&own, ex->dbase) != hipSuccess || own.type != hipMemoryTypeDevice || own.device != dev) {
+    (void)hipGetLastError();  // the calling thread works on another GPU: no launches from here
+    dev = -1;
+  }
+  const char *lo = nullptr, *hi = nullptr;  // the allocation the last source was found in
+  auto on_this_gpu = [&](const char* p, uint64_t bytes) {
+    if (dev < 0 || (uintptr_t)p % 16 || bytes > INT32_MAX) return false;
+    if (!(lo && p >= lo && p + bytes <= hi)) {
+      hipPointerAttribute_t at{};
+      void* base = nullptr;
+      size_t size = 0;
+      if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice || at.device != dev ||
+          hipMemGetAddressRange((hipDeviceptr_t*)&base, &size, (hipDeviceptr_t)p) != hipSuccess || !base) {
+        (void)hipGetLastError();
+        return false;
+      }
+      lo = (const char*)base;
+      hi = lo + size;
+    }
+    return p >= lo && p + bytes <= hi && (p + bytes <= ex->dbase || p >= ex->dbase + ex->dbytes);
+  };
+  CopyBatch copies;
+  copies.n = copies.total_blocks = 0;
   for (int64_t m = 0; m < mg.n_task; ++m) {
     const MVertex& x = mg.v[m];
     if (x.kind != TN_MG_INPUT) continue;
     if (!host_inputs[m]) return fail(TN_ERR_INVALID, "no host buffer for device-resident input %lld", (long long)m);
-    // the source may be host memory or (a tensor another kernel left there) GPU memory: let the runtime tell
+    if (on_this_gpu((const char*)host_inputs[m], x.bytes)) {
+      copies.it[copies.n++] = {host_inputs[m], ex->dbase + x.offset, (uint32_t)x.bytes, (uint32_t)copies.total_blocks};
+      copies.total_blocks += (int32_t)((x.bytes + kCopyBlockBytes - 1) / kCopyBlockBytes);
+      if (copies.n == kMaxCopies) {
+        TN_HIP(launch_device_copies(copies, s));
+        copies.n = copies.total_blocks = 0;
+      }
+      continue;
+    }
     TN_HIP(hipMemcpyAsync(ex->dbase + x.offset, host_inputs[m], x.bytes, hipMemcpyDefault, s));
   }
+  TN_HIP(launch_device_copies(copies, s));
   TN_HIP(hipStreamSynchronize(s));
   return TN_OK;
 }
@@ -1065,9 +1103,8 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       if (early_prof >= 0) xg.prof = early_prof;
       else if (e == hipSuccess && opt.profile && prof_pair(&xg.prof)) e = hipEventRecord(ex->prof_events[xg.prof], sl.stream);
       if (e == hipSuccess && use_copy_kernel) {
-        const int wgs = inside_gpu ? kDeviceCopyWorkgroups
-                        : (dir == 1 && opt.d2h_workgroups > 0) ? opt.d2h_workgroups : opt.copy_workgroups;
-        e = launch_copies(copies, wgs, sl.stream);
+        const int wgs = (dir == 1 && opt.d2h_workgroups > 0) ? opt.d2h_workgroups : opt.copy_workgroups;
+        e = inside_gpu ? launch_device_copies(copies, sl.stream) : launch_copies(copies, wgs, sl.stream);
       }
       if (e == hipSuccess && !stage_verts.empty()) {
         // adjacent arena slots for the gathered offloads (the largest free block was checked to suffice, and

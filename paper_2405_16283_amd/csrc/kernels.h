@@ -88,7 +88,8 @@ constexpr int kCopyThreads = 1024;
 constexpr int kCopyLoads = 2;  // 16-byte loads in flight per lane
 constexpr uint32_t kCopyBlockBytes = kCopyLoads * 16 * kCopyThreads;  // bytes one workgroup moves per step: 32 KiB
 constexpr int kDefaultCopyWorkgroups = 8;
-constexpr int kDeviceCopyWorkgroups = 512;  // copies that stay inside GPU memory: two per compute unit
+constexpr int kDeviceCopyThreads = 512;  // copies that stay inside GPU memory
+constexpr int kDeviceCopyPieces = 1024;  // workgroups per tensor at most
 struct CopyItem {
   const void* src;
   void* dst;
@@ -102,6 +103,8 @@ struct CopyBatch {
 };
 // max_workgroups <= 0 selects kDefaultCopyWorkgroups
 hipError_t launch_copies(const CopyBatch& b, int max_workgroups, hipStream_t stream);
+// every source and destination in memory of this GPU, 16-byte aligned
+hipError_t launch_device_copies(const CopyBatch& b, hipStream_t stream);
 
 // A region of GPU memory that exists from the moment the library is loaded until the process ends,
 // for callers that want the operand tables of a run somewhere nobody has to allocate.  Each GPU

@@ -4,6 +4,7 @@ the store and load vertices are copies inside GPU memory.  The bits must be thos
 goes through pinned host memory, with either copy engine, and the oracle's."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import llama_ref as R
 from oracle import tiled as T
@@ -80,5 +81,27 @@ def test_an_output_buffer_inside_the_device_buffer_is_refused():
             B.tn_execute(s.ex, s.in_ptrs, B.ptr_array(bad), None)
         out, rep = s.run()  # the executor is still usable
         assert rep.n_vertices == s.stats.n_vertices
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("shift", [0, 4, 16])
+def test_inputs_are_placed_from_gpu_memory_of_any_alignment(shift):
+    """Sources that the grouped copies do not take (not 16-byte aligned) go through the runtime; ragged tile sizes."""
+    cfg = config("ragged_f32").with_(weights_resident=True, x_resident=True)
+    full = make_llama_inputs(cfg, 0)
+    print(f"[case] ragged_f32 inputs placed from GPU memory, {shift} bytes off", flush=True)
+    s = H.GpuSession(cfg, full, cap=64 << 20, device_inputs=True)
+    try:
+        want, _ = s.run()
+        slab = torch.zeros(s.in_slab.numel() + 64, dtype=torch.uint8, device="cuda:0")
+        slab[shift:shift + s.in_slab.numel()] = s.in_slab
+        torch.cuda.synchronize()
+        moved = slab.data_ptr() + shift - s.in_slab.data_ptr()
+        s.in_ptrs = B.ptr_array([p + moved if p else 0 for p in s.in_ptrs])
+        s.dev.fill_(0xFF)
+        torch.cuda.synchronize()
+        out, _ = s.run()
+        np.testing.assert_array_equal(out["y"], want["y"])
     finally:
         s.close()
