@@ -482,7 +482,10 @@ typedef struct {
   int32_t queue_depth;   /* kernel groups in flight per compute stream (1..8; 0 = 1).  1: a kernel is
                             launched when its dependencies have completed.  >1: it may be enqueued once the
                             kernels it depends on are enqueued, ordered on the device by stream events;
-                            dependencies on transfers are always awaited on the host. */
+                            dependencies on transfers are awaited on the host, except that with a single
+                            compute stream small copies between kernels (512 KiB per group, no injected
+                            delay, not TN_POLICY_IN_ORDER) are enqueued on that stream among them, where
+                            launches that are over within microseconds do not count towards the depth. */
   int32_t transfer_depth;  /* groups of copies in flight per direction (1..8; 0 = 3): the next group is enqueued
                               while the host has not yet seen the previous one complete */
   int32_t copy_workgroups; /* TN_COPY_KERNEL: workgroups of a copy launch (each walks over 32 KiB pieces of the

@@ -10,8 +10,9 @@
 // polling one HIP event per stream from the loop thread (no callback thread); a stream carries
 // one *group* at a time, where a group is up to `max_batch` ready vertices of the same kernel
 // family served by a single grouped launch (a 512x512 tile cannot fill 256 compute units on its
-// own, and a launch costs more than such a tile's run time); the operand tables the kernels read
-// are built once at creation, since locations never change.
+// own, and a launch costs more than such a tile's run time); with one compute stream, small copies
+// between kernels run on that stream, so that the host is not asked between them; the operand tables
+// the kernels read are built once at creation, since locations never change.
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
@@ -32,6 +33,7 @@ namespace {
 
 using Clock = std::chrono::steady_clock;
 constexpr int kMaxQueueDepth = 8;  // groups in flight per compute stream, at most
+constexpr int kMaxChain = 24;      // the same where transfers are chained between kernels (see `chain` in run_memgraph)
 constexpr int64_t kMaxProfEvents = (1 << 17) + 1;  // timing events per executor: 65536 timed launches per run
 
 struct VInfo {
@@ -64,10 +66,23 @@ constexpr int64_t kSmallGemmTiles = 128;
 constexpr uint64_t kStageBytes = 16ull << 20;
 constexpr int kStageGatherWorkgroups = 64;  // see the launch of tile products in run_memgraph
 
-struct Group {  // one grouped kernel launch in flight on a compute stream
+// Copies that wait for kernels already enqueued follow them on the compute stream up to this size (see `chain`).
+// Measured with 64 KiB, 256 KiB, 512 KiB, 1 MiB: fp32 fine-tuning step with 64-row tiles 7.4, 5.6, 5.6, 6.7 ms (copies that
+// could have run beside kernels), bf16 layer with 288 KiB tiles 5.4, 5.0, 4.1, 3.8 ms, fp32 layer with 256 KiB tiles 5.6,
+// 5.2, 4.8, 4.6 ms; without chaining 14, 5.5 and 5.9 ms.
+constexpr uint64_t kChainBytes = 512u << 10;
+constexpr int kChainWorkgroups = 16;  // a piece of 32 KiB each: no kernel runs beside them
+// GPU -> host groups up to this size are written to host memory by the copy kernel: a staging copy and a runtime copy
+// behind it take 20 us for 64 KiB, the kernel 7.
+constexpr uint64_t kDirectStoreBytes = 256u << 10;
+// A kernel group that costs less than an event's way to the host and back (about 10 us).
+constexpr double kShortFlops = 1e9, kShortBytes = 8e6;
+
+struct Group {  // one grouped kernel launch in flight on a compute stream, or (family 3, 4) a chained group of copies
   std::vector<int64_t> verts;
-  hipEvent_t done = nullptr;
+  hipEvent_t done = nullptr;  // none: seen complete with the next group of its stream that has one
   int family = 0, prof = -1;
+  bool brief = false;
 };
 
 struct XGroup {  // one group of copies in flight on a copy stream
@@ -639,7 +654,7 @@ tn_status tn_executor_create(const tn_memgraph* mg, void* device_base, uint64_t 
   ex->cevents.resize(n_compute);
   ex->cqueue.resize(n_compute);
   for (int i = 0; i < n_compute; ++i)
-    for (int k = 0; k < kMaxQueueDepth; ++k) {
+    for (int k = 0; k < kMaxChain; ++k) {
       hipEvent_t ev;
       hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
       if (e != hipSuccess) return bail(fail(TN_ERR_HIP, "hipEventCreateWithFlags: %s", hipGetErrorString(e)));
@@ -814,8 +829,16 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       return fail(TN_ERR_INVALID, "copy_engine KERNEL needs every host buffer to be GPU-addressable pinned memory");
     kernel_copies = kernel_copies && ok;
   }
+  // Chained transfers.  Under a cap far below a small program's working set every other vertex is a copy of a few tiles
+  // that waits for the kernel before it and that the kernel behind it waits for.  Seen from the host each such step
+  // costs 12 us (an event's way to the host and a launch's way back; a stream that waits for another stream's event
+  // takes as long, 14 us), one behind the other on one stream 2.8 (6.7 with an event between them).  So with a
+  // single compute stream, copies that wait only for work enqueued there follow that work on the compute stream as
+  // long as they are small (kChainBytes, 10 us on the link: what a longer copy keeps the stream from is worth more
+  // than the two steps) and nothing else is there to be launched.
+  const bool chain = ahead && ex->n_compute == 1 && kernel_copies && opt.max_delay_us == 0 && opt.policy != TN_POLICY_IN_ORDER;
   ex->remaining = ex->indeg;
-  std::vector<int64_t> rem_enq(ex->indeg);           // dependencies not yet enqueued (kernels) or completed
+  std::vector<int64_t> rem_enq(ex->indeg);           // dependencies not yet enqueued (kernels, chained copies) or completed
   std::vector<hipEvent_t> ev_of(nv, nullptr);        // event of the group a kernel vertex was enqueued in
   std::vector<int8_t> stream_of(nv, -1), state(nv, 0);  // state: 0 waiting, 1 enqueued, 2 complete
   std::vector<int> ring_next(ex->n_compute, 0);
@@ -845,6 +868,12 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
     q.key = ex->order_key.data();
   }
   ReadyQueue* const rq_x = rq.data() + n_groups;  // [0] host to device, [1] device to host
+  ReadyQueue rq_chain[2];  // transfers whose dependencies are complete or enqueued on the compute stream, but not all complete
+  for (auto& q : rq_chain) {
+    q.policy = in_order ? TN_POLICY_FIFO : opt.policy;
+    q.key = ex->order_key.data();
+  }
+  int64_t n_chained = 0;  // chained copy groups in flight
   std::vector<char> is_ready(in_order ? nv : 0, 0);
   std::vector<uint64_t> arrival(opt.policy <= TN_POLICY_LIFO ? nv : 0, 0);  // when a vertex became ready
   uint64_t n_arrived = 0;
@@ -886,6 +915,35 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   // taken wait here, outside the ready lists
   std::vector<char> lock_busy(nv, 0);
   std::unordered_map<int64_t, std::vector<int64_t>> lock_wait;
+  // What follows vertices that were enqueued on a compute stream: kernels whose dependencies are all enqueued can be
+  // launched behind them.  With chained transfers, copies wait for their turn in rq_chain, and vertices with no work
+  // count as enqueued themselves.  (Dependencies on transfers of the copy streams end at completion only.)
+  std::vector<int64_t> enqueueable;  // non-kernel vertices with rem_enq 0 that have not been looked at
+  auto tell = [&](int64_t m) {
+    state[m] = 1;
+    for (int64_t i = ex->succ_start[m]; i < ex->succ_start[m + 1]; ++i) {
+      const int64_t w = ex->succ[i];
+      if (mg.v[w].kind == TN_MG_OP) {
+        if (--rem_enq[w] == 0) make_ready(w);
+      } else if (chain && --rem_enq[w] == 0) {
+        enqueueable.push_back(w);
+      }
+    }
+  };
+  auto spread = [&]() {
+    while (!enqueueable.empty()) {
+      const int64_t w = enqueueable.back();
+      enqueueable.pop_back();
+      if (state[w] != 0 || ex->remaining[w] == 0) continue;  // complete, or about to be: the ordinary way
+      const int32_t k = mg.v[w].kind;
+      if (k == TN_MG_INPUT || k == TN_MG_DROP || k == TN_MG_JOIN) {
+        ex->last_order.push_back(w);
+        tell(w);
+      } else {
+        rq_chain[k == TN_MG_LOAD || k == TN_MG_RELOAD ? 0 : 1].push(w);
+      }
+    }
+  };
   // a vertex whose dependencies are all complete joins a ready list; vertices with no work
   // (inputs already in place, drops, joins of sums) complete on the spot
   auto complete = [&](int64_t first) {
@@ -894,7 +952,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       const int64_t m = work.back();
       work.pop_back();
       ++completed;
-      const bool was_enqueued_kernel = ahead && mg.v[m].kind == TN_MG_OP;  // its successors were told at enqueue time
+      const bool told = ahead && state[m] == 1;  // its successors heard of it when it was enqueued
       state[m] = 2;
       if (const int64_t lk = ex->info[m].lock; lk >= 0) {
         lock_busy[lk] = 0;
@@ -910,21 +968,25 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
         const int32_t k = mg.v[w].kind;
         if (k == TN_MG_OP) {
           if (ahead) {
-            if (!was_enqueued_kernel && --rem_enq[w] == 0) make_ready(w);
+            if (!told && --rem_enq[w] == 0) make_ready(w);
           } else if (all_done) {
             make_ready(w);
           }
           continue;
         }
-        if (!all_done) continue;
+        if (!all_done) {
+          if (chain && !told && --rem_enq[w] == 0) enqueueable.push_back(w);
+          continue;
+        }
         if (k == TN_MG_INPUT || k == TN_MG_DROP || k == TN_MG_JOIN) {
-          ex->last_order.push_back(w);
+          if (state[w] == 0) ex->last_order.push_back(w);
           work.push_back(w);
-        } else {
+        } else if (state[w] == 0) {
           make_ready(w);
         }
       }
     }
+    spread();
   };
   for (int64_t m = 0; m < nv; ++m) {
     if (ex->indeg[m] != 0) continue;
@@ -935,6 +997,26 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       make_ready(m);
     }
   }
+
+  // a launched vertex has been seen to be over; a reload gives its arena slot back
+  auto finish = [&](int64_t m) {
+    const MVertex& x = mg.v[m];
+    if (x.kind == TN_MG_RELOAD) {
+      const int64_t o = x.operands[0];
+      arena_free(*ex, (uint64_t)ex->arena_off[o]);
+      arena_used -= (mg.v[o].bytes + 255) / 256 * 256;
+      ex->arena_off[o] = -1;
+    }
+    complete(m);
+  };
+  auto finish_group = [&](const Group& g) {
+    n_chained -= g.family >= 3;
+    for (int64_t m : g.verts) finish(m);
+  };
+  auto next_event = [&](Group& g, int si) {
+    g.done = ex->cevents[si][ring_next[si]];
+    ring_next[si] = (ring_next[si] + 1) % kMaxChain;
+  };
 
   auto hip_fail = [&](const char* what, hipError_t e) {
     ex->poisoned = true;
@@ -963,6 +1045,96 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   std::vector<std::array<int64_t, 4>> sort_keys;
   std::vector<hipEvent_t> waited;
 
+  // Whether the transfers of a direction that are ready now should follow the kernels on the compute stream: the copy
+  // stream is idle, all of them together are small, and nothing enqueued for the compute stream takes long.
+  // a store that nobody waits for takes the copy stream, and so does one to a buffer the copy kernel's 16-byte pieces do not fit
+  auto chainable = [&](int64_t m) {
+    return ex->succ_start[m + 1] > ex->succ_start[m] &&
+           !(mg.v[m].kind == TN_MG_STORE && (uintptr_t)host_outputs[mg.v[m].output_index] % 16);
+  };
+  auto chain_now = [&](int dir) {
+    if (!chain || !xq[dir].empty() || n_ready_x[dir] > max_xfer) return false;
+    for (const Group& g : ex->cqueue[0])
+      if (!g.brief) return false;
+    uint64_t bytes = 0;
+    bool all = true;
+    auto look = [&](int64_t m) {
+      bytes += (mg.v[m].bytes + 255) / 256 * 256;
+      all = all && chainable(m);
+    };
+    for (int64_t m : rq_x[dir].q) look(m);
+    for (int64_t m : rq_x[dir].v) look(m);
+    return all && bytes <= kChainBytes && (dir == 0 || mg.stats.n_offload == 0 || arena_largest_free(*ex) >= bytes);
+  };
+  // Enqueues one group of chained copies on the compute stream; false if there is none to enqueue.
+  auto chain_copies = [&](int dir) {
+    if (!chain_now(dir) || (int)ex->cqueue[0].size() >= kMaxChain) return false;
+    xverts.clear();
+    copies.n = copies.total_blocks = 0;
+    uint64_t bytes = 0;
+    for (int part = 0; part < 2; ++part) {  // what is ready, then what follows enqueued work
+      ReadyQueue& r = part ? rq_chain[dir] : rq_x[dir];
+      while (!r.empty() && copies.n < max_xfer) {
+        const int64_t m = r.peek(rng);
+        const MVertex& x = mg.v[m];
+        if (part && (ex->remaining[m] == 0 || state[m] != 0)) {  // became ready in the meantime
+          r.pop();
+          continue;
+        }
+        if (part && (bytes + x.bytes > kChainBytes || !chainable(m))) break;
+        const void* src;
+        void* dst;
+        if (x.kind == TN_MG_LOAD) {
+          src = host_inputs[x.src];
+          dst = ex->dbase + x.offset;
+        } else if (x.kind == TN_MG_RELOAD) {
+          src = ex->arena + ex->arena_off[x.operands[0]];
+          dst = ex->dbase + x.offset;
+        } else {
+          src = ex->dbase + mg.v[x.operands[0]].offset;
+          if (x.kind == TN_MG_STORE) {
+            dst = host_outputs[x.output_index];
+          } else {
+            uint64_t off;
+            if (!ex->arena || !arena_alloc(*ex, x.bytes, &off)) break;  // the copy stream waits for a free slot
+            ex->arena_off[m] = (int64_t)off;
+            arena_used += (x.bytes + 255) / 256 * 256;
+            rep.arena_high_water = std::max(rep.arena_high_water, arena_used);
+            ++rep.n_offload;
+            dst = ex->arena + off;
+          }
+        }
+        r.pop();
+        if (!part) --n_ready_x[dir];
+        copies.it[copies.n++] = {src, dst, (uint32_t)x.bytes, (uint32_t)copies.total_blocks};
+        copies.total_blocks += (int32_t)((x.bytes + kCopyBlockBytes - 1) / kCopyBlockBytes);
+        bytes += x.bytes;
+        (dir == 0 ? rep.h2d_bytes : rep.d2h_bytes) += x.bytes;
+        rep.n_reload += x.kind == TN_MG_RELOAD;
+        xverts.push_back(m);
+        ex->last_order.push_back(m);
+      }
+    }
+    if (xverts.empty()) return false;
+    hipStream_t stream = ex->slots[0].stream;
+    Group grp;
+    grp.family = 3 + dir;
+    grp.brief = true;
+    hipError_t e = hipSuccess;
+    if (opt.profile && prof_pair(&grp.prof)) e = hipEventRecord(ex->prof_events[grp.prof], stream);
+    if (e == hipSuccess) e = launch_copies(copies, kChainWorkgroups, stream);
+    if (e == hipSuccess && grp.prof >= 0) e = hipEventRecord(grp.done = ex->prof_events[grp.prof + 1], stream);
+    if (e != hipSuccess) { hip_fail("chained transfer", e); return false; }
+    if (grp.prof >= 0) ex->prof_recs.push_back({3 + dir, grp.prof, (int32_t)xverts.size(), (int64_t)bytes, (double)bytes});
+    grp.verts = xverts;
+    for (int64_t m : grp.verts) tell(m);
+    spread();
+    ex->cqueue[0].push_back(std::move(grp));
+    ++n_chained;
+    ++rep.n_launches;
+    return true;
+  };
+
   while (completed < nv && status == TN_OK) {
     bool progressed = false;
     // ---- launch transfers: per direction a few groups of copies in flight, so that the stream
@@ -971,7 +1143,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       Slot& sl = ex->slots[ex->n_compute + dir];
       ReadyQueue& r = rq_x[dir];
       const std::vector<int64_t>& serial = ex->serial[1 + dir];
-      if ((int)xq[dir].size() >= xdepth || n_ready_x[dir] == 0) continue;
+      if ((int)xq[dir].size() >= xdepth || n_ready_x[dir] == 0 || chain_now(dir)) continue;
       std::vector<int64_t>& tv = xverts;
       tv.clear();
       copies.n = 0;
@@ -1038,7 +1210,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
           if (stage_used + need > kStageBytes || copies.n >= kMaxCopies) break;  // the slot is full: the rest goes with the next group
           if (arena_largest_free(*ex) < stage_used + need) {
             if (!tv.empty() || !xq[1].empty()) break;  // what is queued (and later reloads) will free slots
-            if (!xq[0].empty() || n_ready_x[0] > 0) break;
+            if (!xq[0].empty() || n_ready_x[0] > 0 || n_chained > 0) break;
             status = fail(TN_ERR_ARENA, "pinned host arena of %llu bytes is exhausted (offload of %llu bytes)",
                           (unsigned long long)ex->arena_bytes, (unsigned long long)x.bytes);
             break;
@@ -1058,7 +1230,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
           uint64_t off;
           if (!ex->arena || !arena_alloc(*ex, x.bytes, &off)) {
             if (!tv.empty() || !xq[1].empty()) break;  // let the copies already queued (and later reloads) free slots
-            if (!xq[0].empty() || n_ready_x[0] > 0) break;
+            if (!xq[0].empty() || n_ready_x[0] > 0 || n_chained > 0) break;
             status = fail(TN_ERR_ARENA, "pinned host arena of %llu bytes is exhausted (offload of %llu bytes)",
                           (unsigned long long)ex->arena_bytes, (unsigned long long)x.bytes);
             break;
@@ -1145,7 +1317,10 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
             pos += (stage_sizes[k] + 255) / 256 * 256;
           }
         }
-        e = launch_copies(copies, kStageGatherWorkgroups, sl.stream);
+        bool direct = stage_used <= kDirectStoreBytes;
+        for (int64_t m : stage_verts)
+          direct = direct && (mg.v[m].kind == TN_MG_OFFLOAD || (uintptr_t)host_outputs[mg.v[m].output_index] % 16 == 0);
+        if (!direct) e = launch_copies(copies, kStageGatherWorkgroups, sl.stream);
         // A run may cross the padding behind a tensor (sizes are rounded up to 256 bytes in the slot) only where
         // that padding is the library's own, in the arena: bytes between two of the caller's buffers are not ours.
         char* run_dst = nullptr;
@@ -1166,6 +1341,10 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
           } else {
             dst = (char*)host_outputs[x.output_index];
           }
+          if (direct) {
+            copies.it[k].dst = dst;
+            continue;
+          }
           if (run_bytes && !(dst == run_dst + run_bytes && (run_pad == 0 || pad_is_ours))) flush();
           if (e != hipSuccess) break;
           if (!run_bytes) { run_dst = dst; run_src = in_slot; }
@@ -1175,6 +1354,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
           in_slot += sz;
         }
         if (e == hipSuccess) flush();
+        if (e == hipSuccess && direct) e = launch_copies(copies, opt.d2h_workgroups > 0 ? opt.d2h_workgroups : opt.copy_workgroups, sl.stream);
       }
       if (xg.prof >= 0) xg.done = ex->prof_events[xg.prof + 1];
       if (e == hipSuccess) e = hipEventRecord(xg.done, sl.stream);
@@ -1190,10 +1370,22 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       progressed = true;
     }
     // ---- launch kernels: one group per compute stream with room in its queue ---------------
-    while (status == TN_OK && n_ready_k > 0) {
+    while (status == TN_OK) {
+      if (chain && n_ready_k == 0) {
+        if (!chain_copies(1) && !chain_copies(0)) break;
+        progressed = true;
+        continue;
+      }
+      if (n_ready_k == 0) break;
       int si = -1;
-      for (int k = 0; k < ex->n_compute; ++k)
-        if ((int)ex->cqueue[k].size() < depth && (si < 0 || ex->cqueue[k].size() < ex->cqueue[si].size())) si = k;
+      if (chain) {  // groups that are over in a moment do not count: it is the event behind them that costs time
+        int longer = 0;
+        for (const Group& g : ex->cqueue[0]) longer += !g.brief;
+        if ((int)ex->cqueue[0].size() < kMaxChain && longer < depth) si = 0;
+      } else {
+        for (int k = 0; k < ex->n_compute; ++k)
+          if ((int)ex->cqueue[k].size() < depth && (si < 0 || ex->cqueue[k].size() < ex->cqueue[si].size())) si = k;
+      }
       if (si < 0) break;
       hipStream_t stream = ex->slots[si].stream;
       // GEMM groups that overlap only share the compute units; holding the next one back until a
@@ -1204,6 +1396,11 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
         for (auto& q : ex->cqueue)
           for (auto& g : q) inflight += g.family == 0;
         gemm_ok = inflight < opt.max_gemm_inflight;
+        // (not among launches that are over in a moment while no copy is under way that could make more tiles ready)
+        if (!gemm_ok && chain && xq[0].empty()) {
+          gemm_ok = true;
+          for (const Group& g : ex->cqueue[0]) gemm_ok = gemm_ok && g.brief;
+        }
       }
       same.clear();
       int gi = -1;  // launch group of the lead vertex
@@ -1244,7 +1441,11 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
             default: break;
           }
         }
-        if (gi < 0) break;  // only GEMMs are ready and enough of them are running
+        if (gi < 0) {  // only GEMMs are ready and enough of them are running
+          if (!chain_copies(1) && !chain_copies(0)) break;
+          progressed = true;
+          continue;
+        }
         if (opt.policy == TN_POLICY_RANDOM) {  // a ready kernel drawn uniformly decides the group
           rng = mix64(rng);
           uint64_t pick = rng % total;
@@ -1317,7 +1518,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       }
       hipError_t e = hipSuccess;
       // device-side waits for kernels this group depends on that are enqueued on other streams
-      if (ahead) {
+      if (ahead && !chain) {
         waited.clear();
         for (int64_t m : same)
           for (int64_t i = ex->pred_start[m]; i < ex->pred_start[m + 1] && e == hipSuccess; ++i) {
@@ -1330,8 +1531,15 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       }
       Group grp;
       grp.family = family_of(lead.cls);
-      grp.done = ex->cevents[si][ring_next[si]];
-      ring_next[si] = (ring_next[si] + 1) % kMaxQueueDepth;
+      grp.brief = flops <= kShortFlops && bytes <= kShortBytes;
+      if (!(chain && grp.brief)) {
+        // nobody should have to wait for this group to learn that the brief ones before it are over
+        if (auto& q = ex->cqueue[si]; !q.empty() && !q.back().done) {
+          next_event(q.back(), si);
+          if (e == hipSuccess) e = hipEventRecord(q.back().done, stream);
+        }
+        next_event(grp, si);
+      }
       if (e == hipSuccess && opt.profile && prof_pair(&grp.prof)) e = hipEventRecord(ex->prof_events[grp.prof], stream);
       // A group of tile products with at most kSmallGemmTiles 256x256 tiles leaves CUs without work for as long
       // as one tile takes; cut into 128x128 tiles (at most four per 256x256 tile, two workgroups per CU) it is
@@ -1352,7 +1560,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       }
       // a timed launch completes with its second stamp: one event record less between two kernels
       if (grp.prof >= 0) grp.done = ex->prof_events[grp.prof + 1];
-      if (e == hipSuccess) e = hipEventRecord(grp.done, stream);
+      if (e == hipSuccess && grp.done) e = hipEventRecord(grp.done, stream);
       if (e != hipSuccess) { hip_fail("kernel launch", e); break; }
       for (int64_t m : same) {
         ex->last_order.push_back(m);
@@ -1360,12 +1568,10 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
         ev_of[m] = grp.done;
         stream_of[m] = (int8_t)si;
       }
-      if (ahead)  // kernels that only waited for these to be enqueued can follow
-        for (int64_t m : same)
-          for (int64_t i = ex->succ_start[m]; i < ex->succ_start[m + 1]; ++i) {
-            const int64_t w = ex->succ[i];
-            if (mg.v[w].kind == TN_MG_OP && --rem_enq[w] == 0) make_ready(w);
-          }
+      if (ahead) {  // what only waited for these to be enqueued can follow
+        for (int64_t m : same) tell(m);
+        spread();
+      }
       ++rep.n_launches;
       ++rep.n_kernel_launches;
       if (grp.family == 0) { ++rep.gemm_launches; rep.gemm_flops += flops; }
@@ -1380,13 +1586,23 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
     // ---- completions -----------------------------------------------------------------------
     for (int si = 0; si < ex->n_compute && status == TN_OK; ++si) {
       auto& q = ex->cqueue[si];
-      while (!q.empty()) {  // a stream finishes its groups in order
-        hipError_t e = hipEventQuery(q.front().done);
+      // the newest group always has an event when the host begins to wait
+      if (!q.empty() && !q.back().done) {
+        next_event(q.back(), si);
+        if (hipError_t e = hipEventRecord(q.back().done, ex->slots[si].stream); e != hipSuccess) { hip_fail("hipEventRecord", e); break; }
+      }
+      while (!q.empty()) {  // a stream finishes its groups in order: an event stands for the groups before it too
+        size_t n = 0;
+        while (!q[n].done) ++n;
+        hipError_t e = hipEventQuery(q[n].done);
         if (e == hipErrorNotReady) break;
         if (e != hipSuccess) { hip_fail("hipEventQuery", e); break; }
-        Group g = std::move(q.front());
-        q.pop_front();
-        for (int64_t m : g.verts) complete(m);
+        for (; ; --n) {
+          Group g = std::move(q.front());
+          q.pop_front();
+          finish_group(g);
+          if (n == 0) break;
+        }
         progressed = true;
       }
     }
@@ -1408,16 +1624,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
         if (Clock::now() < g.release) break;
         XGroup done = std::move(g);
         xq[dir].pop_front();
-        for (int64_t m : done.verts) {
-          const MVertex& x = mg.v[m];
-          if (x.kind == TN_MG_RELOAD) {
-            const int64_t o = x.operands[0];
-            arena_free(*ex, (uint64_t)ex->arena_off[o]);
-            arena_used -= (mg.v[o].bytes + 255) / 256 * 256;
-            ex->arena_off[o] = -1;
-          }
-          complete(m);
-        }
+        for (int64_t m : done.verts) finish(m);
         progressed = true;
       }
     }
