@@ -15,6 +15,9 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef unsigned short bf16_t;  // storage of a bf16 value
 
+// Tiles lie in global memory; said so, their loads are not counted among the LDS and scalar ones.
+#define TN_GLOBAL __attribute__((address_space(1)))
+
 __device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float((uint32_t)b << 16); }
 // round to nearest, ties to even: the hardware conversion of gfx950 (v_cvt_pk_bf16_f32)
 __device__ __forceinline__ bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }

@@ -28,8 +28,6 @@ constexpr int kWaves = 4;
 constexpr int kPitch = kTile + 4;  // floats per row of a partial in LDS
 static_assert(kTile == 32, "two 16-row MFMA tiles per side");
 
-// Tiles lie in global memory; said so, their loads are not counted among the LDS and scalar ones.
-#define TN_GLOBAL __attribute__((address_space(1)))
 __device__ __forceinline__ f32x4 ldg4(const TN_GLOBAL float* p) { return *(const TN_GLOBAL f32x4*)p; }
 __device__ __forceinline__ f32x4 ldg4(const TN_GLOBAL bf16_t* p) {
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));

@@ -80,8 +80,57 @@ __global__ void __launch_bounds__(256) ewise2_kernel(DeviceTables t, Batch b) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// RMSNorm statistic: one wavefront per row, over all column tiles of the row block
+// Statistics of a row that lies in pieces in several tiles: one wavefront per row.  What bounds them is the wait for
+// memory.  Taken tile by tile, each tile costs the wait for its address and width and then the wait for its elements
+// (16 tiles of 128 columns 12 us, whatever the number of rows).  So the wavefront fetches the addresses and
+// widths of 64 tiles at once, one tile per lane, and has U pieces of CH columns in flight; the order in which a
+// lane sums its elements is that of the tiles.  Per launch, before -> after: RMSNorm of 256 rows in 16 tiles of 128
+// 12.3 -> 8.3 us, of 2048 rows in 8 tiles of 512 51 -> 45 (beside copies from the host); its reverse, fp32, 3.5 -> 2.9.
+// N tensors, cut alike: tiles[k] is the table of the k-th.  load(u, tile addresses, tile's columns, first
+// column in the tile, the tile's first column in the row) may leave something for use(u), called in the same order.
 // ---------------------------------------------------------------------------------------------
+template <int U, int CH, int N, typename Load, typename Use>
+__device__ __forceinline__ void walk_pieces(const int* widths, void* const* const (&tiles)[N], int n, int lane, Load load, Use use) {
+  int row_col = 0;
+  for (int base = 0; base < n; base += 64) {
+    const int count = min(64, n - base), mine = base + min(lane, count - 1);
+    const int width = widths[mine];
+    uint32_t lo[N], hi[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const uint64_t a = (uint64_t)tiles[k][mine];
+      lo[k] = (uint32_t)a;
+      hi[k] = (uint32_t)(a >> 32);
+    }
+    int j = 0, c = 0, cols = __builtin_amdgcn_readlane(width, 0);
+    while (j < count) {
+      int used = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (j >= count) break;
+        const TN_GLOBAL void* at[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+          at[k] = (const TN_GLOBAL void*)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi[k], j) << 32) |
+                                (uint32_t)__builtin_amdgcn_readlane((int)lo[k], j));
+        load(u, at, cols, c, row_col);
+        ++used;
+        c += CH;
+        if (c >= cols) {
+          row_col += cols;
+          c = 0;
+          ++j;
+          cols = __builtin_amdgcn_readlane(width, min(j, count - 1));
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (u < used) use(u);
+    }
+  }
+}
+
+// RMSNorm statistic
 template <typename T>
 __global__ void __launch_bounds__(256) rms_stat_kernel(DeviceTables t, Batch b) {
   const OpDesc& d = t.descs[b.at(blockIdx.y)];
@@ -89,26 +138,39 @@ __global__ void __launch_bounds__(256) rms_stat_kernel(DeviceTables t, Batch b) 
   const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= d.rows) return;
   float ss = 0.f;
-  for (int j = 0; j < d.n_in; ++j) {
-    const int cols = t.aux[d.aux0 + j];
-    const T* x = (const T*)t.ptrs[d.ptr0 + j] + (size_t)row * cols;
-    for (int c = lane * 8; c < cols; c += 512) {
-      if (c + 8 <= cols && (cols & 7) == 0) {
+  constexpr int U = 4;
+  const TN_GLOBAL T* x[U];
+  int left[U];  // columns from this lane's first one to the end of the tile
+  f32x4 v[U][2];
+  void* const* const tiles[1] = {t.ptrs + d.ptr0};
+  walk_pieces<U, 512>(t.aux + d.aux0, tiles, d.n_in, lane,
+    [&](int u, const TN_GLOBAL void* const (&at)[1], int cols, int c0, int) {
+      const int c = c0 + lane * 8;
+      x[u] = (const TN_GLOBAL T*)at[0] + (size_t)row * cols + min(c, cols);
+      left[u] = (cols & 7) == 0 ? (c < cols ? 8 : 0) : -max(cols - c, 0);  // negative: not in whole pieces
+      if ((cols & 7) == 0 && c < cols) {
         if constexpr (sizeof(T) == 2) {
-          uint4 v = *(const uint4*)(x + c);
-          const bf16_t* p = (const bf16_t*)&v;
+          v[u][0] = *(const TN_GLOBAL f32x4*)x[u];
+        } else {
+          v[u][0] = *(const TN_GLOBAL f32x4*)x[u];
+          v[u][1] = *(const TN_GLOBAL f32x4*)(x[u] + 4);
+        }
+      }
+    },
+    [&](int u) {
+      if (left[u] > 0) {
+        if constexpr (sizeof(T) == 2) {
+          const bf16_t* p = (const bf16_t*)&v[u][0];
 #pragma unroll
           for (int k = 0; k < 8; ++k) { float f = bf2f(p[k]); ss += f * f; }
         } else {
-          float4 v0 = *(const float4*)(x + c), v1 = *(const float4*)(x + c + 4);
-          ss += v0.x * v0.x; ss += v0.y * v0.y; ss += v0.z * v0.z; ss += v0.w * v0.w;
-          ss += v1.x * v1.x; ss += v1.y * v1.y; ss += v1.z * v1.z; ss += v1.w * v1.w;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) ss += v[u][k / 4][k % 4] * v[u][k / 4][k % 4];
         }
       } else {
-        for (int k = c; k < min(c + 8, cols); ++k) { float f = ld(x + k); ss += f * f; }
+        for (int k = 0; k < min(8, -left[u]); ++k) { const T e = x[u][k]; float f = ld(&e); ss += f * f; }
       }
-    }
-  }
+    });
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
   if (lane == 0) ((float*)d.out)[row] = 1.0f / sqrtf(ss / (float)d.p.d + d.p.eps);
@@ -126,22 +188,25 @@ __global__ void __launch_bounds__(256) softmax_stat_kernel(DeviceTables t, Batch
   const float scale = d.p.scale;
   const int last = d.p.causal ? d.p.q_pos0 + row - d.p.k_pos0 : INT_MAX;  // last visible column
   float m = -INFINITY;
-  for (int j = 0, c0 = 0; j < d.n_in; ++j) {
-    const int cols = t.aux[d.aux0 + j];
-    const T* x = (const T*)t.ptrs[d.ptr0 + j] + (size_t)row * cols;
-    for (int c = lane; c < cols && c0 + c <= last; c += 64) m = fmaxf(m, ld(x + c) * scale);
-    c0 += cols;
-  }
+  constexpr int U = 8;
+  T v[U];
+  bool visible[U];
+  void* const* const tiles[1] = {t.ptrs + d.ptr0};
+  auto load = [&](int u, const TN_GLOBAL void* const (&at)[1], int cols, int c0, int row_col) {
+    const int c = c0 + lane;
+    visible[u] = c < cols && row_col + c <= last;
+    if (visible[u]) v[u] = ((const TN_GLOBAL T*)at[0])[(size_t)row * cols + c];
+  };
+  walk_pieces<U, 64>(t.aux + d.aux0, tiles, d.n_in, lane, load, [&](int u) {
+    if (visible[u]) m = fmaxf(m, ld(&v[u]) * scale);
+  });
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
   const float msafe = m == -INFINITY ? 0.f : m;
   float l = 0.f;
-  for (int j = 0, c0 = 0; j < d.n_in; ++j) {
-    const int cols = t.aux[d.aux0 + j];
-    const T* x = (const T*)t.ptrs[d.ptr0 + j] + (size_t)row * cols;
-    for (int c = lane; c < cols && c0 + c <= last; c += 64) l += __expf(ld(x + c) * scale - msafe);
-    c0 += cols;
-  }
+  walk_pieces<U, 64>(t.aux + d.aux0, tiles, d.n_in, lane, load, [&](int u) {
+    if (visible[u]) l += __expf(ld(&v[u]) * scale - msafe);
+  });
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
   if (lane == 0) {
@@ -166,6 +231,19 @@ __global__ void __launch_bounds__(256) softmax_apply_kernel(DeviceTables t, Batc
   const float m = stat[row * 2], inv = 1.f / stat[row * 2 + 1], scale = d.p.scale;
   const float msafe = m == -INFINITY ? 0.f : m;
   const int last = d.p.causal ? d.p.q_pos0 + row - d.p.k_pos0 : INT_MAX;
+  if ((d.cols & 7) == 0) {
+    const size_t e = (size_t)row * d.cols + c0;
+    f32x4 v[2] = {ld4(x + e), ld4(x + e + 4)};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k / 4][k % 4] = c0 + k <= last ? __expf(v[k / 4][k % 4] * scale - msafe) * inv : 0.f;
+    if constexpr (sizeof(T) == 2) {
+      *(uint4*)(o + e) = make_uint4(f2bf2(v[0][0], v[0][1]), f2bf2(v[0][2], v[0][3]), f2bf2(v[1][0], v[1][1]), f2bf2(v[1][2], v[1][3]));
+    } else {
+      st4(o + e, v[0]);
+      st4(o + e + 4, v[1]);
+    }
+    return;
+  }
   for (int c = c0; c < min(c0 + 8, d.cols); ++c) {
     const size_t e = (size_t)row * d.cols + c;
     st(o + e, c <= last ? __expf(ld(x + e) * scale - msafe) * inv : 0.f);
@@ -391,21 +469,52 @@ __global__ void __launch_bounds__(256) rms_bwd_stat_kernel(DeviceTables t, Batch
   if (row >= d.rows) return;
   const int nk = d.p.nk;
   float ss = 0.f;
-  for (int j = 0; j < nk; ++j) {
-    const int cols = t.aux[d.aux0 + j];
-    const T* dy = (const T*)t.ptrs[d.ptr0 + j] + (size_t)row * cols;
-    const T* x = (const T*)t.ptrs[d.ptr0 + nk + j] + (size_t)row * cols;
-    const T* g = (const T*)t.ptrs[d.ptr0 + 2 * nk + j];
-    if (sizeof(T) == 2 && (cols & 7) == 0) {  // 16-byte pieces
-      for (int c = lane * 8; c < cols; c += 512) {
-        const uint4 vd = *(const uint4*)(dy + c), vx = *(const uint4*)(x + c), vg = *(const uint4*)(g + c);
-        const bf16_t *pd = (const bf16_t*)&vd, *px = (const bf16_t*)&vx, *pg = (const bf16_t*)&vg;
+  void* const* const tiles[3] = {t.ptrs + d.ptr0, t.ptrs + d.ptr0 + nk, t.ptrs + d.ptr0 + 2 * nk};  // dy, x, gain
+  if constexpr (sizeof(T) == 2) {
+    constexpr int U = 4;
+    const TN_GLOBAL T *dy[U], *x[U], *g[U];
+    int end[U];  // whole pieces: 0, or 8 where this lane has one; else minus the columns from dy, x, g to the end of the piece
+    f32x4 vd[U], vx[U], vg[U];
+    walk_pieces<U, 512>(t.aux + d.aux0, tiles, nk, lane,
+      [&](int u, const TN_GLOBAL void* const (&at)[3], int cols, int c0, int) {
+        const bool whole = (cols & 7) == 0;
+        const int c = whole ? c0 + lane * 8 : c0;
+        dy[u] = (const TN_GLOBAL T*)at[0] + (size_t)row * cols + min(c, cols);
+        x[u] = (const TN_GLOBAL T*)at[1] + (size_t)row * cols + min(c, cols);
+        g[u] = (const TN_GLOBAL T*)at[2] + min(c, cols);
+        end[u] = whole ? (c < cols ? 8 : 0) : -min(cols - c0, 512);
+        if (end[u] > 0) {  // 16-byte pieces
+          vd[u] = *(const TN_GLOBAL f32x4*)dy[u];
+          vx[u] = *(const TN_GLOBAL f32x4*)x[u];
+          vg[u] = *(const TN_GLOBAL f32x4*)g[u];
+        }
+      },
+      [&](int u) {
+        if (end[u] > 0) {
+          const bf16_t *pd = (const bf16_t*)&vd[u], *px = (const bf16_t*)&vx[u], *pg = (const bf16_t*)&vg[u];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) ss += bf2f(pd[k]) * bf2f(pg[k]) * bf2f(px[k]);
-      }
-    } else {
-      for (int c = lane; c < cols; c += 64) ss += ld(dy + c) * ld(g + c) * ld(x + c);
-    }
+          for (int k = 0; k < 8; ++k) ss += bf2f(pd[k]) * bf2f(pg[k]) * bf2f(px[k]);
+        } else {
+          for (int c = lane; c < -end[u]; c += 64) ss += bf2f(dy[u][c]) * bf2f(g[u][c]) * bf2f(x[u][c]);
+        }
+      });
+  } else {
+    constexpr int U = 8;
+    float p[U][3];
+    bool there[U];
+    walk_pieces<U, 64>(t.aux + d.aux0, tiles, nk, lane,
+      [&](int u, const TN_GLOBAL void* const (&at)[3], int cols, int c0, int) {
+        const int c = c0 + lane;
+        there[u] = c < cols;
+        if (there[u]) {
+          p[u][0] = ((const TN_GLOBAL T*)at[0])[(size_t)row * cols + c];
+          p[u][1] = ((const TN_GLOBAL T*)at[2])[c];
+          p[u][2] = ((const TN_GLOBAL T*)at[1])[(size_t)row * cols + c];
+        }
+      },
+      [&](int u) {
+        if (there[u]) ss += p[u][0] * p[u][1] * p[u][2];
+      });
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
@@ -490,9 +599,14 @@ __global__ void __launch_bounds__(256) transpose_kernel(DeviceTables t, Batch b)
   }
   __shared__ T tile[64][65];
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4)
-    if (r0 + i < R && c0 + tx < C) tile[i][tx] = x[(size_t)(r0 + i) * C + c0 + tx];
+  T v[16];  // all loads in flight: one at a time the sixteen waits made a 64x64 piece take 7 us
+#pragma unroll
+  for (int k = 0; k < 16; ++k)  // rows and columns past the edge: any that exist, they are not stored
+    v[k] = x[(size_t)min(r0 + ty + 4 * k, R - 1) * C + min(c0 + tx, C - 1)];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) tile[ty + 4 * k][tx] = v[k];
   __syncthreads();
+#pragma unroll 4
   for (int i = ty; i < 64; i += 4)
     if (c0 + i < C && r0 + tx < R) o[(size_t)(c0 + i) * R + r0 + tx] = tile[tx][i];
 }
