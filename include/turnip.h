@@ -476,7 +476,8 @@ typedef struct {
   uint32_t max_delay_us; /* ... in [0, max_delay_us]; 0 = no injected delay */
   int32_t max_batch;     /* most same-kind ready vertices put into one kernel launch; 0 = default */
   int32_t profile;       /* != 0: time every launch with HIP events (fills the *_ms fields) */
-  int32_t max_transfers; /* most ready copies of one direction put into one group; 0 = default */
+  int32_t max_transfers; /* most ready copies of one direction put into one group; 0 = default (32; while they are
+                            below 4 MiB together, 128) */
   int32_t copy_engine;   /* TN_COPY_AUTO, TN_COPY_MEMCPY or TN_COPY_KERNEL */
   int32_t max_gemm_inflight; /* most GEMM groups running at once; 0 = as many as there are streams */
   int32_t queue_depth;   /* kernel groups in flight per compute stream (1..8; 0 = 1).  1: a kernel is

@@ -66,6 +66,9 @@ constexpr int64_t kSmallGemmTiles = 128;
 constexpr uint64_t kStageBytes = 16ull << 20;
 constexpr int kStageGatherWorkgroups = 64;  // see the launch of tile products in run_memgraph
 
+// Between two groups of copies the link rests for 5 us, and 1 MiB takes the copy kernel 21 us instead of the 18 of a
+// MiB of a larger group: 32 tensors of 32 KiB to a group keep the link at 39 GB/s, 4 MiB at 54.
+constexpr uint64_t kGroupBytes = 4u << 20;
 // Copies that wait for kernels already enqueued follow them on the compute stream up to this size (see `chain`).
 // Measured with 64 KiB, 256 KiB, 512 KiB, 1 MiB: fp32 fine-tuning step with 64-row tiles 7.4, 5.6, 5.6, 6.7 ms (copies that
 // could have run beside kernels), bf16 layer with 288 KiB tiles 5.4, 5.0, 4.1, 3.8 ms, fp32 layer with 256 KiB tiles 5.6,
@@ -1171,7 +1174,13 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       int early_prof = -1;
       if (!use_copy_kernel && opt.profile && prof_pair(&early_prof)) e = hipEventRecord(ex->prof_events[early_prof], sl.stream);
       // (copies inside GPU memory need no pipelining against the host link: one group takes all that fit)
-      while (n_ready_x[dir] > 0 && (int)tv.size() < (inside_gpu && use_copy_kernel ? kMaxCopies : max_xfer) && e == hipSuccess) {
+      // (a default-sized group of small tensors takes more of them, until it is worth its launch)
+      uint64_t group_bytes = 0;
+      auto room = [&]() {
+        const int n = (int)tv.size();
+        return n < max_xfer || (n < kMaxCopies && ((inside_gpu && use_copy_kernel) || (opt.max_transfers <= 0 && group_bytes < kGroupBytes)));
+      };
+      while (n_ready_x[dir] > 0 && room() && e == hipSuccess) {
         int64_t m;
         if (in_order) {  // the next transfer of this direction in the serial order, or none
           m = serial[serial_next[1 + dir]];
@@ -1257,6 +1266,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
           r.pop();
         }
         --n_ready_x[dir];
+        group_bytes += x.bytes;
         tv.push_back(m);
         (dir == 0 ? rep.h2d_bytes : rep.d2h_bytes) += x.bytes;
         rep.n_reload += x.kind == TN_MG_RELOAD;
