@@ -74,6 +74,7 @@ constexpr uint64_t kGroupBytes = 4u << 20;
 // could have run beside kernels), bf16 layer with 288 KiB tiles 5.4, 5.0, 4.1, 3.8 ms, fp32 layer with 256 KiB tiles 5.6,
 // 5.2, 4.8, 4.6 ms; without chaining 14, 5.5 and 5.9 ms.
 constexpr uint64_t kChainBytes = 512u << 10;
+constexpr uint64_t kChainMeanBytes = 384u << 10;  // no chaining where the transfers of a program are larger on average
 constexpr int kChainWorkgroups = 16;  // a piece of 32 KiB each: no kernel runs beside them
 // GPU -> host groups up to this size are written to host memory by the copy kernel: a staging copy and a runtime copy
 // behind it take 20 us for 64 KiB, the kernel 7.
@@ -805,8 +806,13 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   const int depth = std::max(1, std::min<int>(opt.queue_depth > 0 ? opt.queue_depth : 1, kMaxQueueDepth));
   const bool ahead = depth > 1;
   // every buffer the run will touch must be there before anything is launched
+  uint64_t n_copies = 0, copy_bytes = 0;
   for (int64_t m = 0; m < nv; ++m) {
     const MVertex& x = mg.v[m];
+    if (x.kind == TN_MG_LOAD || x.kind == TN_MG_RELOAD || x.kind == TN_MG_OFFLOAD || x.kind == TN_MG_STORE) {
+      ++n_copies;
+      copy_bytes += x.bytes;
+    }
     if (x.kind == TN_MG_LOAD && (!host_inputs || !host_inputs[x.src]))
       return fail(TN_ERR_INVALID, "no host buffer for input %d", (int)x.src);
     if (x.kind == TN_MG_STORE && (!host_outputs || !host_outputs[x.output_index]))
@@ -838,8 +844,10 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   // takes as long, 14 us), one behind the other on one stream 2.8 (6.7 with an event between them).  So with a
   // single compute stream, copies that wait only for work enqueued there follow that work on the compute stream as
   // long as they are small (kChainBytes, 10 us on the link: what a longer copy keeps the stream from is worth more
-  // than the two steps) and nothing else is there to be launched.
-  const bool chain = ahead && ex->n_compute == 1 && kernel_copies && opt.max_delay_us == 0 && opt.policy != TN_POLICY_IN_ORDER;
+  // than the two steps) and nothing else is there to be launched.  Not in programs whose copies are mostly larger: there
+  // kernels enqueued early only split the groups of tile products (layer with 512 KiB tiles under 40 % of its peak 9.06 ms
+  // unchained, 9.14 chained; with tiles of 288 KiB 5.5 and 4.0).
+  const bool chain = ahead && copy_bytes <= n_copies * kChainMeanBytes && ex->n_compute == 1 && kernel_copies && opt.max_delay_us == 0 && opt.policy != TN_POLICY_IN_ORDER;
   ex->remaining = ex->indeg;
   std::vector<int64_t> rem_enq(ex->indeg);           // dependencies not yet enqueued (kernels, chained copies) or completed
   std::vector<hipEvent_t> ev_of(nv, nullptr);        // event of the group a kernel vertex was enqueued in
