@@ -485,7 +485,7 @@ typedef struct {
                             kernels it depends on are enqueued, ordered on the device by stream events;
                             dependencies on transfers are awaited on the host, except that with a single
                             compute stream small copies between kernels (512 KiB per group, 384 KiB per
-                            copy on average over the memgraph, no injected
+                            load, reload or offload of the memgraph on average, no injected
                             delay, not TN_POLICY_IN_ORDER) are enqueued on that stream among them, where
                             launches that are over within microseconds do not count towards the depth. */
   int32_t transfer_depth;  /* groups of copies in flight per direction (1..8; 0 = 3): the next group is enqueued

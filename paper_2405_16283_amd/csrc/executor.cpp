@@ -74,7 +74,7 @@ constexpr uint64_t kGroupBytes = 4u << 20;
 // could have run beside kernels), bf16 layer with 288 KiB tiles 5.4, 5.0, 4.1, 3.8 ms, fp32 layer with 256 KiB tiles 5.6,
 // 5.2, 4.8, 4.6 ms; without chaining 14, 5.5 and 5.9 ms.
 constexpr uint64_t kChainBytes = 512u << 10;
-constexpr uint64_t kChainMeanBytes = 384u << 10;  // no chaining where the transfers of a program are larger on average
+constexpr uint64_t kChainMeanBytes = 384u << 10;  // no chaining where a program's loads, reloads and offloads are larger on average
 constexpr int kChainWorkgroups = 16;  // a piece of 32 KiB each: no kernel runs beside them
 // GPU -> host groups up to this size are written to host memory by the copy kernel: a staging copy and a runtime copy
 // behind it take 20 us for 64 KiB, the kernel 7.
@@ -809,7 +809,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   uint64_t n_copies = 0, copy_bytes = 0;
   for (int64_t m = 0; m < nv; ++m) {
     const MVertex& x = mg.v[m];
-    if (x.kind == TN_MG_LOAD || x.kind == TN_MG_RELOAD || x.kind == TN_MG_OFFLOAD || x.kind == TN_MG_STORE) {
+    if (x.kind == TN_MG_LOAD || x.kind == TN_MG_RELOAD || x.kind == TN_MG_OFFLOAD) {  // what kernels wait for
       ++n_copies;
       copy_bytes += x.bytes;
     }
