@@ -802,7 +802,8 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   // With a deeper queue a kernel may be enqueued as soon as the kernels it depends on are
   // enqueued: the stream waits for their events on the device, so the order of execution still
   // respects every dependency while the host no longer sits between two dependent kernels.
-  // Anything that depends on a transfer still waits for the host to see that transfer complete.
+  // Anything that depends on a transfer still waits for the host to see that transfer complete, chained
+  // transfers (below) excepted.
   const int depth = std::max(1, std::min<int>(opt.queue_depth > 0 ? opt.queue_depth : 1, kMaxQueueDepth));
   const bool ahead = depth > 1;
   // every buffer the run will touch must be there before anything is launched
