@@ -1636,7 +1636,10 @@ __global__ void __launch_bounds__(kCopyThreads) copy_kernel(CopyBatch b) {
 __global__ void __launch_bounds__(kDeviceCopyThreads) device_copy_kernel(CopyBatch b) {
   const CopyItem it = b.it[blockIdx.y];
   constexpr int N = kCopyBlockBytes / 16 / kDeviceCopyThreads;
-  for (uint32_t off = blockIdx.x * kCopyBlockBytes; off < it.bytes; off += gridDim.x * kCopyBlockBytes) {
+  // pieces are counted: a 32-bit byte offset stepped past the end of a tensor just below 4 GiB would start over
+  const uint32_t pieces = it.bytes / kCopyBlockBytes + (it.bytes % kCopyBlockBytes != 0);
+  for (uint32_t p = blockIdx.x; p < pieces; p += gridDim.x) {
+    const uint32_t off = p * kCopyBlockBytes;
     const uint32_t len = min(kCopyBlockBytes, it.bytes - off);
     const char* src = (const char*)it.src + off;
     char* dst = (char*)it.dst + off;
@@ -1741,7 +1744,7 @@ hipError_t launch_device_copies(const CopyBatch& b, hipStream_t s) {
   if (b.n <= 0 || b.total_blocks <= 0) return hipSuccess;
   uint32_t largest = 0;
   for (int k = 0; k < b.n; ++k) largest = std::max(largest, b.it[k].bytes);
-  const uint32_t pieces = std::min((largest + kCopyBlockBytes - 1) / kCopyBlockBytes, (uint32_t)kDeviceCopyPieces);
+  const uint32_t pieces = std::min(largest / kCopyBlockBytes + (largest % kCopyBlockBytes != 0), (uint32_t)kDeviceCopyPieces);
   hipLaunchKernelGGL(device_copy_kernel, dim3(pieces, (unsigned)b.n), dim3(kDeviceCopyThreads), 0, s, b);
   return hipGetLastError();
 }
