@@ -88,16 +88,22 @@ struct Side {
   static constexpr int W = P::W;
   typedef typename P::Vec Vec;
   void* const* tiles;
-  const TN_GLOBAL T* p = nullptr;
-  int rows, K = 0, r[2], g;
-  uint32_t off[2];  // bytes from a piece's first element along K to this lane's, for both 16-row tiles (a tile is below 4 GiB)
-  __device__ __forceinline__ Side(void* const* tiles_, int rows_, int r0, int n, int g_) : tiles(tiles_), rows(rows_), g(g_) {
+  const TN_GLOBAL T* p = nullptr;  // the workgroup's first row of the tile
+  int rows, r0, K = 0, r[2], g;    // r: rows from there
+  uint32_t off[2];  // bytes from a piece's first element along K in the first row to this lane's, for both 16-row tiles
+  __device__ __forceinline__ Side(void* const* tiles_, int rows_, int r0_, int n, int g_) : tiles(tiles_), rows(rows_), r0(r0_), g(g_) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) r[i] = min(r0 + 16 * i + n, rows - 1);  // rows past the end: any row, they are not stored
+    for (int i = 0; i < 2; ++i) r[i] = min(16 * i + n, rows - 1 - r0);  // rows past the end: any row, they are not stored
+  }
+  // Whether `off` holds the way from the workgroup's first row to its last (a tile of any size is fine as long as 32 of its
+  // rows, or what a lane skips along K of [K, rows], stay below 4 GiB).
+  __device__ __forceinline__ bool reaches(int K_) const {
+    const uint64_t elems = KC ? (uint64_t)kTile * (uint32_t)K_ : (uint64_t)(4 * W) * (uint32_t)rows;
+    return elems * sizeof(T) <= 0xFFFFFFFFull;
   }
   __device__ __forceinline__ void open(int kt, int K_, int) {
-    p = (const TN_GLOBAL T*)tiles[kt];
     K = K_;
+    p = (const TN_GLOBAL T*)tiles[kt] + (KC ? (size_t)r0 * K : (size_t)r0);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
       off[i] = ((uint32_t)r[i] * (KC ? (uint32_t)K : 1u) + (uint32_t)(W * g) * (KC ? 1u : (uint32_t)rows)) * (uint32_t)sizeof(T);
@@ -119,7 +125,7 @@ struct Side {
         }
       }
   }
-  // the last piece of a K tile, and rows that are not aligned to a whole vector
+  // the last piece of a K tile, and rows that are not aligned to a whole vector or too long for `off`
   __device__ __forceinline__ void load_ragged(int k0, Vec (&f)[2][2]) const {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -128,7 +134,7 @@ struct Side {
         const int k = k0 + 4 * W * j + W * g;
         f[j][i] = P::zero();
         if (KC && K % W == 0) {
-          if (k < K) f[j][i] = P::wide(at(p + k0 + 4 * W * j, i));
+          if (k < K) f[j][i] = P::wide(p + (size_t)r[i] * K + k);
         } else if constexpr (W == 4) {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -141,8 +147,8 @@ struct Side {
 template <typename P, typename SX, typename SY>
 __device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors, f32x4 (&acc)[2][2]) {
   constexpr int DEEP = 8 * P::W;  // elements along K of a piece
-  // whole pieces of a K tile; none where rows stored along K are not aligned to a vector
-  auto pieces = [&](int K) { return (vectors && K % P::W) ? 0 : K / DEEP; };
+  // whole pieces of a K tile; none where rows stored along K are not aligned to a vector or the tile is too wide
+  auto pieces = [&](int K) { return (vectors && K % P::W) || !x.reaches(K) || !y.reaches(K) ? 0 : K / DEEP; };
   int total = 0;
   for (int q = 0; q < s.nk; ++q) total += pieces(s.ks[q]);
   const int mine = (total - s.w + kWaves - 1) / kWaves;  // this wavefront's pieces: w, w + 4, ...
@@ -306,6 +312,7 @@ struct RowsSide {  // row r of the image: the A tiles of vertex r of the group
       tiles[i] = (Table)(t.ptrs + d.ptr0);
     }
   }
+  __device__ __forceinline__ bool reaches(int) const { return true; }
   __device__ __forceinline__ void open(int kt_, int K_, int nk) {
     if (kt_ == kt + 1) {
       p[0] = next[0];
