@@ -838,6 +838,10 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
     if (kernel_copies && !ok && (opt.copy_engine == TN_COPY_KERNEL || opt.copy_engine == TN_COPY_KERNEL_IN))
       return fail(TN_ERR_INVALID, "copy_engine KERNEL needs every host buffer to be GPU-addressable pinned memory");
     kernel_copies = kernel_copies && ok;
+    // a copy kernel's list holds sizes of 32 bits: programs with a larger transfer leave theirs to the runtime
+    for (const MVertex& x : mg.v)
+      if ((x.kind == TN_MG_LOAD || x.kind == TN_MG_RELOAD || x.kind == TN_MG_OFFLOAD || x.kind == TN_MG_STORE) && x.bytes > UINT32_MAX)
+        kernel_copies = false;
   }
   // Chained transfers.  Under a cap far below a small program's working set every other vertex is a copy of a few tiles
   // that waits for the kernel before it and that the kernel behind it waits for.  Seen from the host each such step

@@ -34,9 +34,9 @@ def _row_statistics(rows):
     return out.numpy()
 
 
-@pytest.mark.parametrize("rows", [32768 - 128])
+@pytest.mark.parametrize("rows", [32768 - 128, 32768 + 128])
 def test_a_tensor_near_4_gib_is_copied_whole(rows):
-    """16 MiB below 4 GiB, where a workgroup's last step along the tensor leads past 4 GiB."""
+    """16 MiB below 4 GiB, where a workgroup's last step along the tensor leads past 4 GiB, and 16 MiB above."""
     print(f"[case] copy inside GPU memory of {rows} x {COLS} fp32", flush=True)
     got = _row_statistics(rows)
     # sums of 32768 equal squares in fp32, a division and a square root
