@@ -768,6 +768,11 @@ tn_status tn_executor_place_inputs(tn_executor* ex, const void* const* host_inpu
   };
   CopyBatch copies;
   copies.n = copies.total_blocks = 0;
+  auto launch = [&]() {
+    const hipError_t e = launch_device_copies(copies, s);
+    copies.n = copies.total_blocks = 0;
+    return e;
+  };
   for (int64_t m = 0; m < mg.n_task; ++m) {
     const MVertex& x = mg.v[m];
     if (x.kind != TN_MG_INPUT) continue;
@@ -775,15 +780,14 @@ tn_status tn_executor_place_inputs(tn_executor* ex, const void* const* host_inpu
     if (on_this_gpu((const char*)host_inputs[m], x.bytes)) {
       copies.it[copies.n++] = {host_inputs[m], ex->dbase + x.offset, (uint32_t)x.bytes, (uint32_t)copies.total_blocks};
       copies.total_blocks += (int32_t)((x.bytes + kCopyBlockBytes - 1) / kCopyBlockBytes);
-      if (copies.n == kMaxCopies) {
-        TN_HIP(launch_device_copies(copies, s));
-        copies.n = copies.total_blocks = 0;
-      }
+      if (copies.n == kMaxCopies) TN_HIP(launch());
       continue;
     }
+    // a source inside the device buffer may be where an input before it goes: inputs are placed in their order
+    if (const char* p = (const char*)host_inputs[m]; p < ex->dbase + ex->dbytes && p + x.bytes > ex->dbase) TN_HIP(launch());
     TN_HIP(hipMemcpyAsync(ex->dbase + x.offset, host_inputs[m], x.bytes, hipMemcpyDefault, s));
   }
-  TN_HIP(launch_device_copies(copies, s));
+  TN_HIP(launch());
   TN_HIP(hipStreamSynchronize(s));
   return TN_OK;
 }

@@ -105,3 +105,28 @@ def test_inputs_are_placed_from_gpu_memory_of_any_alignment(shift):
         np.testing.assert_array_equal(out["y"], want["y"])
     finally:
         s.close()
+
+
+def test_inputs_are_placed_in_their_order():
+    """A source inside the device buffer is read after the inputs before it have been placed."""
+    n = 1 << 16
+    tg = B.tn_taskgraph_create()
+    ins = [B.tn_taskgraph_add_input(tg, B.TN_F32, 1, n, B.TN_DEVICE) for _ in range(2)]
+    B.tn_taskgraph_mark_output(tg, B.tn_taskgraph_add_op(tg, B.TN_OP_ADD, B.tn_op_params(), ins, B.TN_F32, 1, n))
+    cap = 1 << 20
+    mg = B.tn_compile(tg, None, cap, None)
+    dev = torch.zeros(cap, dtype=torch.uint8, device="cuda:0")
+    src = torch.arange(n, dtype=torch.float32, device="cuda:0")
+    out = torch.zeros(n, dtype=torch.float32).pin_memory()
+    torch.cuda.synchronize()
+    st = [torch.cuda.Stream() for _ in range(3)]
+    ex = B.tn_executor_create(mg, dev.data_ptr(), cap, 0, 0, [st[0].cuda_stream], st[1].cuda_stream, st[2].cuda_stream)
+    try:
+        print("[case] second input placed from where the first one went", flush=True)
+        B.tn_executor_place_inputs(ex, [src.data_ptr(), dev.data_ptr() + B.tn_memgraph_vertex(mg, ins[0]).offset, 0])
+        B.tn_execute(ex, [0, 0, 0], [out.data_ptr()], None)
+    finally:
+        B.tn_executor_destroy(ex)
+        B.tn_memgraph_destroy(mg)
+        B.tn_taskgraph_destroy(tg)
+    np.testing.assert_array_equal(out.numpy(), 2.0 * np.arange(n, dtype=np.float32))
