@@ -110,6 +110,19 @@ __device__ __forceinline__ void store_chunk_vt(float (*buf)[kRows + 4], const f3
   }
 }
 
+// A row's sum leaves out what the causal mask hides from it.  The matrix cores multiply that by a weight of zero, which
+// is the same as long as it is finite; chunks the diagonal crosses are looked through for infinities and NaN while they
+// are stored, and one that holds some is summed row by row (a wavefront's 64 lanes on 16 rows of HD columns).
+template <int N>
+__device__ __forceinline__ bool not_finite(const f32x4 (&v)[N]) {
+  float z = 0.f;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z = fmaf(v[i][e], 0.f, z);
+  return !(z == 0.f);
+}
+
 // aux: [rows per Q tile, rows per K/V tile, columns per tile, q rows, kv rows]
 template <typename T, int HD>
 __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch b) {
@@ -131,6 +144,8 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch 
   extern __shared__ __attribute__((aligned(16))) char lds[];
   float(*const ks)[HD + 4] = (float(*)[HD + 4])lds;                                   // K chunk [64][HD], padded
   float(*const vs)[kRows + 4] = (float(*)[kRows + 4])(lds + sizeof(float) * kRows * (HD + 4));  // V^T chunk [HD][64], padded
+  int* const odd = (int*)(lds + sizeof(float) * (kRows * (HD + 4) + HD * (kRows + 4)));  // first key of a chunk whose V is not finite
+  if (threadIdx.x == 0) *odd = -1;
 
   const int row = qb * kRows + w * 16 + n, qpos = d.p.q_pos0 + row;
   const int wpos0 = d.p.q_pos0 + qb * kRows + w * 16;  // first position of the wavefront
@@ -154,6 +169,7 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch 
     load_chunk_vt<T, HD, 0, P>(V, v_trans, 0, vn);
   }
   for (int kv0 = 0; kv0 < end; kv0 += kRows) {
+    const bool diagonal = causal && k_pos0 + kv0 + kRows - 1 > d.p.q_pos0 + qb * kRows;  // some row does not see some key
     __syncthreads();  // everybody is done with the chunk before
     if constexpr (!kAhead) {
       load_chunk<T, HD, 0, P>(K, false, kv0, kn);
@@ -161,11 +177,13 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch 
     }
     store_chunk<HD, 0, P>(ks, kn);
     store_chunk_vt<HD, 0, P>(vs, vn);
+    if (diagonal && not_finite(vn)) *odd = kv0;
     if constexpr (!kAhead) {
       load_chunk<T, HD, P, P>(K, false, kv0, kn);
       load_chunk_vt<T, HD, P, P>(V, v_trans, kv0, vn);
       store_chunk<HD, P, P>(ks, kn);
       store_chunk_vt<HD, P, P>(vs, vn);
+      if (diagonal && not_finite(vn)) *odd = kv0;
     }
     __syncthreads();
     if (kAhead && kv0 + kRows < end) {
@@ -212,6 +230,24 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch 
       }
 #pragma unroll
     for (int j = 0; j < HD / 16; ++j) o[j] *= alpha;
+    if (diagonal && *odd == kv0) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll 1
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const int key = 16 * k + 4 * q4 + i;
+            const float p = __shfl(s[k][i], n + 16 * q4, 64);
+            if (kv0 + key < kv_rows && k_pos0 + kv0 + key <= qpos) {
+#pragma unroll
+              for (int j = 0; j < HD / 16; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[j][e] = fmaf(p, vs[16 * j + 4 * g + e][key], o[j][e]);
+            }
+          }
+      continue;
+    }
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -275,6 +311,8 @@ __device__ __forceinline__ void attn_bwd_f32_body(const DeviceTables& t, const O
   float(*const x1)[HD + 4] = (float(*)[HD + 4])lds;                                             // K, or Q
   float(*const x2)[HD + 4] = (float(*)[HD + 4])(lds + sizeof(float) * kRows * (HD + 4));        // V, or dO
   float(*const xs)[2] = (float(*)[2])(lds + 2 * sizeof(float) * kRows * (HD + 4));              // statistics of the queries
+  int* const odd = (int*)(lds + sizeof(float) * (2 * kRows * (HD + 4) + 2 * kRows));  // first row of a chunk that is not finite
+  if (threadIdx.x == 0) *odd = -1;
 
   const int row = rb * kRows + w * 16 + n, rc = min(row, my_rows - 1);
   const int pos = (MODE <= 1 ? d.p.q_pos0 : d.p.k_pos0) + row;
@@ -301,6 +339,10 @@ __device__ __forceinline__ void attn_bwd_f32_body(const DeviceTables& t, const O
     __syncthreads();  // everybody is done with the chunk before
     store_chunk<HD>(x1, v1);
     store_chunk<HD>(x2, v2);
+    // some row of the workgroup and some row of the chunk do not see each other
+    const bool diagonal = causal && (MODE <= 1 ? d.p.k_pos0 + r0 + kRows - 1 > d.p.q_pos0 + rb * kRows
+                                               : d.p.k_pos0 + rb * kRows + kRows - 1 > d.p.q_pos0 + r0);
+    if (MODE != 0 && diagonal && not_finite(MODE == 3 ? v2 : v1)) *odd = r0;
     if (MODE >= 2 && threadIdx.x < 2 * kRows) xs[threadIdx.x / 2][threadIdx.x & 1] = sv;
     __syncthreads();
 #pragma unroll 1
@@ -337,6 +379,7 @@ __device__ __forceinline__ void attn_bwd_f32_body(const DeviceTables& t, const O
           const float z = s[e][i] * scale;
           if (MODE == 0) {
             s[e][i] = ok ? z : -INFINITY;
+            if (!ok) dp[e][i] = 0.f;
             mx = fmaxf(mx, s[e][i]);
           } else {
             float p = __expf(z - (MODE == 1 ? lse : xs[lr][0]));
@@ -360,6 +403,22 @@ __device__ __forceinline__ void attn_bwd_f32_body(const DeviceTables& t, const O
         }
         // acc^T[column, own row] += X^T[column, other row] wgt[other row, own row]; X: K, Q or dO
         float(*const xt)[HD + 4] = MODE == 3 ? x2 : x1;
+        if (diagonal && *odd == r0) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+#pragma unroll 1
+            for (int q4 = 0; q4 < 4; ++q4) {
+              const int lr = 16 * (k + e) + 4 * q4 + c, o = r0 + lr;
+              const float p = __shfl(wgt[c], n + 16 * q4, 64);
+              if (o < o_rows && (MODE <= 1 ? d.p.k_pos0 + o <= pos : pos <= d.p.q_pos0 + o)) {
+#pragma unroll
+                for (int j = 0; j < HD / 16; ++j)
+#pragma unroll
+                  for (int i = 0; i < 4; ++i) acc[j][i] = fmaf(p, xt[lr][16 * j + 4 * g + i], acc[j][i]);
+              }
+            }
+          continue;
+        }
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -404,8 +463,8 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_f32_kernel(DeviceTables t, Ba
   }
 }
 
-constexpr int fwd_lds(int hd) { return 4 * (kRows * (hd + 4) + hd * (kRows + 4)); }
-constexpr int bwd_lds(int hd) { return 4 * (2 * kRows * (hd + 4) + 2 * kRows); }
+constexpr int fwd_lds(int hd) { return 4 * (kRows * (hd + 4) + hd * (kRows + 4) + 4); }
+constexpr int bwd_lds(int hd) { return 4 * (2 * kRows * (hd + 4) + 2 * kRows + 4); }
 
 template <auto kernel>
 hipError_t launch(int lds, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t s) {

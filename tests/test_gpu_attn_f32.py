@@ -107,3 +107,52 @@ def test_attention_reverse(case):
     errs += [R.rel_err(a, t.grad.numpy()) for a, t in zip(got[-3:], (tq_, tk_, tv_))]
     print("  lse, D, dQ, dK, dV:", ", ".join(f"{e:.1e}" for e in errs), flush=True)
     assert max(errs) < TOL[dtype]
+
+
+def _masked_reference(Q, K, V, DO, scale, q_pos0):
+    """lse, D, output, dQ, dK, dV in float64, every row summed over the keys it sees and nothing else."""
+    q_rows, hd = Q.shape
+    lse, dd = np.zeros(q_rows), np.zeros(q_rows)
+    o, dq, dk, dv = np.zeros((q_rows, hd)), np.zeros((q_rows, hd)), np.zeros(K.shape), np.zeros(V.shape)
+    for i in range(q_rows):
+        n = min(len(K), q_pos0 + i + 1)
+        s = (K[:n] * Q[i]).sum(1) * scale
+        m = s.max()
+        lse[i] = m + np.log(np.exp(s - m).sum())
+        p = np.exp(s - lse[i])
+        o[i] = (p[:, None] * V[:n]).sum(0)
+        dp = (V[:n] * DO[i]).sum(1)
+        dd[i] = (p * dp).sum()
+        ds = p * (dp - dd[i]) * scale
+        dq[i] = (ds[:, None] * K[:n]).sum(0)
+        dk[:n] += ds[:, None] * Q[i]
+        dv[:n] += p[:, None] * DO[i]
+    return lse[:, None], dd[:, None], o, dq, dk, dv
+
+
+@pytest.mark.parametrize("which,value", [("k", np.nan), ("v", np.inf), ("v", np.nan), ("q", np.nan), ("do", np.inf), ("do", np.nan)])
+@pytest.mark.parametrize("dtype,hd,v_trans", [("f32", 64, 0), ("f32", 128, 1), ("bf16", 128, 0)])
+def test_what_the_mask_hides_stays_hidden(dtype, hd, v_trans, which, value):
+    """An infinity or NaN at one position reaches the rows that see it and no others, in the chunk on the diagonal too."""
+    print(f"[case] {value} in {which}, {dtype} head size {hd}, V transposed {v_trans}", flush=True)
+    rng = np.random.default_rng(hd + v_trans)
+    rows, scale = 131, 1.0 / np.sqrt(hd)  # 131: no multiple of what the bf16 kernels take
+    full = {k: rng.standard_normal((rows, hd)) for k in ("q", "k", "v", "do")}
+    full[which][100, 5] = value  # chunk of positions 64 .. 127
+    g = Graph(dtype)
+    (q, Q), (k, K), (do, DO) = (g.inp(full[n]) for n in ("q", "k", "do"))
+    v, V = g.inp(full["v"].T if v_trans else full["v"])
+    V = V.T if v_trans else V
+    p = dict(n_q_tiles=1, n_kv_tiles=1, n_col_tiles=1, head_dim=hd, q_pos0=0, k_pos0=0, causal=1, scale=scale, v_trans=v_trans)
+    blk = g.op(B.TN_OP_ATTN_BLOCK, [q, k, v], rows, hd + 2, f32=True, **p)
+    stat = g.op(B.TN_OP_ATTN_BWD, [q, k, v, do], rows, 2, f32=True, mode=0, **p)
+    grads = [g.op(B.TN_OP_ATTN_BWD, [q, k, v, do, stat], rows, hd, mode=m, **p) for m in (1, 2, 3)]
+    with np.errstate(all="ignore"):
+        out, st, dq, dk, dv = g.run([blk, stat] + grads)
+        got = [st[:, :1], st[:, 1:], out[:, :hd] / out[:, hd + 1:], dq, dk, dv]
+        want = _masked_reference(Q, K, V, DO, scale, 0)
+    for name, a, b in zip(("lse", "D", "output", "dQ", "dK", "dV"), got, want):
+        fine = np.isfinite(b)
+        assert np.array_equal(np.isfinite(a), fine), name
+        if fine.any():
+            assert R.rel_err(a[fine], b[fine]) < TOL[dtype], name
