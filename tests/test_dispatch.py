@@ -1,0 +1,144 @@
+"""The executor's dispatch on the CPU: the library's host sources linked with tests/fake_gpu.cpp in place of the HIP runtime
+and the kernels.  There streams run their work late and overtake each other at random, and a vertex's result is a mix of
+its operands', so work enqueued without the order it needs, or a copy taken from or put in the wrong place, changes what
+comes out.  What was enqueued where, behind what, can be read back."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2405_16283_amd import binding as B
+from paper_2405_16283_amd import build
+from paper_2405_16283_amd import harness as H
+from workloads import config
+
+ALIGN = 256
+KERNEL, COPY, DEVICE_COPY, MEMCPY = range(4)  # kinds of log entries
+COMPUTE, H2D, D2H = 0, 100, 101               # stream numbers (compute streams: 0, 1, ...)
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    """The library on a GPU that is not there, in place of the built one for the tests of this file."""
+    out = str(tmp_path_factory.mktemp("fake") / "libturnip_fake.so")
+    here = os.path.dirname(os.path.abspath(__file__))
+    src = [os.path.join(here, "fake_gpu.cpp")] + [os.path.join(build.CSRC, f) for f in sorted(os.listdir(build.CSRC)) if f.endswith(".cpp")]
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, "-Wl,-Bsymbolic", "-o", out] + src, check=True)
+    lib = C.CDLL(out)
+    for name, (res, args) in B.SIGNATURES.items():
+        fn = getattr(lib, name)
+        fn.restype, fn.argtypes = res, args
+    lib.fake_stream.restype = lib.fake_alloc.restype = C.c_void_p
+    lib.fake_alloc.argtypes = [C.c_uint64, C.c_int]
+    lib.fake_reset.argtypes = [C.c_uint64]
+    lib.fake_fail_after.argtypes = [C.c_int64]
+    lib.fake_pending.restype = C.c_int64
+    lib.fake_log.restype, lib.fake_log.argtypes = C.c_int64, [C.c_void_p, C.c_int64]
+    old, B._lib = B._lib, lib
+    yield lib
+    B._lib = old
+
+
+class Session:
+    """A memgraph, its buffers and an executor on the fake GPU.  Takes the taskgraph over."""
+
+    def __init__(self, fake, tg, cap, compile_opts=None, n_compute=1, arena_bytes=0, order=None):
+        self.fake, self.tg = fake, tg
+        self.mg = B.tn_compile(tg, order, cap, compile_opts)
+        self.stats = B.tn_memgraph_stats(self.mg)
+        n = B.tn_taskgraph_num_vertices(tg)
+        desc = [B.tn_taskgraph_vertex(tg, v) for v in range(n)]
+        size = [x.desc.rows * x.desc.cols * (4 if x.desc.dtype == B.TN_F32 else 2) for x in desc]
+        self.ins = [0] * n
+        for v, x in enumerate(desc):
+            if x.kind == B.TN_OP_INPUT:
+                self.ins[v] = fake.fake_alloc(size[v] + 4, 0)
+                C.memmove(self.ins[v], (0x9E3779B1 * (v + 1) % 2**32).to_bytes(4, "little"), 4)
+        self.outs = [0] * B.tn_taskgraph_num_outputs(tg)
+        for v, x in enumerate(desc):
+            if x.output_index >= 0:
+                self.outs[x.output_index] = fake.fake_alloc(size[v] + 4, 0)
+        self.cap, self.dev = cap, fake.fake_alloc(cap, 1)
+        self.n_compute, self.arena_bytes = n_compute, arena_bytes
+        self.ex = None
+
+    def run(self, seed=0, fail_after=-1, **opts):
+        """One execution on fresh streams; (words of the outputs, report, log)."""
+        f = self.fake
+        f.fake_reset(seed)
+        if self.ex:
+            B.tn_executor_destroy(self.ex)
+        self.ex = B.tn_executor_create(self.mg, self.dev, self.cap, 0, self.arena_bytes, [f.fake_stream(k) for k in range(self.n_compute)],
+                                       f.fake_stream(H2D), f.fake_stream(D2H))
+        for o in self.outs:
+            C.memset(o, 0, 4)
+        C.memset(self.dev, 0xEE, self.cap)
+        B.tn_executor_place_inputs(self.ex, self.ins)
+        f.fake_fail_after(fail_after)
+        rep = B.tn_execute(self.ex, self.ins, self.outs, B.tn_exec_opts(**opts))
+        assert f.fake_pending() == 0
+        B.tn_memgraph_simulate(self.mg, B.tn_executor_last_order(self.ex, self.stats.n_vertices))
+        return [C.c_uint32.from_address(o).value for o in self.outs], rep, self.log()
+
+    def log(self):
+        n = self.fake.fake_log(None, 0)
+        a = np.zeros((n, 6), dtype=np.int32)
+        self.fake.fake_log(a.ctypes.data, n)
+        return np.rec.fromarrays(a.T, names="kind,stream,n,detail,kernels_before,to_gpu")
+
+    def close(self):
+        if self.ex:
+            B.tn_executor_destroy(self.ex)
+        B.tn_memgraph_destroy(self.mg)
+        B.tn_taskgraph_destroy(self.tg)
+
+
+def llama(fake, name, cap_pct=None, n_compute=1, arena_bytes=0, compile_opts=None, **kw):
+    cfg = config(name)
+    tg = B.tn_build_llama(H.llama_config_struct(cfg, **kw))
+    cap = H.cap_for(cfg, tg) if cap_pct is None else H.uncapped_peak(tg) * cap_pct // 100 // ALIGN * ALIGN
+    return Session(fake, tg, cap, n_compute=n_compute, arena_bytes=arena_bytes, compile_opts=compile_opts)
+
+
+def chained(log):
+    """Copies on a compute stream."""
+    return log[(log.stream < H2D) & (log.kind != KERNEL)]
+
+
+POLICIES = [B.TN_POLICY_BY_ORDER, B.TN_POLICY_FIFO, B.TN_POLICY_LIFO, B.TN_POLICY_RANDOM]
+
+
+@pytest.mark.parametrize("name,kw", [("c1", {}), ("c1", dict(k_split=2)), ("ragged_f32", dict(kv_outputs=True)), ("decode_f32", {}),
+                                     ("batch2_f32", dict(lora_rank=16, train=True)), ("ragged_f32", dict(materialize_scores=True))],
+                         ids=["c1", "c1_sums", "ragged_kv", "decode", "train", "scores"])
+def test_every_order_computes_the_same(fake, name, kw):
+    """Chained copies (one compute stream, depth above 1) and copies the host waits for, on streams that overtake each other."""
+    s = llama(fake, name, **kw)
+    try:
+        assert s.stats.n_offload > 0
+        want, rep1, log1 = s.run(policy=B.TN_POLICY_IN_ORDER, max_batch=1, max_transfers=1)
+        assert not len(chained(log1))
+        for seed in range(8):
+            got, rep, log = s.run(seed, policy=POLICIES[seed % 4], order_seed=seed, queue_depth=(3, 8, 2)[seed % 3],
+                                  max_gemm_inflight=seed % 2, max_batch=(0, 3, 1920)[seed % 3], max_transfers=(0, 2)[seed // 4])
+            assert got == want and len(chained(log)) > 0
+            assert (rep.n_offload, rep.n_reload, rep.h2d_bytes, rep.d2h_bytes) == (rep1.n_offload, rep1.n_reload, rep1.h2d_bytes, rep1.d2h_bytes)
+        for kw in (dict(queue_depth=1), dict(queue_depth=3, max_delay_us=5), dict(queue_depth=3, copy_engine=B.TN_COPY_MEMCPY)):
+            got, _, log = s.run(1, policy=B.TN_POLICY_RANDOM, order_seed=1, **kw)
+            assert got == want and not len(chained(log))
+    finally:
+        s.close()
+
+
+def test_several_streams_compute_the_same(fake):
+    s = llama(fake, "c1", n_compute=3)
+    try:
+        want, _, _ = s.run(policy=B.TN_POLICY_IN_ORDER, max_batch=1, max_transfers=1)
+        for seed in range(4):
+            got, _, log = s.run(seed, policy=POLICIES[seed], order_seed=seed, queue_depth=1 + seed)
+            assert got == want and not len(chained(log))
+    finally:
+        s.close()
