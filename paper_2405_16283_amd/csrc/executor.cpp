@@ -1088,7 +1088,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   };
   // Enqueues one group of chained copies on the compute stream; false if there is none to enqueue.
   auto chain_copies = [&](int dir) {
-    if (!chain_now(dir) || (int)ex->cqueue[0].size() >= kMaxChain) return false;
+    if (status != TN_OK || !chain_now(dir) || (int)ex->cqueue[0].size() >= kMaxChain) return false;
     xverts.clear();
     copies.n = copies.total_blocks = 0;
     uint64_t bytes = 0;
@@ -1666,17 +1666,12 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       }
     }
   }
-  // drain whatever is still in flight (error paths): every stream the run used is idle on return
-  for (int dir = 0; dir < 2; ++dir)
-    if (!xq[dir].empty()) {
-      (void)hipStreamSynchronize(ex->slots[ex->n_compute + dir].stream);
-      xq[dir].clear();
-    }
-  for (int si = 0; si < ex->n_compute; ++si)
-    if (!ex->cqueue[si].empty()) {
-      (void)hipStreamSynchronize(ex->slots[si].stream);
-      ex->cqueue[si].clear();
-    }
+  // every stream is idle on return, also after an error, and then whether or not a group stands for the work on it (what
+  // was enqueued before the call that failed is in no queue)
+  if (status != TN_OK)
+    for (auto& sl : ex->slots) (void)hipStreamSynchronize(sl.stream);
+  for (auto& q : xq) q.clear();
+  for (auto& q : ex->cqueue) q.clear();
   rep.wall_ms = std::chrono::duration<double, std::milli>(Clock::now() - t_start).count();
   rep.n_vertices = completed;
   if (status == TN_OK && opt.profile) {

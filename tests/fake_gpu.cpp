@@ -32,7 +32,7 @@ std::map<int, Stream> streams;
 std::map<const char*, std::pair<size_t, hipMemoryType>> memory;  // start -> size, kind
 std::vector<Entry> entries;
 uint64_t rng = 1, serial = 0, idle_asks = 0;
-int64_t calls_until_failure = -1;
+int64_t calls_until_failure = -1, enqueued_after_failure = -1;  // -1: no failure yet
 
 uint64_t mix(uint64_t z) {
   z += 0x9E3779B97F4A7C15ull;
@@ -41,7 +41,11 @@ uint64_t mix(uint64_t z) {
   return z ^ (z >> 31);
 }
 Stream& of(hipStream_t s) { return *(Stream*)s; }
-bool fails() { return calls_until_failure >= 0 && calls_until_failure-- == 0; }
+bool fails() {
+  if (calls_until_failure < 0 || calls_until_failure-- > 0) return false;
+  enqueued_after_failure = 0;
+  return true;
+}
 int64_t pending() {
   int64_t n = 0;
   for (auto& s : streams) n += (int64_t)s.second.steps.size();
@@ -82,6 +86,7 @@ bool on_gpu(const void* p) {
 void log(int kind, hipStream_t s, int n, int detail, const void* dst) {
   int before = 0;
   for (auto& st : of(s).steps) before += st.kernel;
+  enqueued_after_failure += enqueued_after_failure >= 0;
   entries.push_back({kind, of(s).index, n, detail, before, dst ? on_gpu(dst) : 0});
 }
 uint32_t word(const void* p) { uint32_t w; memcpy(&w, p, 4); return w; }
@@ -135,8 +140,9 @@ void fake_reset(uint64_t seed) {  // forgets streams and the log, frees nothing
   entries.clear();
   rng = mix(seed + 1);
   idle_asks = 0;
-  calls_until_failure = -1;
+  calls_until_failure = enqueued_after_failure = -1;
 }
+int64_t fake_enqueued_after_failure() { return enqueued_after_failure; }
 void fake_fail_after(int64_t calls) { calls_until_failure = calls; }
 int64_t fake_pending() { return pending(); }
 int64_t fake_log(int32_t* out, int64_t cap) {

@@ -35,7 +35,7 @@ def fake(tmp_path_factory):
     lib.fake_alloc.argtypes = [C.c_uint64, C.c_int]
     lib.fake_reset.argtypes = [C.c_uint64]
     lib.fake_fail_after.argtypes = [C.c_int64]
-    lib.fake_pending.restype = C.c_int64
+    lib.fake_pending.restype = lib.fake_enqueued_after_failure.restype = C.c_int64
     lib.fake_log.restype, lib.fake_log.argtypes = C.c_int64, [C.c_void_p, C.c_int64]
     old, B._lib = B._lib, lib
     yield lib
@@ -140,5 +140,27 @@ def test_several_streams_compute_the_same(fake):
         for seed in range(4):
             got, _, log = s.run(seed, policy=POLICIES[seed], order_seed=seed, queue_depth=1 + seed)
             assert got == want and not len(chained(log))
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("opts", [dict(queue_depth=3), dict(queue_depth=3, copy_engine=B.TN_COPY_KERNEL), dict(queue_depth=1),
+                                  dict(queue_depth=3, copy_engine=B.TN_COPY_MEMCPY)], ids=["chained", "kernel", "depth1", "memcpy"])
+def test_after_a_hip_error_every_stream_is_idle(fake, opts):
+    """Whichever call fails: nothing is enqueued after it, and the buffers are the caller's again when the call returns."""
+    s = llama(fake, "c1", cap_pct=45)
+    try:
+        failed = 0
+        for at in list(range(20)) + list(range(20, 900, 67)):
+            try:
+                s.run(at, fail_after=at, policy=B.TN_POLICY_BY_ORDER, max_gemm_inflight=1, **opts)
+            except B.TurnipError as e:
+                assert e.status == B.TN_ERR_HIP
+                assert fake.fake_pending() == 0, at
+                assert fake.fake_enqueued_after_failure() == 0, at
+                failed += 1
+                with pytest.raises(B.TurnipError, match="poisoned"):
+                    B.tn_execute(s.ex, s.ins, s.outs, None)
+        assert failed > 20
     finally:
         s.close()
