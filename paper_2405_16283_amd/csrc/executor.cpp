@@ -893,7 +893,6 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
     q.policy = in_order ? TN_POLICY_FIFO : opt.policy;
     q.key = ex->order_key.data();
   }
-  int64_t n_chained = 0;  // chained copy groups in flight
   std::vector<char> is_ready(in_order ? nv : 0, 0);
   std::vector<uint64_t> arrival(opt.policy <= TN_POLICY_LIFO ? nv : 0, 0);  // when a vertex became ready
   uint64_t n_arrived = 0;
@@ -1030,7 +1029,6 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
     complete(m);
   };
   auto finish_group = [&](const Group& g) {
-    n_chained -= g.family >= 3;
     for (int64_t m : g.verts) finish(m);
   };
   auto next_event = [&](Group& g, int si) {
@@ -1150,13 +1148,13 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
     for (int64_t m : grp.verts) tell(m);
     spread();
     ex->cqueue[0].push_back(std::move(grp));
-    ++n_chained;
     ++rep.n_launches;
     return true;
   };
 
   while (completed < nv && status == TN_OK) {
     bool progressed = false;
+    int64_t no_slot = -1;  // an offload that found no room in the arena
     // ---- launch transfers: per direction a few groups of copies in flight, so that the stream
     // does not run dry while the host looks at the completion of the previous group
     for (int dir = 0; dir < 2 && status == TN_OK; ++dir) {
@@ -1235,10 +1233,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
           const uint64_t need = (x.bytes + 255) / 256 * 256;
           if (stage_used + need > kStageBytes || copies.n >= kMaxCopies) break;  // the slot is full: the rest goes with the next group
           if (arena_largest_free(*ex) < stage_used + need) {
-            if (!tv.empty() || !xq[1].empty()) break;  // what is queued (and later reloads) will free slots
-            if (!xq[0].empty() || n_ready_x[0] > 0 || n_chained > 0) break;
-            status = fail(TN_ERR_ARENA, "pinned host arena of %llu bytes is exhausted (offload of %llu bytes)",
-                          (unsigned long long)ex->arena_bytes, (unsigned long long)x.bytes);
+            no_slot = m;  // reloads will give slots back as long as anything is under way
             break;
           }
           copies.it[copies.n++] = {ex->dbase + mg.v[x.operands[0]].offset, slot + stage_used, (uint32_t)x.bytes,
@@ -1255,10 +1250,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
           inside_gpu = false;
           uint64_t off;
           if (!ex->arena || !arena_alloc(*ex, x.bytes, &off)) {
-            if (!tv.empty() || !xq[1].empty()) break;  // let the copies already queued (and later reloads) free slots
-            if (!xq[0].empty() || n_ready_x[0] > 0 || n_chained > 0) break;
-            status = fail(TN_ERR_ARENA, "pinned host arena of %llu bytes is exhausted (offload of %llu bytes)",
-                          (unsigned long long)ex->arena_bytes, (unsigned long long)x.bytes);
+            no_slot = m;
             break;
           }
           ex->arena_off[m] = (int64_t)off;
@@ -1659,9 +1651,13 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       bool any_busy = false;
       any_busy = !xq[0].empty() || !xq[1].empty();
       for (auto& q : ex->cqueue) any_busy |= !q.empty();
-      if (!any_busy && n_ready_k == 0 && n_ready_x[0] == 0 && n_ready_x[1] == 0 && completed < nv) {
-        status = fail(TN_ERR_CYCLE, "no vertex is ready and none is running: %lld of %lld completed",
-                      (long long)completed, (long long)nv);
+      if (!any_busy && completed < nv) {  // nothing runs and nothing could be launched: nothing ever will
+        if (no_slot >= 0)
+          status = fail(TN_ERR_ARENA, "pinned host arena of %llu bytes is exhausted (offload of %llu bytes)",
+                        (unsigned long long)ex->arena_bytes, (unsigned long long)mg.v[no_slot].bytes);
+        else
+          status = fail(TN_ERR_CYCLE, "no vertex can be launched and none is running: %lld of %lld completed",
+                        (long long)completed, (long long)nv);
         break;
       }
     }

@@ -164,3 +164,22 @@ def test_after_a_hip_error_every_stream_is_idle(fake, opts):
         assert failed > 20
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("depth", [1, 3])
+def test_an_offload_waits_for_room_in_the_arena(fake, depth):
+    """An arena no larger than some orders need: reloads that kernels in flight are about to allow give slots back."""
+    s = llama(fake, "ragged_f32")
+    try:
+        want, rep, _ = s.run(policy=B.TN_POLICY_BY_ORDER, queue_depth=1)
+        assert rep.arena_high_water < s.stats.host_arena_bytes
+        s.arena_bytes = rep.arena_high_water
+        for seed in range(8):
+            got, rep, _ = s.run(seed, policy=B.TN_POLICY_BY_ORDER, queue_depth=depth, max_gemm_inflight=1)
+            assert got == want and rep.arena_high_water <= s.arena_bytes
+        s.arena_bytes = 4096
+        with pytest.raises(B.TurnipError, match="exhausted") as e:
+            s.run(policy=B.TN_POLICY_BY_ORDER, queue_depth=depth)
+        assert e.value.status == B.TN_ERR_ARENA and fake.fake_pending() == 0
+    finally:
+        s.close()
