@@ -811,13 +811,14 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   const int depth = std::max(1, std::min<int>(opt.queue_depth > 0 ? opt.queue_depth : 1, kMaxQueueDepth));
   const bool ahead = depth > 1;
   // every buffer the run will touch must be there before anything is launched
-  uint64_t n_copies = 0, copy_bytes = 0;
+  uint64_t n_copies = 0, copy_bytes = 0, arena_need = 0;
   for (int64_t m = 0; m < nv; ++m) {
     const MVertex& x = mg.v[m];
     if (x.kind == TN_MG_LOAD || x.kind == TN_MG_RELOAD || x.kind == TN_MG_OFFLOAD) {  // what kernels wait for
       ++n_copies;
       copy_bytes += x.bytes;
     }
+    if (x.kind == TN_MG_OFFLOAD) arena_need += (x.bytes + 255) / 256 * 256;
     if (x.kind == TN_MG_LOAD && (!host_inputs || !host_inputs[x.src]))
       return fail(TN_ERR_INVALID, "no host buffer for input %d", (int)x.src);
     if (x.kind == TN_MG_STORE && (!host_outputs || !host_outputs[x.output_index]))
@@ -855,8 +856,9 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   // long as they are small (kChainBytes, 10 us on the link: what a longer copy keeps the stream from is worth more
   // than the two steps) and nothing else is there to be launched.  Not in programs whose copies are mostly larger: there
   // kernels enqueued early only split the groups of tile products (layer with 512 KiB tiles under 40 % of its peak 9.06 ms
-  // unchained, 9.14 chained; with tiles of 288 KiB 5.5 and 4.0).
-  const bool chain = ahead && copy_bytes <= n_copies * kChainMeanBytes && ex->n_compute == 1 && kernel_copies && opt.max_delay_us == 0 && opt.policy != TN_POLICY_IN_ORDER;
+  // unchained, 9.14 chained; with tiles of 288 KiB 5.5 and 4.0).  And not where the arena cannot hold every offload: a chained
+  // one takes its slot before the kernel before it has ended, when the reloads that give slots back are not yet allowed.
+  const bool chain = arena_need <= ex->arena_bytes && ahead && copy_bytes <= n_copies * kChainMeanBytes && ex->n_compute == 1 && kernel_copies && opt.max_delay_us == 0 && opt.policy != TN_POLICY_IN_ORDER;
   ex->remaining = ex->indeg;
   std::vector<int64_t> rem_enq(ex->indeg);           // dependencies not yet enqueued (kernels, chained copies) or completed
   std::vector<hipEvent_t> ev_of(nv, nullptr);        // event of the group a kernel vertex was enqueued in
@@ -1082,7 +1084,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
     };
     for (int64_t m : rq_x[dir].q) look(m);
     for (int64_t m : rq_x[dir].v) look(m);
-    return all && bytes <= kChainBytes && (dir == 0 || mg.stats.n_offload == 0 || arena_largest_free(*ex) >= bytes);
+    return all && bytes <= kChainBytes;
   };
   // Enqueues one group of chained copies on the compute stream; false if there is none to enqueue.
   auto chain_copies = [&](int dir) {
@@ -1114,7 +1116,10 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
             dst = host_outputs[x.output_index];
           } else {
             uint64_t off;
-            if (!ex->arena || !arena_alloc(*ex, x.bytes, &off)) break;  // the copy stream waits for a free slot
+            if (!ex->arena || !arena_alloc(*ex, x.bytes, &off)) {  // (the arena holds every offload)
+              status = fail(TN_ERR_ARENA, "pinned host arena of %llu bytes is exhausted", (unsigned long long)ex->arena_bytes);
+              return false;
+            }
             ex->arena_off[m] = (int64_t)off;
             arena_used += (x.bytes + 255) / 256 * 256;
             rep.arena_high_water = std::max(rep.arena_high_water, arena_used);

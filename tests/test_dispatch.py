@@ -175,8 +175,9 @@ def test_an_offload_waits_for_room_in_the_arena(fake, depth):
         assert rep.arena_high_water < s.stats.host_arena_bytes
         s.arena_bytes = rep.arena_high_water
         for seed in range(8):
-            got, rep, _ = s.run(seed, policy=B.TN_POLICY_BY_ORDER, queue_depth=depth, max_gemm_inflight=1)
+            got, rep, log = s.run(seed, policy=B.TN_POLICY_BY_ORDER, queue_depth=depth, max_gemm_inflight=1)
             assert got == want and rep.arena_high_water <= s.arena_bytes
+            assert not len(chained(log))  # chained offloads would take slots earlier than others
         s.arena_bytes = 4096
         with pytest.raises(B.TurnipError, match="exhausted") as e:
             s.run(policy=B.TN_POLICY_BY_ORDER, queue_depth=depth)
