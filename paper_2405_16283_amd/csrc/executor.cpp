@@ -951,6 +951,11 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       }
     }
   };
+  // a store that nobody waits for takes the copy stream, and so does one to a buffer the copy kernel's 16-byte pieces do not fit
+  auto chainable = [&](int64_t m) {
+    return ex->succ_start[m + 1] > ex->succ_start[m] &&
+           !(mg.v[m].kind == TN_MG_STORE && (uintptr_t)host_outputs[mg.v[m].output_index] % 16);
+  };
   auto spread = [&]() {
     while (!enqueueable.empty()) {
       const int64_t w = enqueueable.back();
@@ -960,7 +965,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       if (k == TN_MG_INPUT || k == TN_MG_DROP || k == TN_MG_JOIN) {
         ex->last_order.push_back(w);
         tell(w);
-      } else {
+      } else if (chainable(w)) {  // (others would stand in the way of those behind them)
         rq_chain[k == TN_MG_LOAD || k == TN_MG_RELOAD ? 0 : 1].push(w);
       }
     }
@@ -1067,11 +1072,6 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
 
   // Whether the transfers of a direction that are ready now should follow the kernels on the compute stream: the copy
   // stream is idle, all of them together are small, and nothing enqueued for the compute stream takes long.
-  // a store that nobody waits for takes the copy stream, and so does one to a buffer the copy kernel's 16-byte pieces do not fit
-  auto chainable = [&](int64_t m) {
-    return ex->succ_start[m + 1] > ex->succ_start[m] &&
-           !(mg.v[m].kind == TN_MG_STORE && (uintptr_t)host_outputs[mg.v[m].output_index] % 16);
-  };
   auto chain_now = [&](int dir) {
     if (!chain || !xq[dir].empty() || n_ready_x[dir] > max_xfer) return false;
     for (const Group& g : ex->cqueue[0])
@@ -1101,7 +1101,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
           r.pop();
           continue;
         }
-        if (part && (bytes + x.bytes > kChainBytes || !chainable(m))) break;
+        if (part && bytes + x.bytes > kChainBytes) break;
         const void* src;
         void* dst;
         if (x.kind == TN_MG_LOAD) {

@@ -184,3 +184,18 @@ def test_an_offload_waits_for_room_in_the_arena(fake, depth):
         assert e.value.status == B.TN_ERR_ARENA and fake.fake_pending() == 0
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("policy", [B.TN_POLICY_BY_ORDER, B.TN_POLICY_FIFO])
+def test_a_store_nobody_waits_for_does_not_hold_up_offloads(fake, policy):
+    """Small tensors, so that every GPU -> host copy that something waits for can follow the kernel before it."""
+    s = llama(fake, "c1", kv_outputs=True)
+    try:
+        e = H.export_memgraph(s.mg)
+        waited = {a for a, _, _ in e["edges"] if e["kind"][a] in ("offload", "store")}
+        assert 0 < len(waited) < s.stats.n_offload + s.stats.n_store
+        _, _, log = s.run(policy=policy, queue_depth=3, max_gemm_inflight=1)
+        c = chained(log)
+        assert c.n[c.to_gpu == 0].sum() == len(waited)
+    finally:
+        s.close()
