@@ -466,7 +466,10 @@ enum { TN_POLICY_FIFO = 0, TN_POLICY_LIFO = 1, TN_POLICY_RANDOM = 2, TN_POLICY_B
  * to tn_compile) gets copies of up to a whole slot instead of one per tensor, which for tensors of
  * 512 KiB is the difference between 22 and 40 GB/s.  (Stores to host memory from a kernel are accepted slowly by
  * the link and hold up the memory traffic of the kernels that run beside them.)
- * AUTO: KERNEL_IN when all host buffers of the call qualify, otherwise MEMCPY. */
+ * AUTO: when all host buffers of the call qualify, as KERNEL_IN, but GPU -> host groups of at most
+ * 256 KiB are written to host memory by the copy kernel (7 us for 64 KiB against 20), and small copies may be
+ * chained between kernels (see queue_depth); otherwise MEMCPY.
+ * A program with a transfer of 4 GiB or more runs with MEMCPY whatever is asked for. */
 enum { TN_COPY_AUTO = 0, TN_COPY_MEMCPY = 1, TN_COPY_KERNEL = 2, TN_COPY_KERNEL_IN = 3 };
 
 typedef struct {
@@ -478,7 +481,7 @@ typedef struct {
   int32_t profile;       /* != 0: time every launch with HIP events (fills the *_ms fields) */
   int32_t max_transfers; /* most ready copies of one direction put into one group; 0 = default (32; while they are
                             below 4 MiB together, 128) */
-  int32_t copy_engine;   /* TN_COPY_AUTO, TN_COPY_MEMCPY or TN_COPY_KERNEL */
+  int32_t copy_engine;   /* TN_COPY_AUTO, TN_COPY_MEMCPY, TN_COPY_KERNEL or TN_COPY_KERNEL_IN */
   int32_t max_gemm_inflight; /* most GEMM groups running at once; 0 = as many as there are streams */
   int32_t queue_depth;   /* kernel groups in flight per compute stream (1..8; 0 = 1).  1: a kernel is
                             launched when its dependencies have completed.  >1: it may be enqueued once the
@@ -490,9 +493,9 @@ typedef struct {
                             launches that are over within microseconds do not count towards the depth. */
   int32_t transfer_depth;  /* groups of copies in flight per direction (1..8; 0 = 3): the next group is enqueued
                               while the host has not yet seen the previous one complete */
-  int32_t copy_workgroups; /* TN_COPY_KERNEL: workgroups of a copy launch (each walks over 32 KiB pieces of the
-                              group's tensors); 0 = default (8) */
-  int32_t d2h_workgroups;  /* TN_COPY_KERNEL: workgroups of a GPU -> host copy launch; 0 = copy_workgroups */
+  int32_t copy_workgroups; /* workgroups of a launch of the copy kernel (each walks over 32 KiB pieces of the
+                              group's tensors); 0 = default (8; 16 for copies chained between kernels) */
+  int32_t d2h_workgroups;  /* the same for its GPU -> host launches; 0 = copy_workgroups */
   int32_t small_gemm_tiles; /* a group of bf16 tile products with at most this many 256x256 output tiles is launched
                                with 128x128 tiles per workgroup instead (four times the workgroups, the same bits);
                                0 = default (128), negative = never */

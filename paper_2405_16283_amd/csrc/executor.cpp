@@ -75,7 +75,7 @@ constexpr uint64_t kGroupBytes = 4u << 20;
 // 5.2, 4.8, 4.6 ms; without chaining 14, 5.5 and 5.9 ms.
 constexpr uint64_t kChainBytes = 512u << 10;
 constexpr uint64_t kChainMeanBytes = 384u << 10;  // no chaining where a program's loads, reloads and offloads are larger on average
-constexpr int kChainWorkgroups = 16;  // a piece of 32 KiB each: no kernel runs beside them
+constexpr int kChainWorkgroups = 16;  // by default, a piece of 32 KiB each: no kernel runs beside them
 // GPU -> host groups up to this size are written to host memory by the copy kernel: a staging copy and a runtime copy
 // behind it take 20 us for 64 KiB, the kernel 7.
 constexpr uint64_t kDirectStoreBytes = 256u << 10;
@@ -858,7 +858,8 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   // kernels enqueued early only split the groups of tile products (layer with 512 KiB tiles under 40 % of its peak 9.06 ms
   // unchained, 9.14 chained; with tiles of 288 KiB 5.5 and 4.0).  And not where the arena cannot hold every offload: a chained
   // one takes its slot before the kernel before it has ended, when the reloads that give slots back are not yet allowed.
-  const bool chain = arena_need <= ex->arena_bytes && ahead && copy_bytes <= n_copies * kChainMeanBytes && ex->n_compute == 1 && kernel_copies && opt.max_delay_us == 0 && opt.policy != TN_POLICY_IN_ORDER;
+  // (TN_COPY_KERNEL_IN asks for the copy engines in one direction.)
+  const bool chain = arena_need <= ex->arena_bytes && ahead && copy_bytes <= n_copies * kChainMeanBytes && ex->n_compute == 1 && kernel_copies && opt.copy_engine != TN_COPY_KERNEL_IN && opt.max_delay_us == 0 && opt.policy != TN_POLICY_IN_ORDER;
   ex->remaining = ex->indeg;
   std::vector<int64_t> rem_enq(ex->indeg);           // dependencies not yet enqueued (kernels, chained copies) or completed
   std::vector<hipEvent_t> ev_of(nv, nullptr);        // event of the group a kernel vertex was enqueued in
@@ -1145,7 +1146,8 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
     grp.brief = true;
     hipError_t e = hipSuccess;
     if (opt.profile && prof_pair(&grp.prof)) e = hipEventRecord(ex->prof_events[grp.prof], stream);
-    if (e == hipSuccess) e = launch_copies(copies, kChainWorkgroups, stream);
+    const int wgs = (dir == 1 && opt.d2h_workgroups > 0) ? opt.d2h_workgroups : opt.copy_workgroups;
+    if (e == hipSuccess) e = launch_copies(copies, wgs > 0 ? wgs : kChainWorkgroups, stream);
     if (e == hipSuccess && grp.prof >= 0) e = hipEventRecord(grp.done = ex->prof_events[grp.prof + 1], stream);
     if (e != hipSuccess) { hip_fail("chained transfer", e); return false; }
     if (grp.prof >= 0) ex->prof_recs.push_back({3 + dir, grp.prof, (int32_t)xverts.size(), (int64_t)bytes, (double)bytes});
@@ -1341,7 +1343,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
             pos += (stage_sizes[k] + 255) / 256 * 256;
           }
         }
-        bool direct = stage_used <= kDirectStoreBytes;
+        bool direct = stage_used <= kDirectStoreBytes && opt.copy_engine == TN_COPY_AUTO;
         for (int64_t m : stage_verts)
           direct = direct && (mg.v[m].kind == TN_MG_OFFLOAD || (uintptr_t)host_outputs[mg.v[m].output_index] % 16 == 0);
         if (!direct) e = launch_copies(copies, kStageGatherWorkgroups, sl.stream);

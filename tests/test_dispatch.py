@@ -199,3 +199,25 @@ def test_a_store_nobody_waits_for_does_not_hold_up_offloads(fake, policy):
         assert c.n[c.to_gpu == 0].sum() == len(waited)
     finally:
         s.close()
+
+
+def test_options_of_the_copies_hold_for_chained_and_small_groups(fake):
+    s = llama(fake, "c1", kv_outputs=True)
+    try:
+        want, _, log = s.run(policy=B.TN_POLICY_BY_ORDER, queue_depth=3)
+        to_host = log[(log.kind == COPY) & (log.to_gpu == 0)]
+        assert len(chained(log)) and (to_host.stream == D2H).any()  # what the default does with groups of this size
+        # the copy engines take what goes to the host
+        for depth in (1, 3):
+            got, _, log = s.run(policy=B.TN_POLICY_BY_ORDER, queue_depth=depth, copy_engine=B.TN_COPY_KERNEL_IN)
+            assert got == want and not len(chained(log))
+            assert ((log.kind == MEMCPY) & (log.to_gpu == 0)).any() and not ((log.kind == COPY) & (log.to_gpu == 0)).any()
+        # workgroups per direction, tensors per group
+        for engine in (B.TN_COPY_AUTO, B.TN_COPY_KERNEL):
+            got, _, log = s.run(policy=B.TN_POLICY_BY_ORDER, queue_depth=3, copy_engine=engine, copy_workgroups=3, d2h_workgroups=2,
+                                max_transfers=2)
+            c = log[(log.kind == COPY) & ((log.to_gpu == 0) | (log.stream != D2H))]  # (not the gathering into a staging slot)
+            assert got == want and len(chained(c)) and (c.n <= 2).all()
+            assert (c.detail == np.where(c.to_gpu == 1, 3, 2)).all()
+    finally:
+        s.close()
