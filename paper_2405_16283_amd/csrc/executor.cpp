@@ -46,7 +46,8 @@ struct VInfo {
   int32_t nblocks = 0;
   int32_t row_key = -1;  // single-row products: vertices with one key multiply the same B tiles
   int64_t lock = -1;  // increments: the vertex whose output they add to; one of them runs at a time
-  double flops = 0, bytes = 0;
+  double flops = 0, bytes = 0;  // bytes: of products and attention, what no other vertex of a launch is likely to read too
+  bool deep = false;            // a product whose walk along K takes long however little there is to do
 };
 
 struct Slot {  // one stream and the group it carries
@@ -79,8 +80,9 @@ constexpr int kChainWorkgroups = 16;  // by default, a piece of 32 KiB each: no 
 // GPU -> host groups up to this size are written to host memory by the copy kernel: a staging copy and a runtime copy
 // behind it take 20 us for 64 KiB, the kernel 7.
 constexpr uint64_t kDirectStoreBytes = 256u << 10;
-// A kernel group that costs less than an event's way to the host and back (about 10 us).
-constexpr double kShortFlops = 1e9, kShortBytes = 8e6;
+// A brief kernel group: its work takes a few microseconds.  (What a few workgroups wait for memory comes on top: a product
+// that walks K of 4096 alone takes 15 us, reverse attention of 160 positions 18.  An event's way to the host and back takes 10.)
+constexpr double kShortFlops = 1e9, kShortBytes = 8e6, kShortK = 4096;
 
 struct Group {  // one grouped kernel launch in flight on a compute stream, or (family 3, 4) a chained group of copies
   std::vector<int64_t> verts;
@@ -180,6 +182,7 @@ struct tn_executor {
   size_t image_bytes = 0, image_off[4] = {0, 0, 0, 0};
   DeviceTables tables{};
   std::vector<VInfo> info;
+  std::vector<double> row_bytes;  // single-row products: bytes of the B tiles of every row_key
   // dependency structure (CSR of successors)
   std::vector<int64_t> succ_start, succ, indeg;
   // kernel vertices, host-to-device transfers and device-to-host transfers, each in the serial
@@ -295,8 +298,12 @@ tn_status build_tables(tn_executor& ex) {
           std::vector<int64_t> key(x.operands.begin() + x.p.nk, x.operands.begin() + (x.p.mode == 2 ? 3 : 2) * x.p.nk);
           key.push_back(x.p.mode);
           vi.row_key = row_keys.emplace(std::move(key), (int32_t)row_keys.size()).first->second;
+          ex.row_bytes.resize(row_keys.size(), K * elem_bytes(d.dtype) * (x.p.mode == 2 ? 2.0 : 1.0) * d.cols);
         }
         vi.flops = (x.p.mode == 2 ? 4.0 : 2.0) * d.rows * d.cols * K;
+        // A thin product is bound by its long operand; others do 16 and more operations for every byte they read.
+        if (vi.cls != LC_GEMM_ROWS && std::min(d.rows, d.cols) < 64) vi.bytes = K * elem_bytes(d.dtype) * (d.rows + (x.p.mode == 2 ? 2.0 : 1.0) * d.cols);
+        vi.deep = K > kShortK;
         // Products of very different depth do not share a launch.  The workgroups of a launch that run at the same
         // time read the same operand panels at the same moment only as long as they walk along K in step, and that
         // sharing in the L2s is what feeds them: 22016-deep products started one by one between 4096-deep ones
@@ -354,6 +361,7 @@ tn_status build_tables(tn_executor& ex) {
                      ? LC_ATTN_BF16 : LC_ATTN_F32;
         vi.head_dim = (int16_t)hd;
         vi.flops = 4.0 * visible_pairs(q_rows, kv_rows, x.p) * (double)(nc * tc);
+        vi.bytes = (q_rows + 2.0 * kv_rows) * nc * tc * elem_bytes(d.dtype);
         break;
       }
       case TN_OP_ATTN_COMBINE:
@@ -432,6 +440,7 @@ tn_status build_tables(tn_executor& ex) {
                      ? (int8_t)(LC_ATTN_BWD_BF16 + x.p.mode) : (int8_t)LC_ATTN_BWD;
         vi.head_dim = (int16_t)hd;
         vi.flops = (x.p.mode == 3 ? 4.0 : 6.0) * visible_pairs(q_rows, kv_rows, x.p) * (double)(nc * tc);
+        vi.bytes = (2.0 * q_rows + 2.0 * kv_rows) * nc * tc * elem_bytes(d.dtype);
         break;
       }
       default: return fail(TN_ERR_INVALID, "vertex %lld has an unknown kind", (long long)m);
@@ -1534,6 +1543,14 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       int32_t max_blocks = 0;
       int64_t n_blocks = 0;
       double flops = 0, bytes = 0;
+      bool deep = false;
+      if (lead.cls == LC_GEMM_ROWS) {  // rows of one key next to each other: they are formed together, and read B once
+        row_list.clear();
+        for (int64_t m : same) row_list.push_back({ex->info[m].row_key, (uint32_t)ex->info[m].desc});
+        std::sort(row_list.begin(), row_list.end(), [](const RowVertex& a, const RowVertex& b) { return a.key < b.key; });
+        for (size_t k = 0; k < row_list.size(); ++k)
+          if (k == 0 || row_list[k].key != row_list[k - 1].key) bytes += ex->row_bytes[row_list[k].key];
+      }
       for (int k = 0; k < batch.n; ++k) {
         const VInfo& v = ex->info[same[k]];
         batch.idx[k] = (uint16_t)(v.desc - batch.base);
@@ -1541,6 +1558,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
         n_blocks += v.nblocks;
         flops += v.flops;
         bytes += v.bytes;
+        deep = deep || v.deep;
       }
       hipError_t e = hipSuccess;
       // device-side waits for kernels this group depends on that are enqueued on other streams
@@ -1557,7 +1575,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       }
       Group grp;
       grp.family = family_of(lead.cls);
-      grp.brief = flops <= kShortFlops && bytes <= kShortBytes;
+      grp.brief = flops <= kShortFlops && bytes <= kShortBytes && !deep;
       if (!(chain && grp.brief)) {
         // nobody should have to wait for this group to learn that the brief ones before it are over
         if (auto& q = ex->cqueue[si]; !q.empty() && !q.back().done) {
@@ -1577,9 +1595,6 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
         n_blocks *= 4;
       }
       if (e == hipSuccess && lead.cls == LC_GEMM_ROWS) {
-        row_list.clear();
-        for (int64_t m : same) row_list.push_back({ex->info[m].row_key, (uint32_t)ex->info[m].desc});
-        std::sort(row_list.begin(), row_list.end(), [](const RowVertex& a, const RowVertex& b) { return a.key < b.key; });
         e = launch_gemm_rows(lead.dtype, tables, batch.base, row_list.data(), batch.n, max_blocks, stream);
       } else if (e == hipSuccess) {
         e = launch_batch(launch_cls, lead.dtype, lead.head_dim, tables, batch, max_blocks, stream);

@@ -221,3 +221,56 @@ def test_options_of_the_copies_hold_for_chained_and_small_groups(fake):
             assert (c.detail == np.where(c.to_gpu == 1, 3, 2)).all()
     finally:
         s.close()
+
+
+def _behind(fake, make):
+    """Six vertices that each read a small tensor of their own, loaded into the place of the one before, and what `make`
+    keeps in GPU memory; returns for every chained load how many kernels it stood behind."""
+    tg = B.tn_taskgraph_create()
+    add = lambda r, c, where=B.TN_DEVICE: B.tn_taskgraph_add_input(tg, B.TN_F32, r, c, where)
+    shape, op, held = make(tg, add)
+    for _ in range(6):
+        B.tn_taskgraph_mark_output(tg, op(add(*shape, B.TN_HOST)))
+    small = max(B.tn_taskgraph_vertex(tg, B.tn_taskgraph_num_vertices(tg) - 1).desc.rows * B.tn_taskgraph_vertex(
+        tg, B.tn_taskgraph_num_vertices(tg) - 1).desc.cols, shape[0] * shape[1]) * 4
+    s = Session(fake, tg, held + 3 * ((small + 255) // 256 * 256))
+    try:
+        want, _, _ = s.run(queue_depth=1)
+        got, _, log = s.run(queue_depth=3, policy=B.TN_POLICY_BY_ORDER)
+        c = chained(log)
+        assert got == want and len(c) > 0
+        return c.kernels_before[c.to_gpu == 1]
+    finally:
+        s.close()
+
+
+def _rows(k, n):
+    def make(tg, add):
+        b = add(n, k)
+        return (1, k), lambda x: B.tn_taskgraph_add_op(tg, B.TN_OP_GEMM, B.tn_op_params(nk=1, trans_b=1), [x, b], B.TN_F32, 1, n), k * n * 4
+    return make
+
+
+def _product(m, n, k):
+    def make(tg, add):
+        a, b = add(m, k), add(n, k)
+        p = B.tn_op_params(nk=1, trans_b=1, mode=1)
+        return (m, n), lambda x: B.tn_taskgraph_add_op(tg, B.TN_OP_GEMM, p, [a, b, x], B.TN_F32, m, n), (m + n) * k * 4
+    return make
+
+
+def _attention(keys):
+    def make(tg, add):
+        k, v = add(keys, 64), add(keys, 64)
+        p = B.tn_op_params(n_q_tiles=1, n_kv_tiles=1, n_col_tiles=1, head_dim=64, scale=0.125)
+        return (4, 64), lambda x: B.tn_taskgraph_add_op(tg, B.TN_OP_ATTN_BLOCK, p, [x, k, v], B.TN_F32, 4, 66), 2 * keys * 64 * 4
+    return make
+
+
+@pytest.mark.parametrize("brief,long", [(_rows(512, 512), _rows(2048, 2048)), (_product(64, 64, 1024), _product(64, 64, 8192)),
+                                        (_product(32, 1024, 256), _product(32, 1024, 2048)), (_attention(256), _attention(32768))],
+                         ids=["rows", "deep", "thin", "attention"])
+def test_copies_are_chained_behind_brief_kernels_only(fake, brief, long):
+    """A kernel bound by what it reads, or by its walk along K, keeps the stream from a copy for long however few its operations are."""
+    assert (_behind(fake, brief) > 0).any()
+    assert not _behind(fake, long).any()
