@@ -75,7 +75,13 @@ constexpr uint64_t kGroupBytes = 4u << 20;
 // could have run beside kernels), bf16 layer with 288 KiB tiles 5.4, 5.0, 4.1, 3.8 ms, fp32 layer with 256 KiB tiles 5.6,
 // 5.2, 4.8, 4.6 ms; without chaining 14, 5.5 and 5.9 ms.
 constexpr uint64_t kChainBytes = 512u << 10;
-constexpr uint64_t kChainMeanBytes = 384u << 10;  // no chaining where a program's loads, reloads and offloads are larger on average
+// No chaining where a program's loads, reloads and offloads are larger than this on average: what chaining gains, it gains per
+// copy, what it costs goes by their bytes.  Chained against not chained, for layers of 3 to 8 tiles of one size under 40 % of
+// their peak, by mean size in KiB: fp32 64 0.69 of the time, 139 0.75, 247 0.78, 380 0.85, 547 0.97, 744 0.98; bf16 32 0.66, 125 0.86,
+// 196 0.86, 278 0.92, 379 0.89, 495 0.97, 613 1.00, 759 0.99.  Decode steps in tiles of 512 KiB 370 0.97, 480 0.98, fine-tuning
+// steps 480 1.04; a layer of 4096 tokens compiled so that copies have room 495 1.01, since kernels enqueued early are launched
+// in smaller groups (layers of smaller tiles compiled so: 0.97 to 1.08, and 0.78 for 15).
+constexpr uint64_t kChainMeanBytes = 384u << 10;
 constexpr int kChainWorkgroups = 16;  // by default, a piece of 32 KiB each: no kernel runs beside them
 // GPU -> host groups up to this size are written to host memory by the copy kernel: a staging copy and a runtime copy
 // behind it take 20 us for 64 KiB, the kernel 7.
@@ -820,12 +826,15 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   const int depth = std::max(1, std::min<int>(opt.queue_depth > 0 ? opt.queue_depth : 1, kMaxQueueDepth));
   const bool ahead = depth > 1;
   // every buffer the run will touch must be there before anything is launched
-  uint64_t n_copies = 0, copy_bytes = 0, arena_need = 0;
+  uint64_t n_copies = 0, copy_bytes = 0, arena_need = 0, largest_copy = 0;
   for (int64_t m = 0; m < nv; ++m) {
     const MVertex& x = mg.v[m];
     if (x.kind == TN_MG_LOAD || x.kind == TN_MG_RELOAD || x.kind == TN_MG_OFFLOAD) {  // what kernels wait for
       ++n_copies;
       copy_bytes += x.bytes;
+      largest_copy = std::max(largest_copy, x.bytes);
+    } else if (x.kind == TN_MG_STORE) {
+      largest_copy = std::max(largest_copy, x.bytes);
     }
     if (x.kind == TN_MG_OFFLOAD) arena_need += (x.bytes + 255) / 256 * 256;
     if (x.kind == TN_MG_LOAD && (!host_inputs || !host_inputs[x.src]))
@@ -853,9 +862,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       return fail(TN_ERR_INVALID, "copy_engine KERNEL needs every host buffer to be GPU-addressable pinned memory");
     kernel_copies = kernel_copies && ok;
     // a copy kernel's list holds sizes of 32 bits: programs with a larger transfer leave theirs to the runtime
-    for (const MVertex& x : mg.v)
-      if ((x.kind == TN_MG_LOAD || x.kind == TN_MG_RELOAD || x.kind == TN_MG_OFFLOAD || x.kind == TN_MG_STORE) && x.bytes > UINT32_MAX)
-        kernel_copies = false;
+    kernel_copies = kernel_copies && largest_copy <= UINT32_MAX;
   }
   // Chained transfers.  Under a cap far below a small program's working set every other vertex is a copy of a few tiles
   // that waits for the kernel before it and that the kernel behind it waits for.  Seen from the host each such step
@@ -863,12 +870,13 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   // takes as long, 14 us), one behind the other on one stream 2.8 (6.7 with an event between them).  So with a
   // single compute stream, copies that wait only for work enqueued there follow that work on the compute stream as
   // long as they are small (kChainBytes, 10 us on the link: what a longer copy keeps the stream from is worth more
-  // than the two steps) and nothing else is there to be launched.  Not in programs whose copies are mostly larger: there
-  // kernels enqueued early only split the groups of tile products (layer with 512 KiB tiles under 40 % of its peak 9.06 ms
-  // unchained, 9.14 chained; with tiles of 288 KiB 5.5 and 4.0).  And not where the arena cannot hold every offload: a chained
-  // one takes its slot before the kernel before it has ended, when the reloads that give slots back are not yet allowed.
-  // (TN_COPY_KERNEL_IN asks for the copy engines in one direction.)
-  const bool chain = arena_need <= ex->arena_bytes && ahead && copy_bytes <= n_copies * kChainMeanBytes && ex->n_compute == 1 && kernel_copies && opt.copy_engine != TN_COPY_KERNEL_IN && opt.max_delay_us == 0 && opt.policy != TN_POLICY_IN_ORDER;
+  // than the two steps) and nothing else is there to be launched.  Not in programs whose copies are larger.  Programs
+  // without copies keep what comes with it, launches that are over within microseconds without an event each and
+  // beyond the depth (32 decode steps on resident weights 2.5 ms, 2.8 without).  And not where the arena cannot hold every
+  // offload: a chained one takes its slot before the kernel before it has ended, when the reloads that give slots back are not
+  // yet allowed.  (TN_COPY_KERNEL_IN asks for the copy engines in one direction.)
+  const bool chain = arena_need <= ex->arena_bytes && ahead && ex->n_compute == 1 && kernel_copies && opt.copy_engine != TN_COPY_KERNEL_IN &&
+                     opt.max_delay_us == 0 && opt.policy != TN_POLICY_IN_ORDER && copy_bytes <= n_copies * kChainMeanBytes;
   ex->remaining = ex->indeg;
   std::vector<int64_t> rem_enq(ex->indeg);           // dependencies not yet enqueued (kernels, chained copies) or completed
   std::vector<hipEvent_t> ev_of(nv, nullptr);        // event of the group a kernel vertex was enqueued in
@@ -1126,7 +1134,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
             dst = host_outputs[x.output_index];
           } else {
             uint64_t off;
-            if (!ex->arena || !arena_alloc(*ex, x.bytes, &off)) {  // (the arena holds every offload)
+            if (!ex->arena || !arena_alloc(*ex, x.bytes, &off)) {  // (does not happen: the arena holds every offload)
               status = fail(TN_ERR_ARENA, "pinned host arena of %llu bytes is exhausted", (unsigned long long)ex->arena_bytes);
               return false;
             }

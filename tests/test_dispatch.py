@@ -274,3 +274,36 @@ def test_copies_are_chained_behind_brief_kernels_only(fake, brief, long):
     """A kernel bound by what it reads, or by its walk along K, keeps the stream from a copy for long however few its operations are."""
     assert (_behind(fake, brief) > 0).any()
     assert not _behind(fake, long).any()
+
+
+@pytest.mark.parametrize("rows,chains", [(384, True), (385, False)])
+def test_chaining_goes_by_the_mean_size_of_the_copies(fake, rows, chains):
+    tg = B.tn_taskgraph_create()
+    for _ in range(12):
+        x = B.tn_taskgraph_add_input(tg, B.TN_F32, rows, 256, B.TN_HOST)  # a KiB per row
+        B.tn_taskgraph_mark_output(tg, B.tn_taskgraph_add_op(tg, B.TN_OP_ADD, B.tn_op_params(), [x, x], B.TN_F32, rows, 256))
+    s = Session(fake, tg, 4 * rows * 1024)
+    try:
+        want, _, _ = s.run(queue_depth=1)
+        got, _, log = s.run(queue_depth=3, policy=B.TN_POLICY_BY_ORDER)
+        assert got == want and (len(chained(log)) > 0) == chains
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("depth,limit", [(1, 1), (2, 24)])
+def test_brief_kernels_of_a_program_without_copies_go_beyond_the_depth(fake, depth, limit):
+    """A chain of 40 additions on resident inputs: how many are enqueued and not over at a time."""
+    tg = B.tn_taskgraph_create()
+    x = v = B.tn_taskgraph_add_input(tg, B.TN_F32, 1, 256, B.TN_DEVICE)
+    for _ in range(40):
+        v = B.tn_taskgraph_add_op(tg, B.TN_OP_ADD, B.tn_op_params(), [v, x], B.TN_F32, 1, 256)
+    B.tn_taskgraph_mark_output(tg, v)
+    s = Session(fake, tg, 1 << 16)
+    try:
+        want, _, _ = s.run(queue_depth=1)
+        got, _, log = s.run(3, queue_depth=depth, policy=B.TN_POLICY_BY_ORDER)
+        most = 1 + log.kernels_before[log.kind == KERNEL].max()
+        assert got == want and (most == limit if depth == 1 else depth < most <= limit)
+    finally:
+        s.close()
