@@ -289,7 +289,7 @@ tn_status build_tables(tn_executor& ex) {
         }
         const bool big = k32 && d.rows >= 256 && d.cols >= 256;
         // the fused forms (mode 1: + residual, mode 2: gated pair) exist in the 256-tile kernel, which clamps its
-        // loads and guards its stores for any shape, and in the generic one, which the thinnest products take
+        // loads and guards its stores for any shape, and in the 32x32 and single-row ones, which the thinnest products take
         const bool fused_mfma = x.p.mode != 0 && k32 && d.rows >= 64;
         // Small outputs leave a 128x128 workgroup mostly empty and alone with its walk along K.  Measured at K of 4096,
         // 32x32 tiles against 128x128 ones: 32 products of 512x16, 28 against 59 us, two of them 15 against 56; 8 of

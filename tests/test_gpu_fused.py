@@ -1,6 +1,6 @@
 """GPU parity of the fused product vertices (fuse_epilogues: the residual as a last operand of the product
 before it; the gated pair of products with silu * up), through the C ABI, against the oracle's own fused
-graph: small shapes on the generic kernel, the mid-size shapes on the 256-tile MFMA kernel, under caps that
+graph: small shapes on the kernels for small tiles, the mid-size shapes on the 256-tile kernel, under caps that
 offload, across dispatch orders.  (The one-layer workload at full size runs fused in test_gpu_c2.py, as the
 benchmark tiles it.)"""
 import numpy as np
@@ -59,7 +59,7 @@ def test_fused_forward_matches_the_oracle_under_the_cap(name, fuse):
 def test_fused_product_vertex_alone(mode, shape):
     """One vertex of each fused mode on hand-built graphs, two k tiles, weights stored [out, in]: shapes the
     256-tile kernel takes whole, ragged in rows and columns and smaller than one tile (its clamped loads and
-    guarded stores), and shapes that go to the generic kernel (K not a multiple of 32, fewer than 64 rows),
+    guarded stores), and shapes that go to the 32x32 kernel (K not a multiple of 32, fewer than 64 rows),
     against the oracle's vertex in float64."""
     m, n, k = shape
     rng = np.random.default_rng(m + n + mode)
