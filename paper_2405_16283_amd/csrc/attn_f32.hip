@@ -111,16 +111,83 @@ __device__ __forceinline__ void store_chunk_vt(float (*buf)[kRows + 4], const f3
 }
 
 // A row's sum leaves out what the causal mask hides from it.  The matrix cores multiply that by a weight of zero, which
-// is the same as long as it is finite; chunks the diagonal crosses are looked through for infinities and NaN while they
-// are stored, and one that holds some is summed row by row (a wavefront's 64 lanes on 16 rows of HD columns).
-template <int N>
-__device__ __forceinline__ bool not_finite(const f32x4 (&v)[N]) {
+// is the same as long as it is finite.  Chunks the diagonal crosses are looked through for infinities and NaN in LDS;
+// a workgroup that finds some forms its rows again, each summed over what it sees, sixteen lanes to a row (`*_by_rows`: many
+// times slower, and outside the loops on the matrix cores, whose registers and order of instructions it must not cost
+// anything: inside them, and with the look between loads and stores, it took 2 % of a decode program).
+template <int ROWS, int COLS, int PITCH>
+__device__ __forceinline__ bool not_finite(const float (*buf)[PITCH]) {
   float z = 0.f;
 #pragma unroll
-  for (int i = 0; i < N; ++i)
+  for (int i = 0; i < ROWS * COLS / 4 / 256; ++i) {
+    const int p = i * 256 + threadIdx.x;
+    const f32x4 v = *(const f32x4*)&buf[p / (COLS / 4)][p % (COLS / 4) * 4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) z = fmaf(v[i][e], 0.f, z);
+    for (int e = 0; e < 4; ++e) z = fmaf(v[e], 0.f, z);
+  }
   return !(z == 0.f);
+}
+
+// whether any lane of the workgroup says so, once its chunks in LDS are done with
+__device__ __forceinline__ bool any_wave(bool mine, char* lds) {
+  const int wave = __ballot(mine) != 0;
+  int* const said = (int*)lds;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) said[threadIdx.x >> 6] = wave;
+  __syncthreads();
+  return __builtin_expect((said[0] | said[1] | said[2] | said[3]) != 0, 0);
+}
+
+__device__ __forceinline__ float dot4(f32x4 a, f32x4 b) { return fmaf(a[0], b[0], fmaf(a[1], b[1], fmaf(a[2], b[2], a[3] * b[3]))); }
+__device__ __forceinline__ float row_sum(float v) {  // over the sixteen lanes of a row
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+template <typename T, int HD>
+__device__ __forceinline__ void attn_by_rows(DeviceTables t, const OpDesc& d) {
+  const int* ax = t.aux + d.aux0;
+  const int tq = ax[0], tk = ax[1], tc = ax[2], q_rows = ax[3], kv_rows = ax[4], nc = d.p.n_col_tiles, gw = nc * tc;
+  const int qblocks = (q_rows + kRows - 1) / kRows, h = blockIdx.x / qblocks, qb = blockIdx.x % qblocks;
+  void* const* Qt = t.ptrs + d.ptr0;
+  void* const* Kt = Qt + d.p.n_q_tiles * nc;
+  const Side<T, HD> Q(Qt, nc, tq, tc, q_rows, h), K(Kt, nc, tk, tc, kv_rows, h), V(Kt + d.p.n_kv_tiles * nc, nc, tk, tc, kv_rows, h);
+  constexpr int C = HD / 64;  // pieces of four columns per lane: c0, c0 + 64
+  const int c0 = (threadIdx.x & 15) * 4;
+#pragma unroll 1
+  for (int row = qb * kRows + (threadIdx.x >> 4); row < min(Q.rows, (qb + 1) * kRows); row += 16) {
+    f32x4 q[C], o[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+      q[i] = Q.at(row, c0 + 64 * i) * d.p.scale;
+      o[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    float m = -INFINITY, l = 0.f;
+    const int seen = min(K.rows, d.p.q_pos0 + row - d.p.k_pos0 + 1);
+#pragma unroll 1
+    for (int k = 0; k < seen; ++k) {
+      float s = 0.f;
+#pragma unroll
+      for (int i = 0; i < C; ++i) s += dot4(q[i], K.at(k, c0 + 64 * i));
+      s = row_sum(s);
+      const float mn = fmaxf(m, s), ms = mn == -INFINITY ? 0.f : mn;
+      const float alpha = __expf(m - ms), p = __expf(s - ms);
+      m = mn;
+      l = l * alpha + p;
+#pragma unroll
+      for (int i = 0; i < C; ++i) o[i] = o[i] * alpha + (d.p.v_trans ? V.at_t(k, c0 + 64 * i) : V.at(k, c0 + 64 * i)) * p;
+    }
+    float* out = (float*)d.out + (size_t)row * d.cols;
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[h * HD + c0 + 64 * i + e] = o[i][e];
+    if (c0 == 0) {
+      out[gw + h] = m;
+      out[gw + gw / HD + h] = l;
+    }
+  }
 }
 
 // aux: [rows per Q tile, rows per K/V tile, columns per tile, q rows, kv rows]
@@ -144,8 +211,7 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch 
   extern __shared__ __attribute__((aligned(16))) char lds[];
   float(*const ks)[HD + 4] = (float(*)[HD + 4])lds;                                   // K chunk [64][HD], padded
   float(*const vs)[kRows + 4] = (float(*)[kRows + 4])(lds + sizeof(float) * kRows * (HD + 4));  // V^T chunk [HD][64], padded
-  int* const odd = (int*)(lds + sizeof(float) * (kRows * (HD + 4) + HD * (kRows + 4)));  // first key of a chunk whose V is not finite
-  if (threadIdx.x == 0) *odd = -1;
+  bool odd = false;  // a chunk on the diagonal whose V is not finite
 
   const int row = qb * kRows + w * 16 + n, qpos = d.p.q_pos0 + row;
   const int wpos0 = d.p.q_pos0 + qb * kRows + w * 16;  // first position of the wavefront
@@ -169,7 +235,6 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch 
     load_chunk_vt<T, HD, 0, P>(V, v_trans, 0, vn);
   }
   for (int kv0 = 0; kv0 < end; kv0 += kRows) {
-    const bool diagonal = causal && k_pos0 + kv0 + kRows - 1 > d.p.q_pos0 + qb * kRows;  // some row does not see some key
     __syncthreads();  // everybody is done with the chunk before
     if constexpr (!kAhead) {
       load_chunk<T, HD, 0, P>(K, false, kv0, kn);
@@ -177,19 +242,18 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch 
     }
     store_chunk<HD, 0, P>(ks, kn);
     store_chunk_vt<HD, 0, P>(vs, vn);
-    if (diagonal && not_finite(vn)) *odd = kv0;
     if constexpr (!kAhead) {
       load_chunk<T, HD, P, P>(K, false, kv0, kn);
       load_chunk_vt<T, HD, P, P>(V, v_trans, kv0, vn);
       store_chunk<HD, P, P>(ks, kn);
       store_chunk_vt<HD, P, P>(vs, vn);
-      if (diagonal && not_finite(vn)) *odd = kv0;
     }
     __syncthreads();
     if (kAhead && kv0 + kRows < end) {
       load_chunk<T, HD, 0, P>(K, false, kv0 + kRows, kn);
       load_chunk_vt<T, HD, 0, P>(V, v_trans, kv0 + kRows, vn);
     }
+    if (causal && k_pos0 + kv0 + kRows - 1 > d.p.q_pos0 + qb * kRows && not_finite<HD, kRows>(vs)) odd = true;
     f32x4 s[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) s[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -230,24 +294,6 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch 
       }
 #pragma unroll
     for (int j = 0; j < HD / 16; ++j) o[j] *= alpha;
-    if (diagonal && *odd == kv0) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll 1
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const int key = 16 * k + 4 * q4 + i;
-            const float p = __shfl(s[k][i], n + 16 * q4, 64);
-            if (kv0 + key < kv_rows && k_pos0 + kv0 + key <= qpos) {
-#pragma unroll
-              for (int j = 0; j < HD / 16; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[j][e] = fmaf(p, vs[16 * j + 4 * g + e][key], o[j][e]);
-            }
-          }
-      continue;
-    }
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -262,6 +308,7 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch 
         if (j & 4) __builtin_amdgcn_sched_barrier(0);
       }
   }
+  if (causal && any_wave(odd, lds)) return attn_by_rows<T, HD>(t, d);
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
   if (row >= q_rows) return;
@@ -279,6 +326,44 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(DeviceTables t, Batch 
   if (g == 0) {
     out[gw + h] = m;
     out[gw + hpg + h] = l;
+  }
+}
+
+template <typename T, int HD, int MODE, typename Stat>
+__device__ __forceinline__ void attn_bwd_by_rows(const OpDesc& d, const Side<T, HD>& Q, const Side<T, HD>& K, const Side<T, HD>& V,
+                                                 const Side<T, HD>& D, int rb, int h, int gw, Stat stat) {
+  constexpr int C = HD / 64;
+  const Side<T, HD>&own = MODE == 1 ? Q : K, &other = MODE == 1 ? K : Q;
+  const int c0 = (threadIdx.x & 15) * 4;
+  auto v_at = [&](int r, int c) { return d.p.v_trans ? V.at_t(r, c) : V.at(r, c); };
+#pragma unroll 1
+  for (int row = rb * kRows + (threadIdx.x >> 4); row < min(own.rows, (rb + 1) * kRows); row += 16) {
+    f32x4 m1[C], m2[C], acc[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+      m1[i] = own.at(row, c0 + 64 * i);
+      m2[i] = MODE == 1 ? D.at(row, c0 + 64 * i) : v_at(row, c0 + 64 * i);
+      acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    const int begin = MODE == 1 ? 0 : max(0, d.p.k_pos0 + row - d.p.q_pos0);
+    const int end = MODE == 1 ? min(K.rows, d.p.q_pos0 + row - d.p.k_pos0 + 1) : Q.rows;
+#pragma unroll 1
+    for (int o = begin; o < end; ++o) {
+      float s = 0.f, dp = 0.f;
+#pragma unroll
+      for (int i = 0; i < C; ++i) {
+        s += dot4(m1[i], other.at(o, c0 + 64 * i));
+        if (MODE != 3) dp += dot4(m2[i], MODE == 1 ? v_at(o, c0 + 64 * i) : D.at(o, c0 + 64 * i));
+      }
+      const int q = MODE == 1 ? row : o;
+      float p = __expf(row_sum(s) * d.p.scale - stat(q, 0));
+      if (MODE != 3) p *= (row_sum(dp) - stat(q, 1)) * d.p.scale;
+#pragma unroll
+      for (int i = 0; i < C; ++i) acc[i] += (MODE == 3 ? D.at(o, c0 + 64 * i) : other.at(o, c0 + 64 * i)) * p;
+    }
+    T* out = (T*)d.out + (size_t)row * gw + h * HD + c0;
+#pragma unroll
+    for (int i = 0; i < C; ++i) st4(out + 64 * i, acc[i]);
   }
 }
 
@@ -311,8 +396,7 @@ __device__ __forceinline__ void attn_bwd_f32_body(const DeviceTables& t, const O
   float(*const x1)[HD + 4] = (float(*)[HD + 4])lds;                                             // K, or Q
   float(*const x2)[HD + 4] = (float(*)[HD + 4])(lds + sizeof(float) * kRows * (HD + 4));        // V, or dO
   float(*const xs)[2] = (float(*)[2])(lds + 2 * sizeof(float) * kRows * (HD + 4));              // statistics of the queries
-  int* const odd = (int*)(lds + sizeof(float) * (2 * kRows * (HD + 4) + 2 * kRows));  // first row of a chunk that is not finite
-  if (threadIdx.x == 0) *odd = -1;
+  bool odd = false;  // a chunk on the diagonal that is not finite
 
   const int row = rb * kRows + w * 16 + n, rc = min(row, my_rows - 1);
   const int pos = (MODE <= 1 ? d.p.q_pos0 : d.p.k_pos0) + row;
@@ -339,12 +423,13 @@ __device__ __forceinline__ void attn_bwd_f32_body(const DeviceTables& t, const O
     __syncthreads();  // everybody is done with the chunk before
     store_chunk<HD>(x1, v1);
     store_chunk<HD>(x2, v2);
-    // some row of the workgroup and some row of the chunk do not see each other
-    const bool diagonal = causal && (MODE <= 1 ? d.p.k_pos0 + r0 + kRows - 1 > d.p.q_pos0 + rb * kRows
-                                               : d.p.k_pos0 + rb * kRows + kRows - 1 > d.p.q_pos0 + r0);
-    if (MODE != 0 && diagonal && not_finite(MODE == 3 ? v2 : v1)) *odd = r0;
     if (MODE >= 2 && threadIdx.x < 2 * kRows) xs[threadIdx.x / 2][threadIdx.x & 1] = sv;
     __syncthreads();
+    // some row of the workgroup and some row of the chunk do not see each other
+    if (MODE != 0 && causal && (MODE == 1 ? d.p.k_pos0 + r0 + kRows - 1 > d.p.q_pos0 + rb * kRows
+                                          : d.p.k_pos0 + rb * kRows + kRows - 1 > d.p.q_pos0 + r0) &&
+        not_finite<kRows, HD>(MODE == 3 ? x2 : x1))
+      odd = true;
 #pragma unroll 1
     for (int k = 0; k < 4; k += 2) {  // two 16-row tiles of the other side at a time
       f32x4 s[2], dp[2];
@@ -403,22 +488,6 @@ __device__ __forceinline__ void attn_bwd_f32_body(const DeviceTables& t, const O
         }
         // acc^T[column, own row] += X^T[column, other row] wgt[other row, own row]; X: K, Q or dO
         float(*const xt)[HD + 4] = MODE == 3 ? x2 : x1;
-        if (diagonal && *odd == r0) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-#pragma unroll 1
-            for (int q4 = 0; q4 < 4; ++q4) {
-              const int lr = 16 * (k + e) + 4 * q4 + c, o = r0 + lr;
-              const float p = __shfl(wgt[c], n + 16 * q4, 64);
-              if (o < o_rows && (MODE <= 1 ? d.p.k_pos0 + o <= pos : pos <= d.p.q_pos0 + o)) {
-#pragma unroll
-                for (int j = 0; j < HD / 16; ++j)
-#pragma unroll
-                  for (int i = 0; i < 4; ++i) acc[j][i] = fmaf(p, xt[lr][16 * j + 4 * g + i], acc[j][i]);
-              }
-            }
-          continue;
-        }
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -444,6 +513,7 @@ __device__ __forceinline__ void attn_bwd_f32_body(const DeviceTables& t, const O
     }
     return;
   }
+  if (causal && any_wave(odd, lds)) return attn_bwd_by_rows<T, HD, MODE>(d, Q, K, V, D, rb, h, gw, stat);
   if (row >= my_rows) return;
   T* out = (T*)d.out + (size_t)row * gw + h * HD;
 #pragma unroll
@@ -463,8 +533,8 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_f32_kernel(DeviceTables t, Ba
   }
 }
 
-constexpr int fwd_lds(int hd) { return 4 * (kRows * (hd + 4) + hd * (kRows + 4) + 4); }
-constexpr int bwd_lds(int hd) { return 4 * (2 * kRows * (hd + 4) + 2 * kRows + 4); }
+constexpr int fwd_lds(int hd) { return 4 * (kRows * (hd + 4) + hd * (kRows + 4)); }
+constexpr int bwd_lds(int hd) { return 4 * (2 * kRows * (hd + 4) + 2 * kRows); }
 
 template <auto kernel>
 hipError_t launch(int lds, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t s) {
