@@ -86,15 +86,19 @@ constexpr int kChainWorkgroups = 16;  // by default, a piece of 32 KiB each: no 
 // GPU -> host groups up to this size are written to host memory by the copy kernel: a staging copy and a runtime copy
 // behind it take 20 us for 64 KiB, the kernel 7.
 constexpr uint64_t kDirectStoreBytes = 256u << 10;
-// A brief kernel group: its work takes a few microseconds.  (What a few workgroups wait for memory comes on top: a product
-// that walks K of 4096 alone takes 15 us, reverse attention of 160 positions 18.  An event's way to the host and back takes 10.)
-constexpr double kShortFlops = 1e9, kShortBytes = 8e6, kShortK = 4096;
+// A brief kernel group: little arithmetic, not worth an event of its own (4 us on the stream, 10 to the host and back).  A quick
+// one is brief and over in about 10 us, also where it is bound by what it reads or by its walk along K: copies may stand
+// behind it.  (What a few workgroups wait for memory comes on top: reverse attention of 160 positions takes 18 us.)
+// Brief groups that read more than kUnseenBytes since the last event, about 20 us, get one all the same where copies might wait
+// for them.  Without copies they do not: single-row products over 10-100 MB of weights with an event each made decode steps on
+// resident weights 1-4 % slower.
+constexpr double kShortFlops = 1e9, kShortBytes = 8e6, kShortK = 4096, kUnseenBytes = 64e6;
 
 struct Group {  // one grouped kernel launch in flight on a compute stream, or (family 3, 4) a chained group of copies
   std::vector<int64_t> verts;
   hipEvent_t done = nullptr;  // none: seen complete with the next group of its stream that has one
   int family = 0, prof = -1;
-  bool brief = false;
+  bool brief = false, quick = false;
 };
 
 struct XGroup {  // one group of copies in flight on a copy stream
@@ -1056,6 +1060,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   auto finish_group = [&](const Group& g) {
     for (int64_t m : g.verts) finish(m);
   };
+  double unseen = 0;  // what kernel groups read that were enqueued since the last one with an event
   auto next_event = [&](Group& g, int si) {
     g.done = ex->cevents[si][ring_next[si]];
     ring_next[si] = (ring_next[si] + 1) % kMaxChain;
@@ -1093,7 +1098,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   auto chain_now = [&](int dir) {
     if (!chain || !xq[dir].empty() || n_ready_x[dir] > max_xfer) return false;
     for (const Group& g : ex->cqueue[0])
-      if (!g.brief) return false;
+      if (!g.quick) return false;
     uint64_t bytes = 0;
     bool all = true;
     auto look = [&](int64_t m) {
@@ -1160,7 +1165,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
     hipStream_t stream = ex->slots[0].stream;
     Group grp;
     grp.family = 3 + dir;
-    grp.brief = true;
+    grp.brief = grp.quick = true;
     hipError_t e = hipSuccess;
     if (opt.profile && prof_pair(&grp.prof)) e = hipEventRecord(ex->prof_events[grp.prof], stream);
     const int wgs = (dir == 1 && opt.d2h_workgroups > 0) ? opt.d2h_workgroups : opt.copy_workgroups;
@@ -1583,8 +1588,11 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       }
       Group grp;
       grp.family = family_of(lead.cls);
-      grp.brief = flops <= kShortFlops && bytes <= kShortBytes && !deep;
-      if (!(chain && grp.brief)) {
+      grp.brief = flops <= kShortFlops && (grp.family != 2 || bytes <= kShortBytes);
+      grp.quick = grp.brief && bytes <= kShortBytes && !deep;
+      unseen += bytes;
+      if (!(chain && grp.brief) || (n_copies > 0 && (unseen > kUnseenBytes || deep))) {
+        unseen = 0;
         // nobody should have to wait for this group to learn that the brief ones before it are over
         if (auto& q = ex->cqueue[si]; !q.empty() && !q.back().done) {
           next_event(q.back(), si);
