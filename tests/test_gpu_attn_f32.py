@@ -156,3 +156,42 @@ def test_what_the_mask_hides_stays_hidden(dtype, hd, v_trans, which, value):
         assert np.array_equal(np.isfinite(a), fine), name
         if fine.any():
             assert R.rel_err(a[fine], b[fine]) < TOL[dtype], name
+
+
+@pytest.mark.parametrize("which", ["k", "v", "q", "do"])
+@pytest.mark.parametrize("dtype,hd,tc,tq,tk,q_pos0,v_trans", [("f32", 64, 32, 48, 40, 0, 0), ("f32", 128, 256, 64, 33, 21, 1),
+                                                              ("bf16", 64, 128, 50, 48, 7, 0)])
+def test_what_the_mask_hides_stays_hidden_over_tiles(dtype, hd, tc, tq, tk, q_pos0, v_trans, which):
+    """The same with two heads, the second of which holds a NaN, over tiles that cut rows and heads anywhere."""
+    print(f"[case] NaN in {which}, {dtype} head size {hd}, tiles {tq}, {tk} rows, {tc} columns, queries from {q_pos0}", flush=True)
+    rng = np.random.default_rng(tq)
+    kv_rows, scale, gw = 131, 1.0 / np.sqrt(hd), 2 * hd
+    q_rows = kv_rows - q_pos0
+    full = {n: rng.standard_normal((q_rows if n in ("q", "do") else kv_rows, gw)) for n in ("q", "k", "v", "do")}
+    full[which][90, hd + 3] = np.nan
+    g = Graph(dtype)
+    qt, kt = _ranges(q_rows, tq), _ranges(kv_rows, tk)
+    q, Q = _grid(g, full["q"], qt, tc)
+    k, K = _grid(g, full["k"], kt, tc)
+    v, V = _grid(g, full["v"], kt, tc, bool(v_trans))
+    do, DO = _grid(g, full["do"], qt, tc)
+    nc = gw // tc
+    p = dict(n_q_tiles=len(qt), n_kv_tiles=len(kt), n_col_tiles=nc, head_dim=hd, q_pos0=q_pos0, k_pos0=0, causal=1, scale=scale,
+             v_trans=v_trans)
+    blk = g.op(B.TN_OP_ATTN_BLOCK, q + k + v, q_rows, gw + 4, f32=True, **p)
+    stats = [g.op(B.TN_OP_ATTN_BWD, q[i * nc:(i + 1) * nc] + k + v + do[i * nc:(i + 1) * nc], r1 - r0, 4, f32=True, mode=0,
+                  **dict(p, n_q_tiles=1, q_pos0=q_pos0 + r0)) for i, (r0, r1) in enumerate(qt)]
+    grads = [g.op(B.TN_OP_ATTN_BWD, q + k + v + do + stats, rows, gw, mode=m, **p) for m, rows in ((1, q_rows), (2, kv_rows), (3, kv_rows))]
+    with np.errstate(all="ignore"):
+        out, *rest = g.run([blk] + stats + grads)
+        st, (dq, dk, dv) = np.concatenate(rest[:-3]), rest[-3:]
+        for h in range(2):
+            sl = slice(h * hd, (h + 1) * hd)
+            got = [st[:, h:h + 1], st[:, 2 + h:3 + h], out[:, sl] / out[:, gw + 2 + h:gw + 3 + h], dq[:, sl], dk[:, sl], dv[:, sl]]
+            want = _masked_reference(Q[:, sl], K[:, sl], V[:, sl], DO[:, sl], scale, q_pos0)
+            for name, a, b in zip(("lse", "D", "output", "dQ", "dK", "dV"), got, want):
+                fine = np.isfinite(b)
+                assert h == 1 or fine.all()
+                assert np.array_equal(np.isfinite(a), fine), (h, name)
+                if fine.any():
+                    assert R.rel_err(a[fine], b[fine]) < TOL[dtype], (h, name)
