@@ -483,8 +483,8 @@ typedef struct {
                             below 4 MiB together, 128) */
   int32_t copy_engine;   /* TN_COPY_AUTO, TN_COPY_MEMCPY, TN_COPY_KERNEL or TN_COPY_KERNEL_IN */
   int32_t max_gemm_inflight; /* most GEMM groups running at once; 0 = as many as there are streams.  With chained copies
-                              (see queue_depth) another one may follow while all that is enqueued is over within
-                              microseconds and no load is under way */
+                              (see queue_depth) another one may follow while all that is enqueued is brief and no
+                              load is under way */
   int32_t queue_depth;   /* kernel groups in flight per compute stream (1..8; 0 = 1).  1: a kernel is
                             launched when its dependencies have completed.  >1: it may be enqueued once the
                             kernels it depends on are enqueued, ordered on the device by stream events;
@@ -493,8 +493,9 @@ typedef struct {
                             TN_POLICY_IN_ORDER, TN_COPY_AUTO or TN_COPY_KERNEL with pinned buffers, an arena for every
                             offload, loads, reloads and offloads of at most 384 KiB on average or none) copies of
                             up to 512 KiB together that wait only for enqueued kernels are enqueued on that stream
-                            behind them, and launches that are over within microseconds do not count towards
-                            the depth (24 groups at most). */
+                            behind them, as long as those are over in about 10 us, and brief launches (products and
+                            attention of at most 1 GFLOP, others of at most 8 MB) do not count towards the depth
+                            (24 groups at most). */
   int32_t transfer_depth;  /* groups of copies in flight per direction (1..8; 0 = 3): the next group is enqueued
                               while the host has not yet seen the previous one complete */
   int32_t copy_workgroups; /* workgroups of a launch of the copy kernel (each walks over 32 KiB pieces of the

@@ -875,7 +875,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
   // single compute stream, copies that wait only for work enqueued there follow that work on the compute stream as
   // long as they are small (kChainBytes, 10 us on the link: what a longer copy keeps the stream from is worth more
   // than the two steps) and nothing else is there to be launched.  Not in programs whose copies are larger.  Programs
-  // without copies keep what comes with it, launches that are over within microseconds without an event each and
+  // without copies keep what comes with it, brief launches without an event each and
   // beyond the depth (32 decode steps on resident weights 2.5 ms, 2.8 without).  And not where the arena cannot hold every
   // offload: a chained one takes its slot before the kernel before it has ended, when the reloads that give slots back are not
   // yet allowed.  (TN_COPY_KERNEL_IN asks for the copy engines in one direction.)
