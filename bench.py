@@ -44,8 +44,8 @@ HOST_LINK_GBS = 64.0  # PCIe Gen5 x16, per direction
 # against 51 with the defaults; 10 to 16 workgroups measure within 2 % of one another, 24 cost 5 %); on
 # the compute-bound c3 the same setting costs 20 %.  On c5 the small groups of tile products appear while
 # the link is the bottleneck (the reverse pass waits for reloads), and spread over all compute units they
-# slow the copy kernel more than they gain (1.34 against 1.30 s per step); on c4 the 128x128 workgroups share
-# compute units with the copy workgroups, which the 256x256 ones do not, and run at 133 TFLOP/s (62 launches, 63 ms
+# slow the copy kernel more than they gain (1.34 against 1.30 s per step); on c4 128x128 workgroups that share
+# compute units with the copy workgroups, which the 256x256 ones do not, ran at 133 TFLOP/s (62 launches, 63 ms
 # of a step: tile products 960 -> 1010 TFLOP/s in situ without them; the step is bound by the link either way).  The one-layer workload streamed
 # under a fraction of its peak is bound by the link as well: 16 copy workgroups move 52 GB/s beside the tile
 # products where 8 move 45 (11.0 -> 9.9 ms per step under 40 %; larger groups do not help it further).
@@ -171,7 +171,7 @@ def main():
     ap.add_argument("--transfer-depth", type=int, default=0)
     ap.add_argument("--d2h-workgroups", type=int, default=0)
     ap.add_argument("--small-gemm-tiles", type=int, default=0,
-                    help="executor option small_gemm_tiles: 0 = default (128), negative = always 256x256 tiles")
+                    help="executor option small_gemm_tiles: 0 = the form that fills the chip better, negative = always 256x256 tiles")
     ap.add_argument("--train", type=int, default=-1,
                     help="1: fine-tuning step (adapters of rank 16 on q and v, probe loss, reverse pass); default: only for c5")
     ap.add_argument("--layers", type=int, default=0, help="run the workload's shape with this many layers instead of its own")
@@ -413,7 +413,7 @@ def main():
                      "queue_depth": args.queue_depth,
                      "copy_engine": args.copy_engine, "max_transfers": args.max_transfers or TRANSFERS.get(name, (0, 0))[0] or 32,
                      "copy_workgroups": args.copy_workgroups or TRANSFERS.get(name, (0, 0))[1] or 8,
-                     "small_gemm_tiles": args.small_gemm_tiles or SMALL_GEMM_TILES.get(name, 0) or 128,
+                     "small_gemm_tiles": args.small_gemm_tiles or SMALL_GEMM_TILES.get(name, 0),
                      "max_delay_us": args.max_delay_us, "k_split": k_split,
                      "materialize_scores": bool(materialize), "checkpoint": bool(checkpoint)},
         }
@@ -434,7 +434,7 @@ def main():
         subs.append("c2_capped40")
 
     rec, cfg, full, y = run_case(head_name, args.steps, args.warmup, headline=True)
-    gemm_kernel = "gemm_bf16_nt256_kernel" if cfg.dtype == "bf16" else "gemm_small_kernel"
+    gemm_kernel = "gemm_bf16_256_kernel" if cfg.dtype == "bf16" else "gemm_small_kernel"
     config_keys = ("workload", "gpu_cap_bytes", "distinct_layers", "kv_outputs", "outputs", "serial_order", "memgraph", "exec")
     top_keys = config_keys + ("host_link", "mfma", "gpu_idle_frac", "tokens_per_s", "ms_per_step", "steps", "warmup")
     line = {

@@ -503,7 +503,7 @@ typedef struct {
   int32_t d2h_workgroups;  /* the same for its GPU -> host launches; 0 = copy_workgroups */
   int32_t small_gemm_tiles; /* a group of bf16 tile products with at most this many 256x256 output tiles is launched
                                with 128x128 tiles per workgroup instead (four times the workgroups, the same bits);
-                               0 = default (128), negative = never */
+                               0 = default (whichever form fills the chip better), negative = never */
 } tn_exec_opts;
 
 typedef struct {

@@ -44,6 +44,7 @@ struct VInfo {
   int16_t group = -1;  // index of its (cls, dtype, head_dim, depth) combination: vertices of one group can share a launch
   int32_t desc = -1;
   int32_t nblocks = 0;
+  int32_t nblocks128 = 0;  // LC_GEMM_BF16: workgroups in its 128x128 forms
   int32_t row_key = -1;  // single-row products: vertices with one key multiply the same B tiles
   int64_t lock = -1;  // increments: the vertex whose output they add to; one of them runs at a time
   double flops = 0, bytes = 0;  // bytes: of products and attention, what no other vertex of a launch is likely to read too
@@ -61,11 +62,10 @@ struct Slot {  // one stream and the group it carries
   double flops = 0, bytes = 0;
 };
 
-constexpr int64_t kSmallGemmTiles = 128;
 // Offloads moved by the chip's copy engines (TN_COPY_KERNEL_IN) are first gathered, by a copy inside GPU
 // memory, into one of these staging slots, so that a whole group leaves with a single large copy.
 constexpr uint64_t kStageBytes = 16ull << 20;
-constexpr int kStageGatherWorkgroups = 64;  // see the launch of tile products in run_memgraph
+constexpr int kStageGatherWorkgroups = 64;
 
 // Between two groups of copies the link rests for 5 us, and 1 MiB takes the copy kernel 21 us instead of the 18 of a
 // MiB of a larger group: 32 tensors of 32 KiB to a group keep the link at 39 GB/s, 4 MiB at 54.
@@ -231,6 +231,17 @@ double visible_pairs(int q_rows, int kv_rows, const tn_op_params& p) {
   return n;
 }
 
+// The form in which tile products are launched that take n256 workgroups for 256x256 tiles or n128 for 128x128 tiles (with one of these per CU
+// up to 256).  Workgroups for 128x128 tiles fill 512 places at once (two per CU), for 256x256 tiles 256; a round of the former takes 0.6 of a round of the
+// latter (measured 0.54 to 0.67: with K of 4096, 512 and 256 workgroups take 64-70 and 104-118 us).  The last round of a launch
+// takes less the emptier it is, the clock rises: counted as half full.  1371 x 4096 with K of 11008, 96 or 352 workgroups: 192 and
+// 138 us, 0.69 : 0.51 by this rule; 1371 x 11008 gate and up: 276 and 265, 2.5 : 2.3; 4096 x 12288: 300 and 370, 3 : 3.6.
+int gemm_form(int64_t n256, int64_t n128) {
+  if (n128 <= 256) return LC_GEMM_BF16_128;
+  const double c256 = (double)((n256 + 255) / 256) + n256 / 256.0, c128 = (double)((n128 + 511) / 512) + n128 / 512.0;
+  return 0.6 * c128 < c256 ? LC_GEMM_BF16_PAIRED : LC_GEMM_BF16;
+}
+
 // the table pointers for a copy of the image that starts at `base`
 DeviceTables tables_at(const tn_executor& ex, const char* base) {
   return {(const OpDesc*)(base + ex.image_off[0]), (void* const*)(base + ex.image_off[1]),
@@ -281,26 +292,22 @@ tn_status build_tables(tn_executor& ex) {
     switch (x.op_kind) {
       case TN_OP_GEMM: {
         if (x.p.trans_c) std::swap(d.rows, d.cols);  // the kernels work on the logical [rows, cols] product
-        bool mfma = d.dtype == TN_BF16 && d.trans_b && (!x.p.trans_a || d.rows == 1), k32 = true, k4 = true;
+        bool mfma = d.dtype == TN_BF16 && d.trans_b && (!x.p.trans_a || d.rows == 1), k4 = true;
         double K = 0;
         for (int k = 0; k < x.p.nk; ++k) {
           const int32_t kk = x.p.trans_a ? odesc(k).rows : odesc(k).cols;
           aux.push_back(kk);
           K += kk;
           if (kk % 8) mfma = false;
-          if (kk % 32) k32 = false;
           if (kk % 4) k4 = false;
         }
-        const bool big = k32 && d.rows >= 256 && d.cols >= 256;
-        // the fused forms (mode 1: + residual, mode 2: gated pair) exist in the 256-tile kernel, which clamps its
-        // loads and guards its stores for any shape, and in the 32x32 and single-row ones, which the thinnest products take
-        const bool fused_mfma = x.p.mode != 0 && k32 && d.rows >= 64;
         // Small outputs leave a 128x128 workgroup mostly empty and alone with its walk along K.  Measured at K of 4096,
         // 32x32 tiles against 128x128 ones: 32 products of 512x16, 28 against 59 us, two of them 15 against 56; 8 of
         // 16x512 with K of 16384, 53 against 223; 64x64 with K of 512, 64 of them, 5.7 against 13.  From 128x128 up the
         // larger tile's reuse wins once a launch holds more than 64 (256 of them: 120 against 43).
         const bool small = std::min(d.rows, d.cols) <= 32 || (int64_t)d.rows * d.cols <= 64 * 128;
-        vi.cls = !mfma ? LC_GEMM_F32 : (big || fused_mfma) ? LC_GEMM_BF16_NT256 : (small || x.p.mode != 0) ? LC_GEMM_BF16_SMALL : LC_GEMM_BF16_NT;
+        vi.cls = !mfma ? LC_GEMM_F32 : small ? LC_GEMM_BF16_SMALL : d.rows >= 256 && d.cols >= 256 ? LC_GEMM_BF16 : LC_GEMM_BF16_128;
+        vi.nblocks128 = gemm_blocks(128, d);
         // Single rows against the same B tiles are formed together (32 rows against 24 tiles of 512 with K of 4096: 486
         // us one by one, B coming from the caches for every one of them).
         if (d.rows == 1 && d.trans_b && (d.dtype == TN_BF16 ? mfma : k4)) {
@@ -594,8 +601,8 @@ int family_of(int cls) {
     case LC_GEMM_F32:
     case LC_GEMM_BF16_SMALL:
     case LC_GEMM_ROWS:
-    case LC_GEMM_BF16_NT:
-    case LC_GEMM_BF16_NT256: return 0;
+    case LC_GEMM_BF16_128:
+    case LC_GEMM_BF16: return 0;
     case LC_ATTN_F32:
     case LC_ATTN_BF16:
     case LC_ATTN_BWD:
@@ -1533,7 +1540,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       // take a contiguous run of them.  Arrange the tile products so that vertices next to each
       // other share operands both ways -- blocks of two A row panels by four B column panels --
       // instead of one A panel against every B panel of the launch.
-      if (lead.cls == LC_GEMM_BF16_NT256 && same.size() >= 16) {
+      if (lead.cls == LC_GEMM_BF16 && same.size() >= 16) {
         auto b0 = [&](int64_t m) { return mg.v[m].operands[mg.v[m].p.nk]; };
         std::vector<int64_t>& bs = sort_b;
         bs.clear();
@@ -1601,14 +1608,22 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
         next_event(grp, si);
       }
       if (e == hipSuccess && opt.profile && prof_pair(&grp.prof)) e = hipEventRecord(ex->prof_events[grp.prof], stream);
-      // A group of tile products with at most kSmallGemmTiles 256x256 tiles leaves CUs without work for as long
-      // as one tile takes; cut into 128x128 tiles (at most four per 256x256 tile, two workgroups per CU) it is
-      // spread over four times as many workgroups that all run at once.  The bits do not depend on the form.
       int launch_cls = lead.cls;
-      if (lead.cls == LC_GEMM_BF16_NT256 && n_blocks <= (opt.small_gemm_tiles > 0 ? opt.small_gemm_tiles : opt.small_gemm_tiles < 0 ? 0 : kSmallGemmTiles)) {
-        launch_cls = LC_GEMM_BF16_NT256_SMALL;
-        max_blocks *= 4;
-        n_blocks *= 4;
+      if (lead.cls == LC_GEMM_BF16 || lead.cls == LC_GEMM_BF16_128) {
+        int64_t n128 = 0;
+        int32_t max128 = 0;
+        for (int64_t m : same) {
+          n128 += ex->info[m].nblocks128;
+          max128 = std::max(max128, ex->info[m].nblocks128);
+        }
+        const int by_128 = n128 <= 256 ? LC_GEMM_BF16_128 : LC_GEMM_BF16_PAIRED;
+        if (lead.cls == LC_GEMM_BF16_128) launch_cls = by_128;
+        else if (opt.small_gemm_tiles == 0) launch_cls = gemm_form(n_blocks, n128);
+        else if (n_blocks <= opt.small_gemm_tiles) launch_cls = by_128;  // (the caller can say which groups)
+        if (launch_cls != LC_GEMM_BF16) {
+          n_blocks = n128;
+          max_blocks = max128;
+        }
       }
       if (e == hipSuccess && lead.cls == LC_GEMM_ROWS) {
         e = launch_gemm_rows(lead.dtype, tables, batch.base, row_list.data(), batch.n, max_blocks, stream);

@@ -32,8 +32,8 @@ enum LaunchClass {
   LC_GEMM_F32 = 0,   // GEMM with fp32 products, any layout, fp32 or bf16 storage
   LC_GEMM_BF16_SMALL,  // MFMA bf16 GEMM for small or thin products, B tiles stored [cols, K], 32x32 tile per workgroup
   LC_GEMM_ROWS,      // single-row products, either type (see launch_gemm_rows)
-  LC_GEMM_BF16_NT,   // MFMA bf16 GEMM, B tiles stored [cols, K], 128x128 tile per workgroup
-  LC_GEMM_BF16_NT256,  // the same for output tiles of at least 256x256: 256x256 per workgroup
+  LC_GEMM_BF16_128,  // MFMA bf16 GEMM, B tiles stored [cols, K], 128x128 tile per workgroup
+  LC_GEMM_BF16,      // the same for outputs of at least 256x256: 256x256 or 128x128 per workgroup
   LC_RMS_STAT,
   LC_RMS_APPLY,
   LC_ROPE,
@@ -55,9 +55,8 @@ enum LaunchClass {
   LC_SOFTMAX_STAT,   // row maximum and sum of exponentials over the score tiles of a row block
   LC_SOFTMAX_APPLY,  // probabilities of one score tile
   LC_COUNT,
-  // Not a class of its own for grouping: the form in which a group of LC_GEMM_BF16_NT256 vertices is
-  // launched when it has too few 256x256 tiles to give every CU one (128x128 tiles, same bits).
-  LC_GEMM_BF16_NT256_SMALL
+  // Not a class of its own for grouping: 128x128 tiles with two workgroups per CU, a form for launches of either of the two above.
+  LC_GEMM_BF16_PAIRED
 };
 
 // Vertices per launch.  The list travels in the kernel arguments (4 KiB at most), as 16-bit
@@ -120,6 +119,13 @@ int32_t blocks_for(int cls, const OpDesc& d, const int32_t* aux);
 // type and (for attention) the head size.  max_blocks = largest nblocks in the batch.
 hipError_t launch_batch(int cls, int dtype, int head_dim, const DeviceTables& t, const Batch& b,
                         int32_t max_blocks, hipStream_t stream);
+
+// The three forms of bf16 tile products: gemm_bf16.hip.  The bits of a product do not depend on the form.
+inline int32_t gemm_blocks(int tile, const OpDesc& d) {  // workgroups for output tiles of tile x tile
+  const int q = d.p.mode == 2 ? tile / 2 : tile;         // gate and up products take half a tile's columns each
+  return (int32_t)(((int64_t)d.rows + tile - 1) / tile * (((int64_t)d.cols + q - 1) / q));
+}
+hipError_t launch_gemm_bf16(int form, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t stream);
 
 // LC_GEMM_F32 and LC_GEMM_BF16_SMALL: gemm_small.hip.
 constexpr int kGemmSmallTile = 32;  // output rows and columns per workgroup

@@ -611,205 +611,6 @@ __global__ void __launch_bounds__(256) transpose_kernel(DeviceTables t, Batch b)
     if (c0 + i < C && r0 + tx < R) o[(size_t)(c0 + i) * R + r0 + tx] = tile[tx][i];
 }
 
-// ---------------------------------------------------------------------------------------------
-// MFMA bf16 GEMM, C[M,N] = sum_k A_k[M,K_k] * B_k[N,K_k]^T, fp32 accumulate, bf16 store.
-// 128x128 output tile per workgroup of 4 wavefronts (2x2, 64x64 each = 2x2 MFMA 32x32 tiles),
-// K step 64 staged through LDS.  Rows are padded by 8 elements so that the 16-byte fragment
-// reads of the 32 lanes of a half-wave fall on different banks.
-// ---------------------------------------------------------------------------------------------
-// Writes a wavefront's TI x TJ grid of 32x32 accumulator tiles as bf16.  In an accumulator tile a
-// lane holds column l32 and the rows 8*(r/4) + 4*g + r%4: four consecutive rows per group of four
-// registers, which makes the transposed store (C^T, rows contiguous) an 8-byte store per group.
-template <int TI, int TJ>
-__device__ __forceinline__ void store_c_tiles(const f32x16 (&acc)[TI][TJ], bf16_t* Cp, int M, int N, int row0, int col0,
-                                              int l32, int g, bool trans_c) {
-  const bool wide = trans_c && (M & 3) == 0;
-#pragma unroll
-  for (int i = 0; i < TI; ++i) {
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      const int col = col0 + j * 32 + l32;
-      const f32x16 c = acc[i][j];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const int row = row0 + i * 32 + 8 * a + 4 * g;
-        const uint32_t h01 = f2bf2(c[4 * a], c[4 * a + 1]), h23 = f2bf2(c[4 * a + 2], c[4 * a + 3]);
-        const bf16_t h0 = (bf16_t)h01, h1 = (bf16_t)(h01 >> 16), h2 = (bf16_t)h23, h3 = (bf16_t)(h23 >> 16);
-        if (wide) {
-          if (col < N && row < M) {
-            uint2 v;
-            v.x = h01;
-            v.y = h23;
-            *(uint2*)(Cp + (size_t)col * M + row) = v;
-          }
-        } else if (col < N) {
-          const size_t sr = trans_c ? 1 : (size_t)N, sc = trans_c ? (size_t)M : 1;
-          bf16_t* p = Cp + (size_t)row * sr + (size_t)col * sc;
-          if (row < M) p[0] = h0;
-          if (row + 1 < M) p[sr] = h1;
-          if (row + 2 < M) p[2 * sr] = h2;
-          if (row + 3 < M) p[3 * sr] = h3;
-        }
-      }
-    }
-  }
-}
-
-// Accumulator tiles formed with the operands exchanged (B fragments first): acc[i][j] is then the transpose
-// of a 32x32 piece of C -- a lane holds row l32 of row group j and, per group of four registers, the four
-// consecutive columns 8*(r/4) + 4*g + r%4 of column group i.  The wavefront's piece of C (32 TJ rows by
-// 32 NT columns) goes through `stage`, LDS of its own (EpilogueStage<NT, TJ>::BYTES), as bf16 rows of a
-// padded pitch -- 8-byte writes from this layout, 16-byte reads along the rows -- so that every global
-// store instruction writes whole runs of 64 NT bytes.
-// R: a [M, N] bf16 tensor added to the product before the rounding.
-template <int NT, int TJ>
-struct EpilogueStage {
-  static constexpr int PITCH = 64 * NT + 16;  // bytes per row: the lanes of a half-wavefront write 32 rows at once
-  static constexpr int BYTES = 32 * TJ * PITCH;
-};
-template <int NT, int TJ>
-__device__ __forceinline__ void store_c_rows(const f32x16 (&acc)[NT][TJ], char* stage, bf16_t* Cp, int M, int N, int row0,
-                                             int col0, int lane, const bf16_t* R) {
-  constexpr int PITCH = EpilogueStage<NT, TJ>::PITCH;
-  const int l32 = lane & 31, g = lane >> 5;
-#pragma unroll
-  for (int j = 0; j < TJ; ++j) {
-    const int row = row0 + j * 32 + l32;
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      const f32x16 c = acc[i][j];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const int cin = i * 32 + 8 * a + 4 * g;  // column inside the wavefront's piece
-        float v[4] = {c[4 * a], c[4 * a + 1], c[4 * a + 2], c[4 * a + 3]};
-        if (R != nullptr && row < M) {
-          const size_t at = (size_t)row * N + col0 + cin;
-          if ((N & 3) == 0 && col0 + cin + 3 < N) {
-            const uint2 r = *(const uint2*)(R + at);
-            v[0] += __uint_as_float(r.x << 16);
-            v[1] += __uint_as_float(r.x & 0xFFFF0000u);
-            v[2] += __uint_as_float(r.y << 16);
-            v[3] += __uint_as_float(r.y & 0xFFFF0000u);
-          } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-              if (col0 + cin + k < N) v[k] += bf2f(R[at + k]);
-          }
-        }
-        uint2 o;
-        o.x = f2bf2(v[0], v[1]);
-        o.y = f2bf2(v[2], v[3]);
-        *(uint2*)(stage + (j * 32 + l32) * PITCH + cin * 2) = o;
-      }
-    }
-  }
-  // rows of the piece, 16 bytes per lane: 4 NT lanes per row
-  constexpr int LPR = 4 * NT, RPI = 64 / LPR;  // lanes per row, rows per instruction
-  const int rin = lane / LPR, cin = (lane % LPR) * 8;
-  const bool whole = (N & 7) == 0;  // rows of C are 16-byte aligned
-#pragma unroll
-  for (int q = 0; q < 32 * TJ / RPI; ++q) {
-    const int r = q * RPI + rin, row = row0 + r, col = col0 + cin;
-    const uint4 x = *(const uint4*)(stage + r * PITCH + cin * 2);
-    if (row >= M || col >= N) continue;
-    bf16_t* dst = Cp + (size_t)row * N + col;
-    if (whole && col + 7 < N) {
-      *(uint4*)dst = x;
-    } else {
-      const bf16_t* e = (const bf16_t*)&x;
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (col + k < N) dst[k] = e[k];
-    }
-  }
-}
-
-constexpr int GB_M = 128, GB_N = 128, GB_K = 64, GB_LD = GB_K + 8;
-
-__global__ void __launch_bounds__(256) gemm_bf16_nt_kernel(DeviceTables t, Batch b) {
-  const OpDesc& d = t.descs[b.at(blockIdx.y)];
-  if ((int)blockIdx.x >= d.nblocks) return;
-  __shared__ __attribute__((aligned(16))) bf16_t As[GB_M * GB_LD];
-  __shared__ __attribute__((aligned(16))) bf16_t Bs[GB_N * GB_LD];
-  const int M = d.rows, N = d.cols, nk = d.p.nk;
-  const int tn_ = (N + GB_N - 1) / GB_N;
-  const int m0 = (blockIdx.x / tn_) * GB_M, n0 = (blockIdx.x % tn_) * GB_N;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wm = w >> 1, wn = w & 1;
-  const int l32 = lane & 31, g = lane >> 5;
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  for (int kt = 0; kt < nk; ++kt) {
-    const bf16_t* A = (const bf16_t*)t.ptrs[d.ptr0 + kt];
-    const bf16_t* B = (const bf16_t*)t.ptrs[d.ptr0 + nk + kt];
-    const int K = t.aux[d.aux0 + kt];
-    // 128 rows x 8 segments of 16 bytes per operand and K step; 4 segments per thread and operand.
-    // The segments of the next step are fetched into registers while this step is multiplied.
-    uint4 pa[4], pb[4];
-    auto fetch = [&](int k0) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int s = threadIdx.x + 256 * i, r = s >> 3, ks = (s & 7) * 8;
-        pa[i] = make_uint4(0, 0, 0, 0);
-        pb[i] = make_uint4(0, 0, 0, 0);
-        if (m0 + r < M && k0 + ks < K) pa[i] = *(const uint4*)(A + (size_t)(m0 + r) * K + k0 + ks);
-        if (n0 + r < N && k0 + ks < K) pb[i] = *(const uint4*)(B + (size_t)(n0 + r) * K + k0 + ks);
-      }
-    };
-    fetch(0);
-    for (int k0 = 0; k0 < K; k0 += GB_K) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int s = threadIdx.x + 256 * i, r = s >> 3, ks = (s & 7) * 8;
-        *(uint4*)(As + r * GB_LD + ks) = pa[i];
-        *(uint4*)(Bs + r * GB_LD + ks) = pb[i];
-      }
-      __syncthreads();
-      if (k0 + GB_K < K) fetch(k0 + GB_K);
-#pragma unroll
-      for (int s = 0; s < GB_K / 16; ++s) {
-        bf16x8 a[2], bb[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          a[i] = *(const bf16x8*)(As + (wm * 64 + i * 32 + l32) * GB_LD + s * 16 + g * 8);
-          bb[i] = *(const bf16x8*)(Bs + (wn * 64 + i * 32 + l32) * GB_LD + s * 16 + g * 8);
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], bb[j], acc[i][j], 0, 0, 0);
-      }
-      __syncthreads();
-    }
-  }
-  store_c_tiles<2, 2>(acc, (bf16_t*)d.out, M, N, m0 + wm * 64, n0 + wn * 64, l32, g, d.p.trans_c != 0);
-}
-
-// ---------------------------------------------------------------------------------------------
-// MFMA bf16 GEMM for large tiles: 256x256 output tile per workgroup, 4 wavefronts in 2x2, each
-// 128x128 = 4x4 MFMA 32x32x16 tiles (256 accumulator registers per lane).
-//
-// K advances in steps of 32 through a ring of four LDS stages that the global-to-LDS loads of
-// gfx950 fill directly (no staging registers, no LDS store instructions).  The loads of step
-// s+3 are issued while step s computes, so a load has three steps of MFMA work to land; one
-// barrier per step both publishes stage s and frees the stage that step s-1 read.
-//
-// A direct load writes the 64 lanes' 16-byte chunks back to back, so the LDS image of a stage is
-// unpadded: 256 rows x 4 chunks per operand.  Bank conflicts are avoided by choosing *which*
-// chunk each lane fetches: logical chunk c of row r lives at position c ^ ((r >> 2) & 3).
-// ---------------------------------------------------------------------------------------------
-#ifndef TN_GEMM_WAVES
-#define TN_GEMM_WAVES 8
-#endif
-constexpr int G2_K = 32, G2_STAGES = 4;
-// LDS of a workgroup with a tile of bm rows and as many columns: per stage bm x 32 of A, then of B
-constexpr int g2_lds_bytes(int bm) { return G2_STAGES * 2 * bm * G2_K * 2; }  // 128 KiB for 256, 64 KiB for 128
-
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 // 16 bytes per lane from global memory straight into LDS at lds_addr + 16 * lane.  Issued as
@@ -818,11 +619,6 @@ typedef __attribute__((address_space(3))) void* lptr_t;
 __device__ __forceinline__ void load_lds16(const void* gsrc, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gsrc), "s"(lds_addr) : "memory");
 }
-// The same with a wavefront-uniform base address and a 32-bit per-lane byte offset, which leaves
-// the per-step address arithmetic to the scalar unit.
-__device__ __forceinline__ void load_lds16_so(const void* sbase, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_addr) : "memory");
-}
 // Reads of the (read-only, wavefront-uniform) operand tables through the scalar unit, so that
 // they are counted by lgkmcnt and never force a wait on the vector loads in flight.
 __device__ __forceinline__ const void* sload_ptr(const void* const* addr) {
@@ -830,12 +626,6 @@ __device__ __forceinline__ const void* sload_ptr(const void* const* addr) {
   asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(addr) : "memory");
   return v;
 }
-__device__ __forceinline__ int sload_int(const int* addr) {
-  int v;
-  asm volatile("s_load_dword %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(addr) : "memory");
-  return v;
-}
-
 // The idea of xcd_remap for kernels whose workgroups of one vertex share operands (the query blocks of an
 // attention head all read that head's keys and values): vertex by goes to XCD by % 8 as a whole,
 // and vertices that differ in cost (blocks on and off the diagonal) stay spread over the XCDs.
@@ -849,234 +639,6 @@ __device__ __forceinline__ void xcd_remap_rows(int& bx, int& by) {
   const int grp = slot / gx;  // vertices 8 grp .. 8 grp + 7; which XCD takes which rotates with grp, so that a
   by = grp * 8 + ((n + grp) & 7);  // cost pattern with period 8 in the launch order does not pile up on one XCD
   bx = slot - grp * gx;
-}
-
-// NW = wavefronts per workgroup: 4 (2x2, 128x128 each, one per SIMD) or 8 (2x4, 128x64 each, two
-// per SIMD, so that one wavefront's MFMAs fill the time the other spends issuing its loads).
-// MFMA with the accumulator held in the accumulation registers.  Left to itself the compiler
-// keeps the accumulators of this kernel in ordinary vector registers, where the matrix unit's
-// result traffic competes with the fragment reads arriving from LDS.  The asm statements are
-// volatile so that they, and the wait states that follow the last one, keep their order; the
-// same accumulator is not touched again for at least seven other MFMAs.
-#ifndef TN_MFMA_AGPR
-#define TN_MFMA_AGPR 0
-#endif
-__device__ __forceinline__ void mfma_acc(f32x16& acc, const bf16x8& a, const bf16x8& b) {
-#if TN_MFMA_AGPR
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-#else
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-#endif
-}
-__device__ __forceinline__ void mfma_acc_drain() {
-#if TN_MFMA_AGPR
-  asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");  // the last results reach the registers
-#endif
-}
-
-#ifndef TN_GEMM_STAGGER
-#define TN_GEMM_STAGGER(w) (((w) >> 2) & 1)  // wavefronts w and w + 4 share a SIMD
-#endif
-// NW wavefronts in two rows; each holds TI x TJ accumulator tiles of 32x32, so the workgroup's output
-// tile is 64 TI rows by as many columns: (8, 4) is the 256x256 tile, (4, 2) a 128x128 tile with half
-// the LDS and a quarter of the registers, two workgroups per CU, for launches too small to give every
-// CU a 256x256 tile.  Every output element sums its products in the same order of K in all forms (the
-// same MFMA, the same sequence of 16-deep slabs), so the forms agree bit for bit.
-template <int NW, int TI>
-__global__ void __launch_bounds__(64 * NW, TI == 2 ? 2 : 1) gemm_bf16_nt256_kernel(DeviceTables t, Batch b) {
-  constexpr int WNS = NW / 2;             // wavefronts along N
-  constexpr int BM = 64 * TI, BN = BM;    // output tile of the workgroup
-  constexpr int TJ = 2 * TI / WNS;        // 32-column MFMA tiles per wavefront
-  constexpr int NLD = 4 * TI / NW;        // load instructions per thread, operand and step
-  constexpr int OPER_BYTES = BM * G2_K * 2, STAGE_BYTES = 2 * OPER_BYTES;
-  static_assert(TJ >= 1 && NLD >= 1 && BN == 32 * TJ * WNS, "tile shape");
-  int bx, by;
-  xcd_remap(bx, by);
-  const OpDesc& d = t.descs[b.at(by)];
-  const int M = d.rows, N = d.cols, nk = d.p.nk;
-  // Mode 2 (gate and up products, silu(gate) * up): the workgroup's BN rows of B are half gate columns and
-  // half up columns of the same BN / 2 output columns: 32 gate rows, then the 32 up rows of the same outputs,
-  // and so on, so that a wavefront's two 32-column accumulator tiles are the gate and the up of one piece.
-  const bool gated = d.p.mode == 2;
-  static_assert(TJ == 2 && TI % 2 == 0, "the gated form pairs the two accumulator tiles of a wavefront; mode 1 stores in halves");
-  const int bn_out = gated ? BN / 2 : BN;  // output columns per workgroup
-  const int tn_ = (N + bn_out - 1) / bn_out;
-  if (bx >= ((M + BM - 1) / BM) * tn_) return;
-  extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const void* const* ptrA = t.ptrs + d.ptr0;  // A_0.., then nk entries later B_0.. (and nk later again the up tiles)
-  const int* ksz = t.aux + d.aux0;
-  bf16_t* const Cp = (bf16_t*)d.out;
-  const int m0 = (bx / tn_) * BM, n0 = (bx % tn_) * bn_out;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wm = w / WNS, wn = w % WNS;
-  const int l32 = lane & 31, g = lane >> 5;
-
-  f32x16 acc[TI][TJ];
-#pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int j = 0; j < TJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // loader: load instruction i of wavefront w fills chunks [(i*NW + w)*64, +64) of an operand;
-  // this lane's chunk is row (i*NW + w)*16 + lane/4, logical chunk (lane & 3) ^ ((lane >> 4) & 3).
-  // Rows past the edge of a ragged tile are clamped (their products are never stored).  A lane's
-  // byte offset inside an operand tile changes only with the tile's K; the position along K is
-  // added to the (scalar) tile address.
-  const int lrow = w * 16 + (lane >> 2);
-  const int lcol = ((lane & 3) ^ ((lane >> 4) & 3)) * 8;
-  int rowA[NLD], rowB[NLD];
-#pragma unroll
-  for (int i = 0; i < NLD; ++i) {
-    rowA[i] = min(m0 + lrow + i * 16 * NW, M - 1);
-    const int rb = lrow + i * 16 * NW;  // row of the B operand in LDS; gated: columns (rb / 64) * 32 + rb % 32
-    rowB[i] = min(n0 + (gated ? (rb >> 6) * 32 + (rb & 31) : rb), N - 1);
-  }
-  // gated: rows 32..63 of every 64 come from the up tiles; a wavefront's 16-row pieces lie all on one side
-  const int bsel = __builtin_amdgcn_readfirstlane(gated ? nk * (1 + ((w >> 1) & 1)) : nk);
-  int nsteps = 0;
-  for (int k = 0; k < nk; ++k) nsteps += ksz[k] / G2_K;
-  int kt = 0, k0 = 0, K = sload_int(ksz);
-  const bf16_t* A = (const bf16_t*)sload_ptr(ptrA);
-  const bf16_t* B = (const bf16_t*)sload_ptr(ptrA + bsel);
-  uint32_t offA[NLD], offB[NLD];
-  auto set_offsets = [&]() {
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      offA[i] = (uint32_t)(rowA[i] * K + lcol) * 2u;
-      offB[i] = (uint32_t)(rowB[i] * K + lcol) * 2u;
-    }
-  };
-  set_offsets();
-  const uint32_t lds0 = (uint32_t)(size_t)(lptr_t)lds;
-  const uint32_t ldsw = __builtin_amdgcn_readfirstlane(lds0 + w * 1024);
-  auto issue = [&](int stage) {  // loads of the K step (kt, k0) into `stage`, then advance
-    const uint32_t dstA = ldsw + stage * STAGE_BYTES;
-    const bf16_t* a = A + k0;
-    const bf16_t* bq = B + k0;
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      load_lds16_so(a, offA[i], dstA + i * 1024 * NW);
-      load_lds16_so(bq, offB[i], dstA + OPER_BYTES + i * 1024 * NW);
-    }
-    k0 += G2_K;
-    if (k0 >= K && kt + 1 < nk) {
-      ++kt;
-      k0 = 0;
-      const int Kn = sload_int(ksz + kt);
-      A = (const bf16_t*)sload_ptr(ptrA + kt);
-      B = (const bf16_t*)sload_ptr(ptrA + bsel + kt);
-      if (Kn != K) {
-        K = Kn;
-        set_offsets();
-      }
-    }
-  };
-
-  // fragment addresses inside a stage: row-major chunks, swizzled as above
-  const int sw = (l32 >> 2) & 3;
-  // With a residual operand (mode 1) the product is formed with the operands exchanged: the first MFMA
-  // operand (TI fragments, 32 TI rows of its region per wavefront row wm) comes from B and the second (TJ
-  // fragments, wavefront column wn) from A, so an accumulator tile is a piece of C^T and a lane holds runs of
-  // four consecutive columns of one row -- 8-byte pieces of the residual's rows instead of single elements
-  // (see store_c_rows).  The sums are the same sums.  (For the plain product this form measures 2 % slower
-  // than the stores straight from the registers below, so only mode 1 takes it.)
-  const bool exch = d.p.mode == 1;
-  const int fragA = (exch ? OPER_BYTES : 0) + ((wm * 32 * TI + l32) * 4) * 16;
-  const int fragB = (exch ? 0 : OPER_BYTES) + ((wn * 32 * TJ + l32) * 4) * 16;
-  const int c0 = ((0 + g) ^ sw) * 16, c1 = ((2 + g) ^ sw) * 16;
-
-  for (int s = 0; s < G2_STAGES - 1 && s < nsteps; ++s) issue(s);
-  // Each step covers two MFMA slabs of 16 along K, held in the register sets (xa, xb) and
-  // (ya, yb).  While the MFMAs of one slab run, the fragments of the next slab are read,
-  // one LDS read after each MFMA: a wavefront can issue a short instruction in the shadow of
-  // its own MFMA, so the reads cost no matrix-unit time, and both register sets keep their role
-  // from step to step (no copies).  The second slab of a step is multiplied after the barrier
-  // of the next step.
-  bf16x8 xa[TI], xb[TJ], ya[TI], yb[TJ];
-  const bool loads_first = __builtin_amdgcn_readfirstlane(TN_GEMM_STAGGER(w)) != 0;
-#define TN_READ_SLAB(DA, DB, COL)                                                                      \
-  _Pragma("unroll") for (int i = 0; i < TI; ++i) DA[i] = *(const bf16x8*)(st_ + fragA + i * 2048 + COL); \
-  _Pragma("unroll") for (int j = 0; j < TJ; ++j) DB[j] = *(const bf16x8*)(st_ + fragB + j * 2048 + COL);
-#define TN_MFMA_SLAB(SA, SB)                                  \
-  _Pragma("unroll") for (int i = 0; i < TI; ++i)              \
-  _Pragma("unroll") for (int j = 0; j < TJ; ++j) mfma_acc(acc[i][j], SA[i], SB[j]);
-  // one MFMA, then one LDS read, for as many reads as a slab has; the remaining MFMAs follow
-#define TN_INTERLEAVE()                                                          \
-  _Pragma("unroll") for (int q = 0; q < (TI + TJ < TI * TJ ? TI + TJ : TI * TJ); ++q) { \
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                           \
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                           \
-  }                                                                              \
-  if constexpr (TI * TJ > TI + TJ) __builtin_amdgcn_sched_group_barrier(0x008, TI * TJ - (TI + TJ), 0);
-  // stage s must have landed: at most the loads of the next two steps may still be in flight
-  // (2 NLD load instructions per thread and step)
-  constexpr int W2 = NLD == 4 ? 0x4F70 : 0x0F78, W1 = NLD == 4 ? 0x0F78 : 0x0F74;  // vmcnt(16 | 8), vmcnt(8 | 4)
-  static_assert(NLD == 2 || NLD == 4, "the wait counts above are written for 4 or 8 loads per step");
-  for (int s = 0; s < nsteps; ++s) {
-    if (s + 2 < nsteps) __builtin_amdgcn_s_waitcnt(W2);
-    else if (s + 1 < nsteps) __builtin_amdgcn_s_waitcnt(W1);
-    else __builtin_amdgcn_s_waitcnt(0x0F70);                                         // vmcnt(0)
-    __syncthreads();
-    const char* st_ = lds + (s % G2_STAGES) * STAGE_BYTES;
-    const bool more = s + G2_STAGES - 1 < nsteps;
-    // Issuing a load stalls a wavefront for as long as the address path is busy with the loads
-    // of the others, so the two wavefronts of a SIMD issue theirs at different points of a step.
-    if (loads_first && more) issue((s + G2_STAGES - 1) % G2_STAGES);
-    __builtin_amdgcn_sched_barrier(0);
-    if (s > 0) {
-      TN_MFMA_SLAB(ya, yb)
-      TN_READ_SLAB(xa, xb, c0)
-      TN_INTERLEAVE()
-    } else {
-      TN_READ_SLAB(xa, xb, c0)
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (!loads_first && more) issue((s + G2_STAGES - 1) % G2_STAGES);
-    __builtin_amdgcn_sched_barrier(0);
-    TN_MFMA_SLAB(xa, xb)
-    TN_READ_SLAB(ya, yb, c1)
-    TN_INTERLEAVE()
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  if (nsteps > 0) {
-    TN_MFMA_SLAB(ya, yb)
-  }
-#undef TN_READ_SLAB
-#undef TN_MFMA_SLAB
-#undef TN_INTERLEAVE
-  mfma_acc_drain();
-
-  if (gated) {
-    f32x16 act[TI][1];
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float gt = acc[i][0][r];
-        act[i][0][r] = gt / (1.f + __expf(-gt)) * acc[i][1][r];
-      }
-    store_c_tiles<TI, 1>(act, Cp, M, N, m0 + wm * 32 * TI, n0 + wn * 32, l32, g, false);
-    return;
-  }
-  if (!exch) {
-    store_c_tiles<TI, TJ>(acc, Cp, M, N, m0 + wm * 32 * TI, n0 + wn * 32 * TJ, l32, g, d.p.trans_c != 0);
-    return;
-  }
-  // exchanged: this wavefront holds rows m0 + 32 TJ wn .. and columns n0 + 32 TI wm ..; it stores them in
-  // two halves of 16 TI columns through LDS of its own, once nobody reads the last stage any more
-  static_assert(NW * EpilogueStage<TI / 2, TJ>::BYTES <= G2_STAGES * STAGE_BYTES, "the epilogue's rows fit the stages' LDS");
-  __syncthreads();
-  char* const ep = lds + w * EpilogueStage<TI / 2, TJ>::BYTES;
-  const bf16_t* R = (const bf16_t*)sload_ptr(ptrA + 2 * nk);
-#pragma unroll
-  for (int hf = 0; hf < 2; ++hf) {
-    f32x16 part[TI / 2][TJ];
-#pragma unroll
-    for (int i = 0; i < TI / 2; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) part[i][j] = acc[hf * (TI / 2) + i][j];
-    store_c_rows<TI / 2, TJ>(part, ep, Cp, M, N, m0 + wn * 32 * TJ, n0 + wm * 32 * TI + hf * 16 * TI, lane, R);
-  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1670,8 +1232,8 @@ int32_t blocks_for(int cls, const OpDesc& d, const int32_t* aux) {
     case LC_GEMM_F32:
     case LC_GEMM_BF16_SMALL: return cdiv(d.rows, kGemmSmallTile) * cdiv(d.cols, kGemmSmallTile);
     case LC_GEMM_ROWS: return cdiv(d.cols, kGemmSmallTile);
-    case LC_GEMM_BF16_NT: return cdiv(d.rows, GB_M) * cdiv(d.cols, GB_N);
-    case LC_GEMM_BF16_NT256: return cdiv(d.rows, 256) * cdiv(d.cols, d.p.mode == 2 ? 128 : 256);
+    case LC_GEMM_BF16_128: return gemm_blocks(128, d);
+    case LC_GEMM_BF16: return gemm_blocks(256, d);
     case LC_RMS_STAT: return cdiv(d.rows, 4);
     case LC_RMS_APPLY: return cdiv((int64_t)d.rows * cdiv(d.cols, 8), 256);
     case LC_ROPE:
@@ -1762,21 +1324,9 @@ hipError_t launch_batch(int cls, int dtype, int head_dim, const DeviceTables& t,
   switch (cls) {
     case LC_GEMM_F32:
     case LC_GEMM_BF16_SMALL: return launch_gemm_small(cls == LC_GEMM_BF16_SMALL, dtype, t, b, max_blocks, s);
-    case LC_GEMM_BF16_NT: hipLaunchKernelGGL(gemm_bf16_nt_kernel, grid, wg, 0, s, t, b); break;
-    case LC_GEMM_BF16_NT256: {
-      static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_bf16_nt256_kernel<TN_GEMM_WAVES, 4>,
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, g2_lds_bytes(256));
-      if (attr != hipSuccess) return attr;
-      hipLaunchKernelGGL((gemm_bf16_nt256_kernel<TN_GEMM_WAVES, 4>), grid, dim3(64 * TN_GEMM_WAVES), g2_lds_bytes(256), s, t, b);
-      break;
-    }
-    case LC_GEMM_BF16_NT256_SMALL: {
-      static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_bf16_nt256_kernel<4, 2>,
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, g2_lds_bytes(128));
-      if (attr != hipSuccess) return attr;
-      hipLaunchKernelGGL((gemm_bf16_nt256_kernel<4, 2>), grid, dim3(256), g2_lds_bytes(128), s, t, b);
-      break;
-    }
+    case LC_GEMM_BF16:
+    case LC_GEMM_BF16_128:
+    case LC_GEMM_BF16_PAIRED: return launch_gemm_bf16(cls, t, b, max_blocks, s);
     case LC_RMS_STAT: TN_LAUNCH_T(rms_stat_kernel); break;
     case LC_RMS_APPLY: TN_LAUNCH_T(rms_apply_kernel); break;
     case LC_ROPE: TN_LAUNCH_T(rope_kernel); break;
