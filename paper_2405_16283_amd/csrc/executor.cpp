@@ -27,6 +27,7 @@
 
 #include "graph.h"
 #include "kernels.h"
+#include "load_order.h"
 
 namespace tn {
 namespace {
@@ -199,6 +200,7 @@ struct tn_executor {
   // order the memgraph was compiled for (TN_POLICY_IN_ORDER dispatches along these)
   std::vector<int64_t> serial[3];
   std::vector<int64_t> order_key;  // position of every vertex in that order
+  std::vector<int64_t> load_key;   // the same for host-to-device transfers under TN_POLICY_BY_ORDER (see order_loads)
   std::vector<VInfo> groups;       // one representative per launch group (cls, dtype, head_dim)
   // per run
   std::vector<int64_t> remaining, last_order, arena_off;
@@ -723,6 +725,11 @@ tn_status tn_executor_create(const tn_memgraph* mg, void* device_base, uint64_t 
       by_pos[m] = m;
     }
     std::stable_sort(by_pos.begin(), by_pos.end(), [&](int64_t a, int64_t b) { return ex->order_key[a] < ex->order_key[b]; });
+    std::vector<double> seconds(nv, 0.0);  // at about the rates the kernels reach
+    for (int64_t m = 0; m < nv; ++m)
+      if (ex->info[m].cls >= 0) seconds[m] = ex->info[m].flops / (ex->info[m].dtype == TN_BF16 ? 1e15 : 5e13) + ex->info[m].bytes / 3e12;
+    ex->load_key = ex->order_key;
+    order_loads(*mg, seconds, ex->load_key);
     for (int64_t m : by_pos) {
       const int32_t k = mg->v[m].kind;
       if (k == TN_MG_OP) ex->serial[0].push_back(m);
@@ -919,11 +926,13 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
     q.key = ex->order_key.data();
   }
   ReadyQueue* const rq_x = rq.data() + n_groups;  // [0] host to device, [1] device to host
+  rq_x[0].key = ex->load_key.data();
   ReadyQueue rq_chain[2];  // transfers whose dependencies are complete or enqueued on the compute stream, but not all complete
   for (auto& q : rq_chain) {
     q.policy = in_order ? TN_POLICY_FIFO : opt.policy;
     q.key = ex->order_key.data();
   }
+  rq_chain[0].key = ex->load_key.data();
   std::vector<char> is_ready(in_order ? nv : 0, 0);
   std::vector<uint64_t> arrival(opt.policy <= TN_POLICY_LIFO ? nv : 0, 0);  // when a vertex became ready
   uint64_t n_arrived = 0;
