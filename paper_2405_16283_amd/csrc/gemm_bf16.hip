@@ -249,10 +249,9 @@ __device__ __forceinline__ void store_tiles(const f32x4 (&acc)[TQ][TP], char* st
       if (whole && c + 7 < Q) {
         *(uint4*)dst = x;
       } else {
-        const bf16_t* e = (const bf16_t*)&x;
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-          if (c + k < Q) dst[k] = e[k];
+        const bf16_t* e = (const bf16_t*)(st + r * PITCH + cin * 2);
+#pragma clang loop unroll(disable)
+        for (int k = 0; k < 8 && c + k < Q; ++k) dst[k] = e[k];
       }
     }
   }
@@ -480,12 +479,13 @@ __global__ void __launch_bounds__(256, NC == 2 ? 2 : 1) gemm_bf16_128_kernel(Dev
   auto next_get = [&]() __attribute__((always_inline)) { get = get + CB == NC * CB ? 0 : get + CB; };
 
   if (total > 0) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-      if (c < total) {
-        load_chunk();
-        next_chunk();
-      }
+    // (one copy of it: what a short product takes is the way of its instructions from memory as much as that of its operands.  128x128
+    // with K of 128, 256 and 1024 of them 7.5 -> 6.4 and 18.5 -> 14.9 us against the unrolled form and element stores)
+#pragma clang loop unroll(disable)
+    for (int c = 0; c < NC && c < total; ++c) {
+      load_chunk();
+      next_chunk();
+    }
     if (total >= NC) wait_loads<LOADS * (NC - 1)>();
     else wait_loads<0>();
     barrier();
