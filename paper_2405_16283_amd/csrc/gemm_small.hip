@@ -6,17 +6,19 @@
 // be mostly empty.  gemm_rows_kernel: single rows, those of many vertices at once.
 //
 // One workgroup = 32x32 elements of the output; its four wavefronts form the same 32x32 each over a quarter of
-// K (pieces of 128 bytes per row, dealt out in turn) and add up through LDS.  Operands go from memory straight
-// into the registers that feed the MFMAs: lane (n = lane & 15, g = lane >> 4) reads 16 bytes along K of row n, and
-// K is summed in a permuted but fixed order.  No LDS and no barrier on the way, three pieces in flight per wavefront.
+// K (pieces of 128 bytes per row, dealt out in turn) and add up through LDS.  K is summed in a permuted but fixed order.
+// Where both operands are stored along K, pieces come by `buffer_load ... lds` into a ring of the wavefront's own in LDS (no barrier),
+// three of them in flight, eight lanes to a row; fragments are read from there.  Other layouts, and tiles whose rows are not aligned,
+// go from memory straight into the registers that feed the MFMAs: lane (n = lane & 15, g = lane >> 4) reads 16 bytes
+// along K of row n.  That way a load instruction touches 16 rows out of order, and a wavefront spends more time on issuing its
+// eight loads per piece than on its 32 MFMAs.
 //
 // Why: these products are many and small (fp32 graphs: 64x64 to 256x256 with K of 64 to 2752; decode steps: one row;
-// adapters: 16 rows or columns), and a launch seldom holds more than a few, so what bounds them is the wait for
-// memory along a serial K loop and the number of workgroups, not the L1 traffic of a small tile.  (With many
-// workgroups L1 is the bound: 53-65 TFLOP/s in fp32, of 157, and 150 in bf16.)  Per launch, before -> after:
-// fp32, 64x64 tiles staged through LDS for vector FMAs: 64x64 with K of 256 and 688, 40 -> 7 us; 256x256 with K of 1024
-// and 2752, two or three to a launch, 172 -> 20 us.  bf16, 128x128 tiles: 32 products of 512x16, K 4096, 59 -> 28 us;
-// 8 of 16x512, K 16384, 223 -> 53 us; 32 single rows against 24 tiles of 512, K 4096, 486 -> 47 us.
+// adapters: 16 rows or columns), and a launch seldom holds more than a few, so what bounds them is one workgroup's walk along K,
+// the way to its first operands (about 4 us with launch and end) and the number of workgroups.  Per launch, straight into
+// registers -> by way of LDS: 256x256 in fp32 with K of 1024, one to four of them, 11.5 -> 9.7 us, twelve 28.9 -> 26.2 (61 TFLOP/s); with K of
+// 2560 22.6 -> 19.1 and 66.4 -> 54.8 (73, of 157); 64x64 with K of 256 5.7 -> 5.4, with 704 in tiles of 64 9.5 -> 9.8 (every piece
+// lies in another tile).  bf16: 32 products of 512x16, K 4096, 28 us; 8 of 16x512, K 16384, 53 us.
 #include "device.h"
 #include "kernels.h"
 
@@ -26,6 +28,11 @@ namespace {
 constexpr int kTile = kGemmSmallTile;  // 32: output rows and columns of a workgroup
 constexpr int kWaves = 4;
 constexpr int kPitch = kTile + 4;  // floats per row of a partial in LDS
+constexpr int kStages = 4;         // pieces of a wavefront in LDS
+constexpr int kPieceBytes = 2 * kTile * 128;
+constexpr int kRingBytes = kWaves * kStages * kPieceBytes;
+constexpr int kTableTiles = 64;    // gemm_rows: K tiles whose addresses are held in LDS
+static_assert(kWaves * kTile * kPitch * 4 <= kRingBytes, "the partials take the place of the ring");
 static_assert(kTile == 32, "two 16-row MFMA tiles per side");
 
 __device__ __forceinline__ f32x4 ldg4(const TN_GLOBAL float* p) { return *(const TN_GLOBAL f32x4*)p; }
@@ -38,6 +45,38 @@ __device__ __forceinline__ f32x4 ldg4(const TN_GLOBAL bf16_t* p) {
 __device__ __forceinline__ float ldg(const TN_GLOBAL float* p) { return *p; }
 __device__ __forceinline__ float ldg(const TN_GLOBAL bf16_t* p) { return bf2f(*p); }
 
+typedef __attribute__((ext_vector_type(4))) uint32_t rsrc_t;
+typedef __attribute__((address_space(3))) void* lptr_t;
+// 16 bytes per lane from global memory straight into LDS at lds_addr + 16 * lane, not tracked by the compiler.  (M0 has to be
+// written one instruction ahead.)
+__device__ __forceinline__ void load_lds(uint32_t voff, rsrc_t r, uint32_t soff, uint32_t lds_addr, int imm) {
+  asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(r), "s"(soff), "s"(lds_addr), "n"(imm) : "memory", "scc");
+}
+__device__ __forceinline__ void load_lds(uint64_t addr, uint32_t lds_addr, int imm) {
+  asm volatile("s_add_u32 m0, %1, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(addr), "s"(lds_addr), "n"(imm) : "memory", "scc");
+}
+
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+// The first 64 entries of a table, one per lane.  Read where it is needed, each would be a wait of its own in the walk along K: 64x64
+// products with 11 tiles of 64 along K spent more time on these than on their products.
+struct LaneTable {
+  uint32_t lo, hi;
+  __device__ __forceinline__ uint64_t address(void* const* t, int q) const {
+    if (q >= 64) return uniform((uint64_t)t[q]);
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, q) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)lo, q);
+  }
+  __device__ __forceinline__ int size(const int* t, int q) const {
+    return q >= 64 ? __builtin_amdgcn_readfirstlane(t[q]) : __builtin_amdgcn_readlane((int)lo, q);
+  }
+};
+__device__ __forceinline__ LaneTable read_addresses(void* const* t, int n) {
+  const uint64_t a = (uint64_t)t[min((int)(threadIdx.x & 63), n - 1)];
+  return {(uint32_t)a, (uint32_t)(a >> 32)};
+}
+__device__ __forceinline__ LaneTable read_sizes(const int* t, int n) { return {(uint32_t)t[min((int)(threadIdx.x & 63), n - 1)], 0}; }
+
 // The two kinds of products.  A piece is what a wavefront takes at once along K: two slabs, of which a lane
 // (n = lane & 15, g = lane >> 4) holds W neighbours, elements W g .. W g + W - 1, of row n.
 // lane (n, g) of the result holds rows 16 i + n and columns 16 j + 4 g .. + 3 of the image.
@@ -47,15 +86,10 @@ struct Fp32Products {  // element c of every lane goes to MFMA c of a slab
   typedef f32x4 Vec;
   static __device__ __forceinline__ Vec wide(const TN_GLOBAL T* p) { return ldg4(p); }
   static __device__ __forceinline__ Vec zero() { return (f32x4){0.f, 0.f, 0.f, 0.f}; }
-  static __device__ __forceinline__ void multiply(const Vec (&x)[2][2], const Vec (&y)[2][2], f32x4 (&acc)[2][2]) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f32(y[s][j][c], x[s][i][c], acc[i][j]);
+  static constexpr int M = 4;  // MFMAs in an eighth of a piece
+  static __device__ __forceinline__ void mfma(int q, int m, const Vec (&x)[2][2], const Vec (&y)[2][2], f32x4 (&acc)[2][2]) {
+    const int s = q >> 2, c = q & 3, i = m >> 1, j = m & 1;
+    acc[i][j] = mfma_f32(y[s][j][c], x[s][i][c], acc[i][j]);
   }
 };
 struct Bf16Products {
@@ -63,13 +97,10 @@ struct Bf16Products {
   typedef bf16x8 Vec;
   static __device__ __forceinline__ Vec wide(const TN_GLOBAL bf16_t* p) { return *(const TN_GLOBAL bf16x8*)p; }
   static __device__ __forceinline__ Vec zero() { return __builtin_bit_cast(bf16x8, (f32x4){0.f, 0.f, 0.f, 0.f}); }
-  static __device__ __forceinline__ void multiply(const Vec (&x)[2][2], const Vec (&y)[2][2], f32x4 (&acc)[2][2]) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[s][j], x[s][i], acc[i][j], 0, 0, 0);
+  static constexpr int M = 1;
+  static __device__ __forceinline__ void mfma(int q, int, const Vec (&x)[2][2], const Vec (&y)[2][2], f32x4 (&acc)[2][2]) {
+    const int s = q >> 2, i = (q >> 1) & 1, j = q & 1;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[s][j], x[s][i], acc[i][j], 0, 0, 0);
   }
 };
 
@@ -80,6 +111,8 @@ struct Sides {
   void* const* py;
   const int* ks;
   int nk, X, Y, x0, y0, w, n, g;
+  LaneTable sizes;
+  __device__ __forceinline__ int size(int q) const { return sizes.size(ks, q); }
 };
 
 // One side of the product in the K tile at hand.  KC: tiles are stored [rows, K], else [K, rows] (fp32 products only).
@@ -91,7 +124,9 @@ struct Side {
   const TN_GLOBAL T* p = nullptr;  // the workgroup's first row of the tile
   int rows, r0, K = 0, r[2], g;    // r: rows from there
   uint32_t off[2];  // bytes from a piece's first element along K in the first row to this lane's, for both 16-row tiles
-  __device__ __forceinline__ Side(void* const* tiles_, int rows_, int r0_, int n, int g_) : tiles(tiles_), rows(rows_), r0(r0_), g(g_) {
+  LaneTable at_lane;  // addresses of the tiles
+  __device__ __forceinline__ Side(void* const* tiles_, int nk, int rows_, int r0_, int n, int g_)
+      : tiles(tiles_), rows(rows_), r0(r0_), g(g_), at_lane(read_addresses(tiles_, nk)) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) r[i] = min(16 * i + n, rows - 1 - r0);  // rows past the end: any row, they are not stored
   }
@@ -103,7 +138,7 @@ struct Side {
   }
   __device__ __forceinline__ void open(int kt, int K_, int) {
     K = K_;
-    p = (const TN_GLOBAL T*)tiles[kt] + (KC ? (size_t)r0 * K : (size_t)r0);
+    p = (const TN_GLOBAL T*)at_lane.address(tiles, kt) + (KC ? (size_t)r0 * K : (size_t)r0);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
       off[i] = ((uint32_t)r[i] * (KC ? (uint32_t)K : 1u) + (uint32_t)(W * g) * (KC ? 1u : (uint32_t)rows)) * (uint32_t)sizeof(T);
@@ -125,6 +160,22 @@ struct Side {
         }
       }
   }
+  // The same by way of LDS (KC only): what `load_staged` issues for the piece `bytes` along K, eight rows to an instruction.
+  uint32_t lane_off[4] = {0, 0, 0, 0};
+  rsrc_t rsrc = {0, 0, 0, 0};
+  __device__ __forceinline__ void open_staged(int kt, int K_) {
+    const uint64_t a = uniform(at_lane.address(tiles, kt) + (uint64_t)r0 * (uint64_t)K_ * sizeof(T));
+    rsrc = (rsrc_t){(uint32_t)a, (uint32_t)(a >> 32) & 0xFFFFu, 0xFFFFFFF0u, 0x00020000u};
+    if (K_ == K) return;
+    K = K_;
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      lane_off[i] = (uint32_t)min(8 * i + (lane >> 3), rows - 1 - r0) * (uint32_t)K * (uint32_t)sizeof(T) + (((lane & 7) ^ (lane >> 3)) * 16);
+  }
+  __device__ __forceinline__ void load_staged(int i, uint32_t bytes, uint32_t lds_addr, int imm) const {
+    load_lds(lane_off[i], rsrc, bytes, lds_addr, imm + i * 1024);
+  }
   // the last piece of a K tile, and rows that are not aligned to a whole vector or too long for `off`
   __device__ __forceinline__ void load_ragged(int k0, Vec (&f)[2][2]) const {
 #pragma unroll
@@ -144,61 +195,128 @@ struct Side {
   }
 };
 
-template <typename P, typename SX, typename SY>
-__device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors, f32x4 (&acc)[2][2]) {
+template <typename P, bool STAGED, typename SX, typename SY>
+__device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors, f32x4 (&acc)[2][2], char* lds) {
   constexpr int DEEP = 8 * P::W;  // elements along K of a piece
   // whole pieces of a K tile; none where rows stored along K are not aligned to a vector or the tile is too wide
   auto pieces = [&](int K) { return (vectors && K % P::W) || !x.reaches(K) || !y.reaches(K) ? 0 : K / DEEP; };
   int total = 0;
-  for (int q = 0; q < s.nk; ++q) total += pieces(s.ks[q]);
-  const int mine = (total - s.w + kWaves - 1) / kWaves;  // this wavefront's pieces: w, w + 4, ...
+  for (int q = 0; q < s.nk; ++q) total += pieces(s.size(q));
+  const int mine = __builtin_amdgcn_readfirstlane((total - s.w + kWaves - 1) / kWaves);  // this wavefront's pieces: w, w + 4, ...
   int kt = -1, left = 0, at = s.w;  // `at`: the next one, counted from the first of the `left` pieces of K tile kt
-  typename P::Vec fx[3][2][2], fy[3][2][2];
-  auto fetch = [&](int b) {
-    if (at >= left) {
-      int K = 0;
-      do {
-        at -= left;
-        K = s.ks[++kt];
-        left = pieces(K);
-      } while (at >= left);
-      x.open(kt, K, s.nk);
-      y.open(kt, K, s.nk);
-    }
-    x.load(at * DEEP, fx[b]);
-    y.load(at * DEEP, fy[b]);
-    at += kWaves;
+  // goes on to the K tile that holds piece `at`; true if that is another one
+  auto seek = [&](int& K) {
+    if (__builtin_amdgcn_readfirstlane(at < left)) return false;
+    do {
+      at -= left;
+      K = s.size(++kt);
+      left = pieces(K);
+    } while (__builtin_amdgcn_readfirstlane(at >= left));
+    return true;
   };
-  auto multiply = [&](int b) { P::multiply(fx[b], fy[b], acc); };
-  if (mine >= 3) {  // three pieces in flight
-    fetch(0);
-    fetch(1);
-    fetch(2);
-    int left_over = mine;
-    for (; left_over >= 6; left_over -= 3) {
+  typename P::Vec fx[STAGED ? 1 : 3][2][2], fy[STAGED ? 1 : 3][2][2];
+  auto multiply = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        multiply(b);
-        fetch(b);
-        __builtin_amdgcn_sched_barrier(0);
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int m = 0; m < P::M; ++m) P::mfma(q, m, fx[b], fy[b], acc);
+  };
+  if constexpr (STAGED) {
+    const uint32_t ring = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t)lds + s.w * kStages * kPieceBytes);
+    const char* const mem = lds + s.w * kStages * kPieceBytes;
+    uint32_t put = 0, get = 0;  // stages, in bytes
+    int issued = 0;
+    uint32_t bytes = 0;  // the next piece's place along K
+    auto load = [&](int q) __attribute__((always_inline)) {
+      if (q < 4) x.load_staged(q, bytes, ring + put, 0);
+      else y.load_staged(q - 4, bytes, ring + put, kPieceBytes / 2);
+    };
+    auto find = [&]() {
+      int K = 0;
+      if (seek(K)) {
+        x.open_staged(kt, K);
+        y.open_staged(kt, K);
       }
+      bytes = __builtin_amdgcn_readfirstlane(at * 128);
+    };
+    auto next = [&]() {
+      put = put + kPieceBytes == kStages * kPieceBytes ? 0 : put + kPieceBytes;
+      at += kWaves;
+      ++issued;
+    };
+    auto load_next = [&]() __attribute__((always_inline)) {
+      find();
+#pragma unroll
+      for (int q = 0; q < 8; ++q) load(q);
+      next();
+    };
+#pragma clang loop unroll(disable)
+    for (int q = 0; q < kStages - 1 && q < mine; ++q) load_next();
+    // One piece: its fragments are read, and behind them the loads of the piece three on are issued, into the stage of the one
+    // before.  (Taking these in turn with the MFMAs of the piece before, with two sets of registers, needs several
+    // copies of the loop: 0.3 us faster per 32 KiB of operands, but 0.5 us for the first of them, instructions come cold.)
+#pragma clang loop unroll(disable)
+    for (int done = 0; done < mine; ++done) {
+      const int behind = issued - done - 1;  // pieces behind this one that may be on their way
+      if (behind >= 2) __builtin_amdgcn_s_waitcnt(0x0070 | (1 << 14));  // vmcnt(16)
+      else if (behind == 1) __builtin_amdgcn_s_waitcnt(0x0070 | 8);
+      else __builtin_amdgcn_s_waitcnt(0x0070);
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {  // rows 16 i + n, 16-byte piece 4 j + g
+        const int i = (q >> 1) & 1, j = q >> 2;
+        const char* const p = mem + get + (q & 1) * (kPieceBytes / 2) + (16 * i + s.n) * 128 + (((4 * j + s.g) ^ (s.n & 7)) * 16);
+        if (q & 1) fy[0][j][i] = *(const typename P::Vec*)p;
+        else fx[0][j][i] = *(const typename P::Vec*)p;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (issued < mine) load_next();
+      __builtin_amdgcn_sched_barrier(0);
+      get = get + kPieceBytes == kStages * kPieceBytes ? 0 : get + kPieceBytes;
+      multiply(0);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    multiply(0);
-    if (left_over > 3) fetch(0);
-    multiply(1);
-    if (left_over > 4) fetch(1);
-    multiply(2);
-    if (left_over > 3) multiply(0);
-    if (left_over > 4) multiply(1);
-  } else if (mine > 0) {
-    fetch(0);
-    if (mine > 1) fetch(1);
-    multiply(0);
-    if (mine > 1) multiply(1);
+  } else {
+    auto fetch = [&](int b) {
+      int K = 0;
+      if (seek(K)) {
+        x.open(kt, K, s.nk);
+        y.open(kt, K, s.nk);
+      }
+      x.load(at * DEEP, fx[b]);
+      y.load(at * DEEP, fy[b]);
+      at += kWaves;
+    };
+    if (mine >= 3) {  // three pieces in flight
+      fetch(0);
+      fetch(1);
+      fetch(2);
+      int left_over = mine;
+      for (; left_over >= 6; left_over -= 3) {
+  #pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          multiply(b);
+          fetch(b);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      multiply(0);
+      if (left_over > 3) fetch(0);
+      multiply(1);
+      if (left_over > 4) fetch(1);
+      multiply(2);
+      if (left_over > 3) multiply(0);
+      if (left_over > 4) multiply(1);
+    } else if (mine > 0) {
+      fetch(0);
+      if (mine > 1) fetch(1);
+      multiply(0);
+      if (mine > 1) multiply(1);
+    }
   }
   // what the whole pieces leave of each K tile
   for (int q = 0, turn = 0; q < s.nk; ++q) {
-    const int K = s.ks[q];
+    const int K = s.size(q);
     for (int k0 = pieces(K) * DEEP; k0 < K; k0 += DEEP, ++turn) {
       if (turn % kWaves != s.w) continue;
       x.open(q, K, s.nk);
@@ -211,7 +329,9 @@ __device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors
 }
 
 // The four partials of the workgroup added up: thread t receives columns 4 (t % 8) .. + 3 of row t / 8.
-__device__ __forceinline__ f32x4 add_up(const f32x4 (&acc)[2][2], float (*part)[kTile][kPitch], int w, int n, int g) {
+__device__ __forceinline__ f32x4 add_up(const f32x4 (&acc)[2][2], char* lds, int w, int n, int g) {
+  float (*const part)[kTile][kPitch] = (float (*)[kTile][kPitch])lds;
+  __syncthreads();  // the rings are read to the end
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -226,21 +346,24 @@ __device__ __forceinline__ f32x4 add_up(const f32x4 (&acc)[2][2], float (*part)[
 
 // B16: bf16 products (both sides stored along K, every K a multiple of 8), else fp32 products
 template <typename T, bool B16>
-__global__ void __launch_bounds__(64 * kWaves, sizeof(T) == 4 || B16 ? 3 : 2) gemm_small_kernel(DeviceTables t, Batch b) {
-  __shared__ __attribute__((aligned(16))) float part[kWaves][kTile][kPitch];
+__global__ void __launch_bounds__(64 * kWaves) gemm_small_kernel(DeviceTables t, Batch b) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
   int bx, by;
   xcd_remap(bx, by);
   const OpDesc& d = t.descs[b.at(by)];
   if (bx >= d.nblocks) return;
-  const int nk = d.p.nk, lane = threadIdx.x & 63;
-  const bool tc = d.p.trans_c != 0;
-  void* const* const A = t.ptrs + d.ptr0;
+  const int nk = __builtin_amdgcn_readfirstlane(d.p.nk), lane = threadIdx.x & 63;
+  // (told to be uniform: the compiler does not see it, and staged loads take their descriptors from scalar registers)
+  const int rows = __builtin_amdgcn_readfirstlane(d.rows), cols = __builtin_amdgcn_readfirstlane(d.cols), mode = __builtin_amdgcn_readfirstlane(d.p.mode);
+  const bool tc = __builtin_amdgcn_readfirstlane(d.p.trans_c) != 0;
+  void* const* const A = t.ptrs + __builtin_amdgcn_readfirstlane(d.ptr0);
   Sides s;
-  s.ks = t.aux + d.aux0;
+  s.ks = t.aux + __builtin_amdgcn_readfirstlane(d.aux0);
   s.nk = nk;
-  s.X = tc ? d.cols : d.rows;
-  s.Y = tc ? d.rows : d.cols;
-  const bool a_k = d.p.trans_a == 0, b_k = d.trans_b != 0;
+  s.sizes = read_sizes(s.ks, nk);
+  s.X = tc ? cols : rows;
+  s.Y = tc ? rows : cols;
+  const bool a_k = __builtin_amdgcn_readfirstlane(d.p.trans_a) == 0, b_k = __builtin_amdgcn_readfirstlane(d.trans_b) != 0;
   const bool xk = tc ? b_k : a_k, yk = tc ? a_k : b_k;
   const int across = (s.Y + kTile - 1) / kTile;
   s.x0 = bx / across * kTile;
@@ -249,7 +372,7 @@ __global__ void __launch_bounds__(64 * kWaves, sizeof(T) == 4 || B16 ? 3 : 2) ge
   s.n = lane & 15;
   s.g = lane >> 4;
   f32x4 v = {0.f, 0.f, 0.f, 0.f}, gate = v;
-  const int passes = d.p.mode == 2 ? 2 : 1;  // mode 2: the gate product, then the up product
+  const int passes = mode == 2 ? 2 : 1;  // mode 2: the gate product, then the up product
   for (int pass = 0; pass < passes; ++pass) {
     void* const* const Bt = A + (1 + pass) * nk;
     s.px = tc ? Bt : A;
@@ -261,18 +384,18 @@ __global__ void __launch_bounds__(64 * kWaves, sizeof(T) == 4 || B16 ? 3 : 2) ge
       for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     if constexpr (B16) {
       typedef Side<T, Bf16Products, true> K;
-      product<Bf16Products>(s, K(s.px, s.X, s.x0, s.n, s.g), K(s.py, s.Y, s.y0, s.n, s.g), true, acc);
+      product<Bf16Products, true>(s, K(s.px, nk, s.X, s.x0, s.n, s.g), K(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
     } else {
       typedef Fp32Products<T> P;
       typedef Side<T, P, true> K;
       typedef Side<T, P, false> R;
-      if (xk && yk) product<P>(s, K(s.px, s.X, s.x0, s.n, s.g), K(s.py, s.Y, s.y0, s.n, s.g), true, acc);
-      else if (xk) product<P>(s, K(s.px, s.X, s.x0, s.n, s.g), R(s.py, s.Y, s.y0, s.n, s.g), true, acc);
-      else if (yk) product<P>(s, R(s.px, s.X, s.x0, s.n, s.g), K(s.py, s.Y, s.y0, s.n, s.g), true, acc);
-      else product<P>(s, R(s.px, s.X, s.x0, s.n, s.g), R(s.py, s.Y, s.y0, s.n, s.g), false, acc);
+      if (xk && yk) product<P, sizeof(T) == 4>(s, K(s.px, nk, s.X, s.x0, s.n, s.g), K(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
+      else if (xk) product<P, false>(s, K(s.px, nk, s.X, s.x0, s.n, s.g), R(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
+      else if (yk) product<P, false>(s, R(s.px, nk, s.X, s.x0, s.n, s.g), K(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
+      else product<P, false>(s, R(s.px, nk, s.X, s.x0, s.n, s.g), R(s.py, nk, s.Y, s.y0, s.n, s.g), false, acc, lds);
     }
     gate = v;
-    v = add_up(acc, part, s.w, s.n, s.g);
+    v = add_up(acc, lds, s.w, s.n, s.g);
   }
   const int row = s.x0 + (threadIdx.x >> 3), col = s.y0 + (threadIdx.x & 7) * 4;
   if (row >= s.X || col >= s.Y) return;
@@ -313,6 +436,16 @@ struct RowsSide {  // row r of the image: the A tiles of vertex r of the group
     }
   }
   __device__ __forceinline__ bool reaches(int) const { return true; }
+  const uint64_t* table = nullptr;  // addresses of the image's rows in the first K tiles, in LDS
+  uint64_t lane_at[4];              // this lane's place in piece 0 of the K tile at hand, for each of four loads
+  __device__ __forceinline__ void open_staged(int kt_, int) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) lane_at[i] = table[kt_ * kTile + 8 * i + (lane >> 3)] + (((lane & 7) ^ (lane >> 3)) * 16);
+  }
+  __device__ __forceinline__ void load_staged(int i, uint32_t bytes, uint32_t lds_addr, int imm) const {
+    load_lds(lane_at[i] + bytes, lds_addr, imm + i * 1024);
+  }
   __device__ __forceinline__ void open(int kt_, int K_, int nk) {
     if (kt_ == kt + 1) {
       p[0] = next[0];
@@ -345,36 +478,48 @@ struct RowsSide {  // row r of the image: the A tiles of vertex r of the group
 };
 
 template <typename T, typename P>
-__global__ void __launch_bounds__(64 * kWaves, 3) gemm_rows_kernel(DeviceTables t, Batch b) {
-  __shared__ __attribute__((aligned(16))) float part[kWaves][kTile][kPitch];
+__global__ void __launch_bounds__(64 * kWaves) gemm_rows_kernel(DeviceTables t, Batch b) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
   int bx, by;
   xcd_remap(bx, by);
   const int first = b.idx[by], count = b.idx[by + 1] - first;
   const OpDesc& d = t.descs[b.base + b.idx[b.n + 1 + first]];  // what the group has in common
   if (bx >= d.nblocks) return;
-  const int nk = d.p.nk, lane = threadIdx.x & 63;
+  const int nk = __builtin_amdgcn_readfirstlane(d.p.nk), lane = threadIdx.x & 63;
   Sides s;
-  s.ks = t.aux + d.aux0;
+  s.ks = t.aux + __builtin_amdgcn_readfirstlane(d.aux0);
   s.nk = nk;
+  s.sizes = read_sizes(s.ks, nk);
   s.X = count;
-  s.Y = d.cols;
+  s.Y = __builtin_amdgcn_readfirstlane(d.cols);
   s.x0 = 0;
   s.y0 = bx * kTile;
   s.w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   s.n = lane & 15;
   s.g = lane >> 4;
+  RowsSide<T, P> x(t, b, first, count, s.n, s.g);
+  uint64_t* const table = (uint64_t*)(lds + kRingBytes);
+  if (nk <= kTableTiles) {
+    for (int q = threadIdx.x; q < kTile * nk; q += 64 * kWaves) {
+      const OpDesc& o = t.descs[b.base + b.idx[b.n + 1 + first + min(q % kTile, count - 1)]];
+      table[q] = (uint64_t)t.ptrs[o.ptr0 + q / kTile];
+    }
+    x.table = table;
+    __syncthreads();
+  }
   f32x4 v = {0.f, 0.f, 0.f, 0.f}, gate = v;
-  const int passes = d.p.mode == 2 ? 2 : 1;
+  const int passes = __builtin_amdgcn_readfirstlane(d.p.mode) == 2 ? 2 : 1;
   for (int pass = 0; pass < passes; ++pass) {
     f32x4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    product<P>(s, RowsSide<T, P>(t, b, first, count, s.n, s.g),
-               Side<T, P, true>(t.ptrs + d.ptr0 + (1 + pass) * nk, s.Y, s.y0, s.n, s.g), true, acc);
+    const Side<T, P, true> y(t.ptrs + __builtin_amdgcn_readfirstlane(d.ptr0) + (1 + pass) * nk, nk, s.Y, s.y0, s.n, s.g);
+    if (nk <= kTableTiles) product<P, true>(s, x, y, true, acc, lds);
+    else product<P, false>(s, x, y, true, acc, lds);
     gate = v;
-    v = add_up(acc, part, s.w, s.n, s.g);
+    v = add_up(acc, lds, s.w, s.n, s.g);
   }
   const int row = threadIdx.x >> 3, col = s.y0 + (threadIdx.x & 7) * 4;
   if (row >= count || col >= s.Y) return;
@@ -397,11 +542,18 @@ __global__ void __launch_bounds__(64 * kWaves, 3) gemm_rows_kernel(DeviceTables 
 
 }  // namespace
 
+#define TN_LAUNCH_SMALL(KERNEL, LDS)                                                                                              \
+  do {                                                                                                                            \
+    static const hipError_t attr = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, (LDS));   \
+    if (attr != hipSuccess) return attr;                                                                                          \
+    hipLaunchKernelGGL(KERNEL, grid, wg, (LDS), s, t, b);                                                                         \
+  } while (0)
+
 hipError_t launch_gemm_small(bool bf16_products, int dtype, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t s) {
   const dim3 grid((unsigned)max_blocks, (unsigned)b.n), wg(64 * kWaves);
-  if (bf16_products) hipLaunchKernelGGL((gemm_small_kernel<bf16_t, true>), grid, wg, 0, s, t, b);
-  else if (dtype == TN_BF16) hipLaunchKernelGGL((gemm_small_kernel<bf16_t, false>), grid, wg, 0, s, t, b);
-  else hipLaunchKernelGGL((gemm_small_kernel<float, false>), grid, wg, 0, s, t, b);
+  if (bf16_products) TN_LAUNCH_SMALL((gemm_small_kernel<bf16_t, true>), kRingBytes);
+  else if (dtype == TN_BF16) TN_LAUNCH_SMALL((gemm_small_kernel<bf16_t, false>), kWaves * kTile * kPitch * 4);
+  else TN_LAUNCH_SMALL((gemm_small_kernel<float, false>), kRingBytes);
   return hipGetLastError();
 }
 
@@ -426,13 +578,16 @@ hipError_t launch_gemm_rows(int dtype, const DeviceTables& t, uint32_t base, con
     for (int k = 0; k <= groups; ++k) b.idx[k] = start[k];
     for (int k = 0; k < taken; ++k) b.idx[groups + 1 + k] = (uint16_t)(rows[at + k].desc - base);
     const dim3 grid((unsigned)max_blocks, (unsigned)groups), wg(64 * kWaves);
-    if (dtype == TN_BF16) hipLaunchKernelGGL((gemm_rows_kernel<bf16_t, Bf16Products>), grid, wg, 0, s, t, b);
-    else hipLaunchKernelGGL((gemm_rows_kernel<float, Fp32Products<float>>), grid, wg, 0, s, t, b);
+    constexpr int kRowsLds = kRingBytes + kTableTiles * kTile * 8;
+    if (dtype == TN_BF16) TN_LAUNCH_SMALL((gemm_rows_kernel<bf16_t, Bf16Products>), kRowsLds);
+    else TN_LAUNCH_SMALL((gemm_rows_kernel<float, Fp32Products<float>>), kRowsLds);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     at += taken;
   }
   return hipSuccess;
 }
+
+#undef TN_LAUNCH_SMALL
 
 }  // namespace tn
