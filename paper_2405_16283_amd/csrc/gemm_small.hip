@@ -27,12 +27,14 @@ namespace {
 
 constexpr int kTile = kGemmSmallTile;  // 32: output rows and columns of a workgroup
 constexpr int kWaves = 4;
-constexpr int kPitch = kTile + 4;  // floats per row of a partial in LDS
-constexpr int kStages = 4;         // pieces of a wavefront in LDS
-constexpr int kPieceBytes = 2 * kTile * 128;
-constexpr int kRingBytes = kWaves * kStages * kPieceBytes;
+constexpr int kStages = 4;  // pieces of a wavefront in LDS
+// F: fragments of 16 rows or columns per side of a workgroup's tile; floats per row of a partial in LDS, bytes of a piece and of a ring
+constexpr int pitch(int f) { return 16 * f + 4; }
+constexpr int piece_bytes(int f) { return 2 * 16 * f * 128; }
+constexpr int ring_bytes(int f) { return kWaves * kStages * piece_bytes(f); }
+constexpr int partials_bytes(int f) { return kWaves * 16 * f * pitch(f) * 4; }
 constexpr int kTableTiles = 64;    // gemm_rows: K tiles whose addresses are held in LDS
-static_assert(kWaves * kTile * kPitch * 4 <= kRingBytes, "the partials take the place of the ring");
+static_assert(partials_bytes(2) <= ring_bytes(2) && partials_bytes(1) <= ring_bytes(1), "the partials take the place of the ring");
 static_assert(kTile == 32, "two 16-row MFMA tiles per side");
 
 __device__ __forceinline__ f32x4 ldg4(const TN_GLOBAL float* p) { return *(const TN_GLOBAL f32x4*)p; }
@@ -86,10 +88,16 @@ struct Fp32Products {  // element c of every lane goes to MFMA c of a slab
   typedef f32x4 Vec;
   static __device__ __forceinline__ Vec wide(const TN_GLOBAL T* p) { return ldg4(p); }
   static __device__ __forceinline__ Vec zero() { return (f32x4){0.f, 0.f, 0.f, 0.f}; }
-  static constexpr int M = 4;  // MFMAs in an eighth of a piece
-  static __device__ __forceinline__ void mfma(int q, int m, const Vec (&x)[2][2], const Vec (&y)[2][2], f32x4 (&acc)[2][2]) {
-    const int s = q >> 2, c = q & 3, i = m >> 1, j = m & 1;
-    acc[i][j] = mfma_f32(y[s][j][c], x[s][i][c], acc[i][j]);
+  template <int F>
+  static __device__ __forceinline__ void multiply(const Vec (&x)[2][F], const Vec (&y)[2][F], f32x4 (&acc)[F][F]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+          for (int j = 0; j < F; ++j) acc[i][j] = mfma_f32(y[s][j][c], x[s][i][c], acc[i][j]);
   }
 };
 struct Bf16Products {
@@ -97,10 +105,14 @@ struct Bf16Products {
   typedef bf16x8 Vec;
   static __device__ __forceinline__ Vec wide(const TN_GLOBAL bf16_t* p) { return *(const TN_GLOBAL bf16x8*)p; }
   static __device__ __forceinline__ Vec zero() { return __builtin_bit_cast(bf16x8, (f32x4){0.f, 0.f, 0.f, 0.f}); }
-  static constexpr int M = 1;
-  static __device__ __forceinline__ void mfma(int q, int, const Vec (&x)[2][2], const Vec (&y)[2][2], f32x4 (&acc)[2][2]) {
-    const int s = q >> 2, i = (q >> 1) & 1, j = q & 1;
-    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[s][j], x[s][i], acc[i][j], 0, 0, 0);
+  template <int F>
+  static __device__ __forceinline__ void multiply(const Vec (&x)[2][F], const Vec (&y)[2][F], f32x4 (&acc)[F][F]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < F; ++i)
+#pragma unroll
+        for (int j = 0; j < F; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[s][j], x[s][i], acc[i][j], 0, 0, 0);
   }
 };
 
@@ -116,19 +128,19 @@ struct Sides {
 };
 
 // One side of the product in the K tile at hand.  KC: tiles are stored [rows, K], else [K, rows] (fp32 products only).
-template <typename T, typename P, bool KC>
+template <typename T, typename P, bool KC, int F>
 struct Side {
   static constexpr int W = P::W;
   typedef typename P::Vec Vec;
   void* const* tiles;
   const TN_GLOBAL T* p = nullptr;  // the workgroup's first row of the tile
-  int rows, r0, K = 0, r[2], g;    // r: rows from there
-  uint32_t off[2];  // bytes from a piece's first element along K in the first row to this lane's, for both 16-row tiles
+  int rows, r0, K = 0, r[F], g;    // r: rows from there
+  uint32_t off[F];  // bytes from a piece's first element along K in the first row to this lane's, for the 16-row tiles
   LaneTable at_lane;  // addresses of the tiles
   __device__ __forceinline__ Side(void* const* tiles_, int nk, int rows_, int r0_, int n, int g_)
       : tiles(tiles_), rows(rows_), r0(r0_), g(g_), at_lane(read_addresses(tiles_, nk)) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) r[i] = min(16 * i + n, rows - 1 - r0);  // rows past the end: any row, they are not stored
+    for (int i = 0; i < F; ++i) r[i] = min(16 * i + n, rows - 1 - r0);  // rows past the end: any row, they are not stored
   }
   // Whether `off` holds the way from the workgroup's first row to its last (a tile of any size is fine as long as 32 of its
   // rows, or what a lane skips along K of [K, rows], stay below 4 GiB).
@@ -140,16 +152,16 @@ struct Side {
     K = K_;
     p = (const TN_GLOBAL T*)at_lane.address(tiles, kt) + (KC ? (size_t)r0 * K : (size_t)r0);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < F; ++i)
       off[i] = ((uint32_t)r[i] * (KC ? (uint32_t)K : 1u) + (uint32_t)(W * g) * (KC ? 1u : (uint32_t)rows)) * (uint32_t)sizeof(T);
   }
   __device__ __forceinline__ const TN_GLOBAL T* at(const TN_GLOBAL T* base, int i) const {
     return (const TN_GLOBAL T*)((const TN_GLOBAL char*)base + off[i]);
   }
   // a piece all of whose elements exist along K
-  __device__ __forceinline__ void load(int k0, Vec (&f)[2][2]) const {
+  __device__ __forceinline__ void load(int k0, Vec (&f)[2][F]) const {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < F; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         if constexpr (KC) {
@@ -161,7 +173,7 @@ struct Side {
       }
   }
   // The same by way of LDS (KC only): what `load_staged` issues for the piece `bytes` along K, eight rows to an instruction.
-  uint32_t lane_off[4] = {0, 0, 0, 0};
+  uint32_t lane_off[2 * F] = {};
   rsrc_t rsrc = {0, 0, 0, 0};
   __device__ __forceinline__ void open_staged(int kt, int K_) {
     const uint64_t a = uniform(at_lane.address(tiles, kt) + (uint64_t)r0 * (uint64_t)K_ * sizeof(T));
@@ -170,16 +182,16 @@ struct Side {
     K = K_;
     const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 2 * F; ++i)
       lane_off[i] = (uint32_t)min(8 * i + (lane >> 3), rows - 1 - r0) * (uint32_t)K * (uint32_t)sizeof(T) + (((lane & 7) ^ (lane >> 3)) * 16);
   }
   __device__ __forceinline__ void load_staged(int i, uint32_t bytes, uint32_t lds_addr, int imm) const {
     load_lds(lane_off[i], rsrc, bytes, lds_addr, imm + i * 1024);
   }
   // the last piece of a K tile, and rows that are not aligned to a whole vector or too long for `off`
-  __device__ __forceinline__ void load_ragged(int k0, Vec (&f)[2][2]) const {
+  __device__ __forceinline__ void load_ragged(int k0, Vec (&f)[2][F]) const {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < F; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int k = k0 + 4 * W * j + W * g;
@@ -195,8 +207,9 @@ struct Side {
   }
 };
 
-template <typename P, bool STAGED, typename SX, typename SY>
-__device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors, f32x4 (&acc)[2][2], char* lds) {
+template <typename P, bool STAGED, int F, typename SX, typename SY>
+__device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors, f32x4 (&acc)[F][F], char* lds) {
+  constexpr int kPieceBytes = piece_bytes(F), LOADS = 4 * F;  // (of a stage of the ring; load instructions)
   constexpr int DEEP = 8 * P::W;  // elements along K of a piece
   // whole pieces of a K tile; none where rows stored along K are not aligned to a vector or the tile is too wide
   auto pieces = [&](int K) { return (vectors && K % P::W) || !x.reaches(K) || !y.reaches(K) ? 0 : K / DEEP; };
@@ -214,13 +227,8 @@ __device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors
     } while (__builtin_amdgcn_readfirstlane(at >= left));
     return true;
   };
-  typename P::Vec fx[STAGED ? 1 : 3][2][2], fy[STAGED ? 1 : 3][2][2];
-  auto multiply = [&](int b) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-#pragma unroll
-      for (int m = 0; m < P::M; ++m) P::mfma(q, m, fx[b], fy[b], acc);
-  };
+  typename P::Vec fx[STAGED ? 1 : 3][2][F], fy[STAGED ? 1 : 3][2][F];
+  auto multiply = [&](int b) __attribute__((always_inline)) { P::template multiply<F>(fx[b], fy[b], acc); };
   if constexpr (STAGED) {
     const uint32_t ring = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t)lds + s.w * kStages * kPieceBytes);
     const char* const mem = lds + s.w * kStages * kPieceBytes;
@@ -228,8 +236,8 @@ __device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors
     int issued = 0;
     uint32_t bytes = 0;  // the next piece's place along K
     auto load = [&](int q) __attribute__((always_inline)) {
-      if (q < 4) x.load_staged(q, bytes, ring + put, 0);
-      else y.load_staged(q - 4, bytes, ring + put, kPieceBytes / 2);
+      if (q < 2 * F) x.load_staged(q, bytes, ring + put, 0);
+      else y.load_staged(q - 2 * F, bytes, ring + put, kPieceBytes / 2);
     };
     auto find = [&]() {
       int K = 0;
@@ -247,7 +255,7 @@ __device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors
     auto load_next = [&]() __attribute__((always_inline)) {
       find();
 #pragma unroll
-      for (int q = 0; q < 8; ++q) load(q);
+      for (int q = 0; q < LOADS; ++q) load(q);
       next();
     };
 #pragma clang loop unroll(disable)
@@ -258,13 +266,13 @@ __device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors
 #pragma clang loop unroll(disable)
     for (int done = 0; done < mine; ++done) {
       const int behind = issued - done - 1;  // pieces behind this one that may be on their way
-      if (behind >= 2) __builtin_amdgcn_s_waitcnt(0x0070 | (1 << 14));  // vmcnt(16)
-      else if (behind == 1) __builtin_amdgcn_s_waitcnt(0x0070 | 8);
+      if (behind >= 2) __builtin_amdgcn_s_waitcnt(0x0070 | ((2 * LOADS) & 15) | (((2 * LOADS) >> 4) << 14));  // vmcnt(2 LOADS)
+      else if (behind == 1) __builtin_amdgcn_s_waitcnt(0x0070 | LOADS);
       else __builtin_amdgcn_s_waitcnt(0x0070);
       asm volatile("" ::: "memory");
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {  // rows 16 i + n, 16-byte piece 4 j + g
-        const int i = (q >> 1) & 1, j = q >> 2;
+      for (int q = 0; q < 4 * F; ++q) {  // rows 16 i + n, 16-byte piece 4 j + g
+        const int i = (q >> 1) % F, j = q / (2 * F);
         const char* const p = mem + get + (q & 1) * (kPieceBytes / 2) + (16 * i + s.n) * 128 + (((4 * j + s.g) ^ (s.n & 7)) * 16);
         if (q & 1) fy[0][j][i] = *(const typename P::Vec*)p;
         else fx[0][j][i] = *(const typename P::Vec*)p;
@@ -328,16 +336,17 @@ __device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors
   }
 }
 
-// The four partials of the workgroup added up: thread t receives columns 4 (t % 8) .. + 3 of row t / 8.
-__device__ __forceinline__ f32x4 add_up(const f32x4 (&acc)[2][2], char* lds, int w, int n, int g) {
-  float (*const part)[kTile][kPitch] = (float (*)[kTile][kPitch])lds;
+// The four partials of the workgroup added up: thread t < 64 F F receives columns 4 (t % 4F) .. + 3 of row t / 4F.
+template <int F>
+__device__ __forceinline__ f32x4 add_up(const f32x4 (&acc)[F][F], char* lds, int w, int n, int g) {
+  float (*const part)[16 * F][pitch(F)] = (float (*)[16 * F][pitch(F)])lds;
   __syncthreads();  // the rings are read to the end
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < F; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) *(f32x4*)&part[w][16 * i + n][16 * j + 4 * g] = acc[i][j];
+    for (int j = 0; j < F; ++j) *(f32x4*)&part[w][16 * i + n][16 * j + 4 * g] = acc[i][j];
   __syncthreads();
-  const int r = threadIdx.x >> 3, c = (threadIdx.x & 7) * 4;
+  const int t = threadIdx.x & (64 * F * F - 1), r = t / (4 * F), c = t % (4 * F) * 4;
   const f32x4 v = (*(const f32x4*)&part[0][r][c] + *(const f32x4*)&part[1][r][c]) +
                   (*(const f32x4*)&part[2][r][c] + *(const f32x4*)&part[3][r][c]);
   __syncthreads();
@@ -345,13 +354,12 @@ __device__ __forceinline__ f32x4 add_up(const f32x4 (&acc)[2][2], char* lds, int
 }
 
 // B16: bf16 products (both sides stored along K, every K a multiple of 8), else fp32 products
-template <typename T, bool B16>
+template <typename T, bool B16, int F>
 __global__ void __launch_bounds__(64 * kWaves) gemm_small_kernel(DeviceTables t, Batch b) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int bx, by;
   xcd_remap(bx, by);
   const OpDesc& d = t.descs[b.at(by)];
-  if (bx >= d.nblocks) return;
   const int nk = __builtin_amdgcn_readfirstlane(d.p.nk), lane = threadIdx.x & 63;
   // (told to be uniform: the compiler does not see it, and staged loads take their descriptors from scalar registers)
   const int rows = __builtin_amdgcn_readfirstlane(d.rows), cols = __builtin_amdgcn_readfirstlane(d.cols), mode = __builtin_amdgcn_readfirstlane(d.p.mode);
@@ -365,9 +373,11 @@ __global__ void __launch_bounds__(64 * kWaves) gemm_small_kernel(DeviceTables t,
   s.Y = tc ? rows : cols;
   const bool a_k = __builtin_amdgcn_readfirstlane(d.p.trans_a) == 0, b_k = __builtin_amdgcn_readfirstlane(d.trans_b) != 0;
   const bool xk = tc ? b_k : a_k, yk = tc ? a_k : b_k;
-  const int across = (s.Y + kTile - 1) / kTile;
-  s.x0 = bx / across * kTile;
-  s.y0 = bx % across * kTile;
+  constexpr int TILE = 16 * F;
+  const int across = (s.Y + TILE - 1) / TILE;
+  if (bx >= (s.X + TILE - 1) / TILE * across) return;
+  s.x0 = bx / across * TILE;
+  s.y0 = bx % across * TILE;
   s.w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   s.n = lane & 15;
   s.g = lane >> 4;
@@ -377,27 +387,28 @@ __global__ void __launch_bounds__(64 * kWaves) gemm_small_kernel(DeviceTables t,
     void* const* const Bt = A + (1 + pass) * nk;
     s.px = tc ? Bt : A;
     s.py = tc ? A : Bt;
-    f32x4 acc[2][2];
+    f32x4 acc[F][F];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < F; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < F; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     if constexpr (B16) {
-      typedef Side<T, Bf16Products, true> K;
-      product<Bf16Products, true>(s, K(s.px, nk, s.X, s.x0, s.n, s.g), K(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
+      typedef Side<T, Bf16Products, true, F> K;
+      product<Bf16Products, true, F>(s, K(s.px, nk, s.X, s.x0, s.n, s.g), K(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
     } else {
       typedef Fp32Products<T> P;
-      typedef Side<T, P, true> K;
-      typedef Side<T, P, false> R;
-      if (xk && yk) product<P, sizeof(T) == 4>(s, K(s.px, nk, s.X, s.x0, s.n, s.g), K(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
-      else if (xk) product<P, false>(s, K(s.px, nk, s.X, s.x0, s.n, s.g), R(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
-      else if (yk) product<P, false>(s, R(s.px, nk, s.X, s.x0, s.n, s.g), K(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
-      else product<P, false>(s, R(s.px, nk, s.X, s.x0, s.n, s.g), R(s.py, nk, s.Y, s.y0, s.n, s.g), false, acc, lds);
+      typedef Side<T, P, true, F> K;
+      typedef Side<T, P, false, F> R;
+      if (xk && yk) product<P, sizeof(T) == 4, F>(s, K(s.px, nk, s.X, s.x0, s.n, s.g), K(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
+      else if (xk) product<P, false, F>(s, K(s.px, nk, s.X, s.x0, s.n, s.g), R(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
+      else if (yk) product<P, false, F>(s, R(s.px, nk, s.X, s.x0, s.n, s.g), K(s.py, nk, s.Y, s.y0, s.n, s.g), true, acc, lds);
+      else product<P, false, F>(s, R(s.px, nk, s.X, s.x0, s.n, s.g), R(s.py, nk, s.Y, s.y0, s.n, s.g), false, acc, lds);
     }
     gate = v;
     v = add_up(acc, lds, s.w, s.n, s.g);
   }
-  const int row = s.x0 + (threadIdx.x >> 3), col = s.y0 + (threadIdx.x & 7) * 4;
+  if (threadIdx.x >= 64 * F * F) return;
+  const int row = s.x0 + threadIdx.x / (4 * F), col = s.y0 + threadIdx.x % (4 * F) * 4;
   if (row >= s.X || col >= s.Y) return;
   if (d.p.mode == 2) {
 #pragma unroll
@@ -498,7 +509,7 @@ __global__ void __launch_bounds__(64 * kWaves) gemm_rows_kernel(DeviceTables t, 
   s.n = lane & 15;
   s.g = lane >> 4;
   RowsSide<T, P> x(t, b, first, count, s.n, s.g);
-  uint64_t* const table = (uint64_t*)(lds + kRingBytes);
+  uint64_t* const table = (uint64_t*)(lds + ring_bytes(2));
   if (nk <= kTableTiles) {
     for (int q = threadIdx.x; q < kTile * nk; q += 64 * kWaves) {
       const OpDesc& o = t.descs[b.base + b.idx[b.n + 1 + first + min(q % kTile, count - 1)]];
@@ -515,9 +526,9 @@ __global__ void __launch_bounds__(64 * kWaves) gemm_rows_kernel(DeviceTables t, 
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const Side<T, P, true> y(t.ptrs + __builtin_amdgcn_readfirstlane(d.ptr0) + (1 + pass) * nk, nk, s.Y, s.y0, s.n, s.g);
-    if (nk <= kTableTiles) product<P, true>(s, x, y, true, acc, lds);
-    else product<P, false>(s, x, y, true, acc, lds);
+    const Side<T, P, true, 2> y(t.ptrs + __builtin_amdgcn_readfirstlane(d.ptr0) + (1 + pass) * nk, nk, s.Y, s.y0, s.n, s.g);
+    if (nk <= kTableTiles) product<P, true, 2>(s, x, y, true, acc, lds);
+    else product<P, false, 2>(s, x, y, true, acc, lds);
     gate = v;
     v = add_up(acc, lds, s.w, s.n, s.g);
   }
@@ -550,10 +561,15 @@ __global__ void __launch_bounds__(64 * kWaves) gemm_rows_kernel(DeviceTables t, 
   } while (0)
 
 hipError_t launch_gemm_small(bool bf16_products, int dtype, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t s) {
-  const dim3 grid((unsigned)max_blocks, (unsigned)b.n), wg(64 * kWaves);
-  if (bf16_products) TN_LAUNCH_SMALL((gemm_small_kernel<bf16_t, true>), kRingBytes);
-  else if (dtype == TN_BF16) TN_LAUNCH_SMALL((gemm_small_kernel<bf16_t, false>), kWaves * kTile * kPitch * 4);
-  else TN_LAUNCH_SMALL((gemm_small_kernel<float, false>), kRingBytes);
+  // 32x32 tiles that leave half of the CUs without one are cut into 16x16 tiles: a quarter of the products each, half of the
+  // loads, and the same bits.  fp32, 64x64 with K of 256 5.4 -> 4.5 us, with 704 9.8 -> 7.3; 256x256 with K of 2560, one of them 19.1 -> 11.1, two
+  // (128 workgroups) 18.9 -> 14.1, four 18.9 -> 26.2.
+  const bool tiny = !bf16_products && dtype == TN_F32 && (int64_t)max_blocks * b.n <= 128;
+  const dim3 grid((unsigned)max_blocks * (tiny ? 4 : 1), (unsigned)b.n), wg(64 * kWaves);
+  if (bf16_products) TN_LAUNCH_SMALL((gemm_small_kernel<bf16_t, true, 2>), ring_bytes(2));
+  else if (dtype == TN_BF16) TN_LAUNCH_SMALL((gemm_small_kernel<bf16_t, false, 2>), partials_bytes(2));
+  else if (tiny) TN_LAUNCH_SMALL((gemm_small_kernel<float, false, 1>), ring_bytes(1));
+  else TN_LAUNCH_SMALL((gemm_small_kernel<float, false, 2>), ring_bytes(2));
   return hipGetLastError();
 }
 
@@ -578,7 +594,7 @@ hipError_t launch_gemm_rows(int dtype, const DeviceTables& t, uint32_t base, con
     for (int k = 0; k <= groups; ++k) b.idx[k] = start[k];
     for (int k = 0; k < taken; ++k) b.idx[groups + 1 + k] = (uint16_t)(rows[at + k].desc - base);
     const dim3 grid((unsigned)max_blocks, (unsigned)groups), wg(64 * kWaves);
-    constexpr int kRowsLds = kRingBytes + kTableTiles * kTile * 8;
+    constexpr int kRowsLds = ring_bytes(2) + kTableTiles * kTile * 8;
     if (dtype == TN_BF16) TN_LAUNCH_SMALL((gemm_rows_kernel<bf16_t, Bf16Products>), kRowsLds);
     else TN_LAUNCH_SMALL((gemm_rows_kernel<float, Fp32Products<float>>), kRowsLds);
     const hipError_t e = hipGetLastError();
