@@ -456,6 +456,21 @@ __global__ void __launch_bounds__(256) silu_bwd_kernel(DeviceTables t, Batch b) 
       *(uint4*)(o + i0) = vo;
       return;
     }
+  } else if (i0 + 8 <= n) {  // (element by element, eight waits one behind the other, 64x64 took 5.8 us; so 2.9)
+    f32x4 a[2], g[2], u[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      a[h] = ld4(dact + i0 + 4 * h);
+      g[h] = ld4(gate + i0 + 4 * h);
+      u[h] = ld4(up + i0 + 4 * h);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) a[h][k] = grad(a[h][k], g[h][k], u[h][k]);
+      st4(o + i0 + 4 * h, a[h]);
+    }
+    return;
   }
   for (int i = i0; i < min(i0 + 8, n); ++i) st(o + i, grad(ld(dact + i), ld(gate + i), ld(up + i)));
 }
@@ -555,6 +570,27 @@ __global__ void __launch_bounds__(256) rms_bwd_apply_kernel(DeviceTables t, Batc
       *(uint4*)(o + e) = vo;
       return;
     }
+  } else if ((d.cols & 7) == 0) {  // (element by element 64x64 took 6.7 us; so 3.1)
+    const size_t e = (size_t)row * d.cols + c0;
+    f32x4 vd[2], vx[2], vg[2], vr[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      vd[h] = ld4(dy + e + 4 * h);
+      vx[h] = ld4(x + e + 4 * h);
+      vg[h] = ld4(g + c0 + 4 * h);
+      vr[h] = res ? ld4(res + e + 4 * h) : (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float v = r * vg[h][q] * vd[h][q] - vx[h][q] * k;
+        if (res) v += vr[h][q];
+        vd[h][q] = v;
+      }
+      st4(o + e + 4 * h, vd[h]);
+    }
+    return;
   }
   for (int c = c0; c < min(c0 + 8, d.cols); ++c) {
     const size_t e = (size_t)row * d.cols + c;
