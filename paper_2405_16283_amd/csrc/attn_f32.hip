@@ -83,14 +83,19 @@ template <typename T, int HD, int I0 = 0, int N = kPieces(HD)>
 __device__ __forceinline__ void load_chunk_vt(const Side<T, HD>& s, bool transposed, int row0, f32x4 (&v)[N]) {
   const int rt0 = row0 / s.trows, rin0 = row0 - rt0 * s.trows, n = min(kRows, s.rows - row0);
   const int pitch = min(s.trows, s.rows - rt0 * s.trows);
-  const bool plain = s.whole && transposed && rin0 + n <= s.trows && pitch % 4 == 0 && rin0 % 4 == 0;
-  const T* base = plain ? (const T*)s.t[rt0 * s.nc + s.ct] + (size_t)s.cin * pitch + rin0 : nullptr;
+  const bool linear = s.whole && transposed && rin0 + n <= s.trows;  // one tile: the address is linear in the key and the column
+  const bool plain = linear && pitch % 4 == 0 && rin0 % 4 == 0;
+  const T* base = linear ? (const T*)s.t[rt0 * s.nc + s.ct] + (size_t)s.cin * pitch + rin0 : nullptr;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const int p = (I0 + i) * 256 + threadIdx.x, c = p / 16, k = (p % 16) * 4;
     v[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
     if (plain) {  // n is a multiple of 4 here: the tile's rows are
       if (k < n) v[i] = ld4(base + (size_t)c * pitch + k);
+    } else if (linear) {  // (347 keys: with the tile looked up for every element 132 us a launch, so 103)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (k + e < n) v[i][e] = ld(base + (size_t)c * pitch + k + e);
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
