@@ -1230,7 +1230,9 @@ __global__ void __launch_bounds__(kCopyThreads) copy_kernel(CopyBatch b) {
 
 // Copies inside GPU memory: nothing to keep off the compute units and no search for the tensor a piece belongs to (a
 // column of the grid per tensor; walking the list cost a workgroup more than its piece), four 16-byte loads per
-// lane in flight in registers.
+// lane in flight in registers.  What is read is not read again soon and need not stay in the caches: placing the 405 MB of a 7B-shaped
+// layer takes 60 us less of 1.32 ms in one launch instead of seven, and 30 more with loads that pass the caches by (400 MB by themselves
+// 155 and 134 us, 5.4 and 6.2 TB/s read and written).
 __global__ void __launch_bounds__(kDeviceCopyThreads) device_copy_kernel(CopyBatch b) {
   const CopyItem it = b.it[blockIdx.y];
   constexpr int N = kCopyBlockBytes / 16 / kDeviceCopyThreads;
@@ -1244,7 +1246,7 @@ __global__ void __launch_bounds__(kDeviceCopyThreads) device_copy_kernel(CopyBat
     if (len == kCopyBlockBytes) {
       uint4 v[N];
 #pragma unroll
-      for (int k = 0; k < N; ++k) v[k] = ((const uint4*)src)[threadIdx.x + kDeviceCopyThreads * k];
+      for (int k = 0; k < N; ++k) v[k] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const f32x4*)src + threadIdx.x + kDeviceCopyThreads * k));
 #pragma unroll
       for (int k = 0; k < N; ++k) ((uint4*)dst)[threadIdx.x + kDeviceCopyThreads * k] = v[k];
     } else {
