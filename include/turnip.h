@@ -451,7 +451,9 @@ tn_status tn_memgraph_simulate(const tn_memgraph* mg, const int64_t* order, int6
 
 /* IN_ORDER is the deterministic executor of the ablation in Section 8 (item 3): kernels are launched
  * strictly in the serial order the memgraph was compiled for, and so are the transfers of each
- * direction; a vertex whose turn has come but which is not ready holds back everything behind it. */
+ * direction; a vertex whose turn has come but which is not ready holds back everything behind it.
+ * Under BY_ORDER the ready vertex that stands first in the serial order goes first, except that host -> GPU loads that
+ * do not wait for memory go in the order in which they let kernels run, where that is expected to pay. */
 enum { TN_POLICY_FIFO = 0, TN_POLICY_LIFO = 1, TN_POLICY_RANDOM = 2, TN_POLICY_BY_ORDER = 3, TN_POLICY_IN_ORDER = 4 };
 /* How transfers are carried out.  MEMCPY: one hipMemcpyAsync per tensor on the copy streams.
  * KERNEL: one grouped copy kernel per group of ready transfers, on the same streams; needs every

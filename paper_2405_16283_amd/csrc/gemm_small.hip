@@ -262,7 +262,7 @@ __device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors
     for (int q = 0; q < kStages - 1 && q < mine; ++q) load_next();
     // One piece: its fragments are read, and behind them the loads of the piece three on are issued, into the stage of the one
     // before.  (Taking these in turn with the MFMAs of the piece before, with two sets of registers, needs several
-    // copies of the loop: 0.3 us faster per 32 KiB of operands, but 0.5 us for the first of them, instructions come cold.)
+    // copies of the loop, whose instructions come cold: 256x256 with K of 2560 took 18.8 us against 19.1, 64x64 with K of 704 10.3 against 9.8.)
 #pragma clang loop unroll(disable)
     for (int done = 0; done < mine; ++done) {
       const int behind = issued - done - 1;  // pieces behind this one that may be on their way

@@ -456,7 +456,7 @@ __global__ void __launch_bounds__(256) silu_bwd_kernel(DeviceTables t, Batch b) 
       *(uint4*)(o + i0) = vo;
       return;
     }
-  } else if (i0 + 8 <= n) {  // (element by element, eight waits one behind the other, 64x64 took 5.8 us; so 2.9)
+  } else if (i0 + 8 <= n) {  // (element by element, eight waits one behind the other, 64x64 took 5.8 us; so 3.1)
     f32x4 a[2], g[2], u[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -653,7 +653,8 @@ typedef __attribute__((address_space(3))) void* lptr_t;
 // inline assembly so that the compiler does not track it: the kernel keeps several such loads
 // in flight across barriers and waits for them with explicit vmcnt values.
 __device__ __forceinline__ void load_lds16(const void* gsrc, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gsrc), "s"(lds_addr) : "memory");
+  // m0 is read one wait state after it is written at the earliest
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gsrc), "s"(lds_addr) : "memory");
 }
 // Reads of the (read-only, wavefront-uniform) operand tables through the scalar unit, so that
 // they are counted by lgkmcnt and never force a wait on the vector loads in flight.
@@ -1231,8 +1232,8 @@ __global__ void __launch_bounds__(kCopyThreads) copy_kernel(CopyBatch b) {
 // Copies inside GPU memory: nothing to keep off the compute units and no search for the tensor a piece belongs to (a
 // column of the grid per tensor; walking the list cost a workgroup more than its piece), four 16-byte loads per
 // lane in flight in registers.  What is read is not read again soon and need not stay in the caches: placing the 405 MB of a 7B-shaped
-// layer takes 60 us less of 1.32 ms in one launch instead of seven, and 30 more with loads that pass the caches by (400 MB by themselves
-// 155 and 134 us, 5.4 and 6.2 TB/s read and written).
+// layer, 217 us in seven launches of the plain loads, takes 120 to 135 in one with loads that pass the caches by (6.0 to 6.7 TB/s read and
+// written); a prompt of 1371 tokens on that layer 1.33 ms before, 1.26 in one launch, 1.22 with these loads.
 __global__ void __launch_bounds__(kDeviceCopyThreads) device_copy_kernel(CopyBatch b) {
   const CopyItem it = b.it[blockIdx.y];
   constexpr int N = kCopyBlockBytes / 16 / kDeviceCopyThreads;
