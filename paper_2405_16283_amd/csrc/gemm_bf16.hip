@@ -16,7 +16,8 @@
 //
 // Operands lie in LDS in regions of 128 rows x 64 of K (16 KiB), a ring of them that `buffer_load ... lds` fills directly, 64 lanes
 // x 16 bytes per instruction, unpadded: piece c of row r lies at position c ^ (r & 7) of its row, so that the 16 lanes
-// of a fragment read fall on different banks.  Rows past the edge of a ragged tile are clamped (their products are never
+// of a fragment read fall on different banks.  A resource begins at the workgroup's first row, found in 64 bits: tiles of any size are
+// fine as long as 256 of their rows stay below 4 GiB.  Rows past the edge of a ragged tile are clamped (their products are never
 // stored); past the end of K a lane's offset lies outside the buffer resource and zeros arrive, in both operands.  Chunks are
 // taken two at a time, an odd one is followed by zeros.
 #include <type_traits>
@@ -100,6 +101,10 @@ struct Source {
   __device__ __forceinline__ static rsrc_t resource(const void* p) {
     return (rsrc_t){(uint32_t)(uintptr_t)p, (uint32_t)((uintptr_t)p >> 32) & 0xFFFFu, 0xFFFFFFF0u, 0x00020000u};
   }
+  // a tile's resource, from the workgroup's first row on
+  __device__ __forceinline__ rsrc_t tile(const void* const* p, int row0) const {
+    return resource((const char*)sload_ptr(p) + (uint64_t)(uint32_t)row0 * (uint32_t)K * 2u);
+  }
   // (lane goes through an empty asm statement: rows and columns are not to be kept in registers between two calls)
   __device__ __forceinline__ void set_offsets(const Job& j, int w, int lane) {
     asm volatile("" : "+v"(lane));
@@ -110,13 +115,13 @@ struct Source {
 #pragma unroll
       for (int h = 0; h < HP; ++h) {
         const int row = HP == 1 ? rr : (rr >> 6) * 128 + h * 64 + (rr & 63);
-        off_p[h][i] = (uint32_t)(min(j.p0 + row, j.P - 1) * K + lcol) * 2u;
+        off_p[h][i] = ((uint32_t)min(row, j.P - 1 - j.p0) * (uint32_t)K + (uint32_t)lcol) * 2u;
       }
 #pragma unroll
       for (int h = 0; h < HQ; ++h) {
         const int row = HQ == 1 ? rr : (rr >> 6) * 128 + h * 64 + (rr & 63);
         // gated: 32 rows of the gate tile, then the 32 rows of the up tile for the same outputs, and so on
-        off_q[h][i] = (uint32_t)(min(j.q0 + (j.gated ? (row >> 6) * 32 + (row & 31) : row), j.Q - 1) * K + lcol) * 2u;
+        off_q[h][i] = ((uint32_t)min(j.gated ? (row >> 6) * 32 + (row & 31) : row, j.Q - 1 - j.q0) * (uint32_t)K + (uint32_t)lcol) * 2u;
       }
     }
   }
@@ -135,9 +140,9 @@ struct Source {
     kt = k0 = 0;
     at = 0;
     K = sload_int(j.ksz);
-    rp = resource(sload_ptr(j.tiles_p));
-    rq = resource(sload_ptr(j.tiles_q));
-    rq2 = j.gated ? resource(sload_ptr(j.tiles_q + j.nk)) : rq;
+    rp = tile(j.tiles_p, j.p0);
+    rq = tile(j.tiles_q, j.q0);
+    rq2 = j.gated ? tile(j.tiles_q + j.nk, j.q0) : rq;
     set_offsets(j, w, lane);
     if (K < kChunk) cut_offsets(lane);
   }
@@ -149,14 +154,12 @@ struct Source {
       ++kt;
       k0 = 0;
       at = 0;
-      const int next = sload_int(j.ksz + kt);
-      rp = resource(sload_ptr(j.tiles_p + kt));
-      rq = resource(sload_ptr(j.tiles_q + kt));
-      rq2 = j.gated ? resource(sload_ptr(j.tiles_q + j.nk + kt)) : rq;
-      if (next != K || K % kChunk) {
-        K = next;
-        set_offsets(j, w, lane);
-      }
+      const int before = K;
+      K = sload_int(j.ksz + kt);
+      rp = tile(j.tiles_p + kt, j.p0);
+      rq = tile(j.tiles_q + kt, j.q0);
+      rq2 = j.gated ? tile(j.tiles_q + j.nk + kt, j.q0) : rq;
+      if (K != before || K % kChunk) set_offsets(j, w, lane);
     }
     if (k0 + kChunk > K) cut_offsets(lane);
   }

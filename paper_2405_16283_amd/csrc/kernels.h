@@ -125,6 +125,7 @@ inline int32_t gemm_blocks(int tile, const OpDesc& d) {  // workgroups for outpu
   const int q = d.p.mode == 2 ? tile / 2 : tile;         // gate and up products take half a tile's columns each
   return (int32_t)(((int64_t)d.rows + tile - 1) / tile * (((int64_t)d.cols + q - 1) / q));
 }
+constexpr int32_t kGemmBf16MaxK = (1 << 23) - 8;  // their offsets from a workgroup's first row hold 256 rows of a tile that is no deeper
 hipError_t launch_gemm_bf16(int form, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t stream);
 
 // LC_GEMM_F32 and LC_GEMM_BF16_SMALL: gemm_small.hip.

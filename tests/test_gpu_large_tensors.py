@@ -48,6 +48,12 @@ PRODUCTS = [
     ("f32", 33000, 16, 32768, 0, 1),      # A
     ("f32", 16, 33000, 32768, 0, 0),      # B, stored [K, n]
     ("bf16", 66000, 16, 32768, 0, 1),     # A, bf16 products
+    ("bf16", 66000, 128, 32768, 0, 1),    # A, tiles of 128x128
+    ("bf16", 128, 66000, 32768, 0, 1),    # B
+    ("bf16", 66000, 256, 32776, 0, 1),    # A, K no multiple of the chunks along it
+    ("bf16", 66000, 520, 32768, 0, 1),    # A, tiles of 256x256
+    ("bf16", 257, 256, (1 << 23) - 8, 0, 1),  # 257 rows along K, the deepest that these kernels take
+    ("bf16", 72, 128, (1 << 23) + 8, 0, 1),   # deeper
     ("f32", 1, 33000, 32768, 0, 1),       # B of a single row
     ("bf16", 1, 66000, 32768, 0, 1),
     ("f32", 33, 1, (1 << 25) + 64, 0, 1),  # 32 rows along K
@@ -77,7 +83,7 @@ def test_products_of_operands_beyond_4_gib(dtype, m, n, k, ta, tb):
     ex = B.tn_executor_create(mg, dev.data_ptr(), cap, 0, 0, [st[0].cuda_stream], st[1].cuda_stream, st[2].cuda_stream)
     try:
         B.tn_executor_place_inputs(ex, [a.data_ptr(), b.data_ptr(), 0])
-        B.tn_execute(ex, [0, 0, 0], [out.data_ptr()], None)
+        B.tn_execute(ex, [0, 0, 0], [out.data_ptr()], B.tn_exec_opts(small_gemm_tiles=-1 if k >> 22 else 0))  # (-1: 256 rows to a workgroup)
     finally:
         B.tn_executor_destroy(ex)
         B.tn_memgraph_destroy(mg)
