@@ -57,7 +57,7 @@ __device__ __forceinline__ void load_lds(uint32_t voff, rsrc_t r, uint32_t soff,
 }
 // The accumulators stay in the accumulation registers and each is updated in place: left to itself the compiler gives the
 // result other registers than the summand, and the 256 of a wavefront do not fit twice.  It does not know that these
-// are MFMAs, so whatever else reads an accumulator comes after mfma_drain().
+// are MFMAs, so whatever else reads accumulators comes after mfma_drain(), through which they pass.
 __device__ __forceinline__ void mfma(f32x4& c, bf16x8 x, bf16x8 y) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(y));
 }
@@ -66,7 +66,14 @@ __device__ __forceinline__ void mfma_then_load(f32x4& c, bf16x8 x, bf16x8 y, uin
   asm volatile("s_add_u32 m0, %6, %7\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tbuffer_load_dwordx4 %3, %4, %5 offen lds"
                : "+a"(c) : "v"(x), "v"(y), "v"(voff), "s"(r), "s"(soff), "s"(lds_addr), "n"(imm) : "memory", "scc");
 }
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+template <int N, int M>
+__device__ __forceinline__ void mfma_drain(f32x4 (&acc)[N][M]) {
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = 0; j < M; ++j) asm volatile("" : "+a"(acc[i][j]));  // behind the wait: volatile statements keep their order
+}
 
 // all LDS operations of this wavefront done and at most N (0..63) of its loads on their way
 template <int N>
@@ -193,89 +200,95 @@ __device__ __forceinline__ int count_chunks(const Job& j) {  // an even number
   return (n + 1) & ~1;
 }
 
-// Stores a wavefront's TQ x TP accumulator tiles of 16x16 as bf16.  They go through LDS of the wavefront's own, 32 P rows at a time,
-// so that a store instruction writes whole runs of a row, 16 bytes per lane: from the accumulator layout, 8 bytes in each
-// of 16 rows, the stores of a 256x256 tile take 17 us, this way 10 (two bytes per lane, as before: 11).
-// MODE 1: a [P, Q] bf16 tensor R is added before the rounding.  MODE 2: silu(gate) * up, tiles 4n, 4n+1 are gates, the next two their ups.
-constexpr int epilogue_pitch(int tq) { return tq * 32 + 16; }  // bytes
+// Stores a wavefront's TQ x TP accumulator tiles of 16x16 as bf16.  They go through LDS of the wavefront's own, 32 P rows at a time, so that a
+// store instruction writes whole runs of a row, 16 bytes per lane.  They lie there in fp32, straight from their
+// registers, whatever becomes of them then: a wavefront with 256 accumulators has no others to turn them over in.  Those of the 128x128 form
+// are rounded before, where nothing is left to be done to them (LDS is what bounds its epilogue).
+// Against bf16 rows in LDS for every form, which left the 256x256 form 152 bytes of scratch, and element by element stores of 16 bytes
+// per lane where rows are not aligned: 512x512 with K of 1024, 300 of them, 173 -> 158 us; with K of 504, 100 of them, 52 -> 46;
+// 347x512 with K of 4096 stored transposed, 32 of them, 61 -> 56; 96x100 with K of 512, 300 of them, 20 -> 15.
+// MODE 1: a [P, Q] bf16 tensor R is added before the rounding.  MODE 2: silu(gate) * up, every 32 gates are followed by their 32 ups.
+constexpr int epilogue_pitch(int tq) { return tq * 64 + 16; }  // bytes
 constexpr int epilogue_bytes(int tq) { return 32 * epilogue_pitch(tq); }
-template <int MODE, int TQ, int TP>
+constexpr int kRounded = 3;  // a MODE
+// V columns per lane (1: any row length; else rows of C are aligned to V elements)
+template <int MODE, int TQ, int V>
+__device__ __forceinline__ void store_rows(const char* st, bf16_t* C, int P, int Q, int prow0, int qcol0, int lane, const bf16_t* R) {
+  constexpr int QW = MODE == 2 ? 8 * TQ : 16 * TQ;  // columns of the wavefront's piece
+  constexpr int LPR = QW / V < 64 ? QW / V : 64, RPI = 64 / LPR;  // lanes per row, rows per store instruction
+  typedef float vec __attribute__((ext_vector_type(V)));
+  typedef bf16_t half_vec __attribute__((ext_vector_type(V)));
+#pragma clang loop unroll_count(4)
+  for (int n = 0; n < 32 / RPI; ++n) {
+    const int r = n * RPI + lane / LPR, row = prow0 + r;
+    const char* const from = st + r * epilogue_pitch(TQ);
+#pragma unroll
+    for (int half = 0; half < QW / (LPR * V); ++half) {
+      const int cin = (half * LPR + lane % LPR) * V, c = qcol0 + cin;
+      const size_t at = (size_t)row * Q + c;
+      half_vec out;
+      if constexpr (MODE == kRounded) {
+        out = *(const half_vec*)(from + 2 * cin);
+      } else {
+        const float* const x = (const float*)from + (MODE == 2 ? (cin >> 5) * 64 + (cin & 31) : cin);
+        vec v = *(const vec*)x, u = v;
+        if constexpr (MODE == 2) u = *(const vec*)(x + 32);
+        if constexpr (MODE == 1) {
+          if (row < P && c < Q) {
+            const half_vec res = *(const half_vec*)(R + at);
+#pragma unroll
+            for (int k = 0; k < V; ++k) v[k] += bf2f(res[k]);
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+          if constexpr (MODE == 2) v[k] = v[k] / (1.f + __expf(-v[k])) * u[k];
+          out[k] = f2bf(v[k]);
+        }
+      }
+      if (row < P && c < Q) *(half_vec*)(C + at) = out;
+    }
+  }
+}
+template <int MODE, int TQ, int TP, int V>
 __device__ __forceinline__ void store_tiles(const f32x4 (&acc)[TQ][TP], char* st, bf16_t* C, int P, int Q, int prow0, int qcol0, int lane,
                                             const bf16_t* R) {
-  constexpr int QW = MODE == 2 ? 8 * TQ : 16 * TQ;  // columns of the wavefront's piece
   constexpr int PITCH = epilogue_pitch(TQ);
-  constexpr int LPR = QW / 8, RPI = 64 / LPR;       // lanes per row, rows per store instruction
-  const int l16 = lane & 15, g = lane >> 4;
-  const int rin = lane / LPR, cin = (lane % LPR) * 8;
-  const bool whole = (Q & 7) == 0;  // rows of C are 16-byte aligned
+  char* const to = st + (lane & 15) * PITCH + (lane >> 4) * (MODE == kRounded ? 8 : 16);
 #pragma unroll
   for (int h = 0; h < TP / 2; ++h) {
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {
-      const int j = 2 * h + jj, prow = prow0 + 16 * j + l16;
-      char* const to = st + (16 * jj + l16) * PITCH + 8 * g;
+    for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
       for (int i = 0; i < TQ; ++i) {
-        if (MODE == 2 && (i & 2)) continue;
-        float v[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = acc[i][j][r];
-        if constexpr (MODE == 2) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] = v[r] / (1.f + __expf(-v[r])) * acc[i | 2][j][r];
-        }
-        const int c = MODE == 2 ? (i >> 2) * 32 + (i & 1) * 16 : i * 16;  // column of the piece
-        if constexpr (MODE == 1) {
-          const int q = qcol0 + c + 4 * g;
-          if (prow < P) {
-            const bf16_t* at = R + (size_t)prow * Q + q;
-            if ((Q & 3) == 0 && q + 3 < Q) {
-              const f32x4 x = ld4(at);
-#pragma unroll
-              for (int r = 0; r < 4; ++r) v[r] += x[r];
-            } else {
-#pragma unroll
-              for (int k = 0; k < 4; ++k)
-                if (q + k < Q) v[k] += bf2f(at[k]);
-            }
-          }
-        }
-        *(uint2*)(to + c * 2) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+        const f32x4 v = acc[i][2 * h + jj];
+        if constexpr (MODE == kRounded) *(uint2*)(to + 16 * jj * PITCH + 32 * i) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+        else *(f32x4*)(to + 16 * jj * PITCH + 64 * i) = v;
       }
-    }
-#pragma unroll
-    for (int n = 0; n < 32 / RPI; ++n) {
-      const int r = n * RPI + rin, row = prow0 + 32 * h + r, c = qcol0 + cin;
-      const uint4 x = *(const uint4*)(st + r * PITCH + cin * 2);
-      if (row >= P || c >= Q) continue;
-      bf16_t* dst = C + (size_t)row * Q + c;
-      if (whole && c + 7 < Q) {
-        *(uint4*)dst = x;
-      } else {
-        const bf16_t* e = (const bf16_t*)(st + r * PITCH + cin * 2);
-#pragma clang loop unroll(disable)
-        for (int k = 0; k < 8 && c + k < Q; ++k) dst[k] = e[k];
-      }
-    }
+    store_rows<MODE, TQ, V>(st, C, P, Q, prow0 + 32 * h, qcol0, lane, R);
   }
 }
 // wp, wq: the wavefront's place in the tile
 template <int TQ, int TP>
 __device__ __forceinline__ void finish(const f32x4 (&acc)[TQ][TP], char* lds, const DeviceTables& t, const OpDesc& d, const Job& j, int w,
                                        int wp, int wq, int lane) {
-  mfma_drain();
   __syncthreads();  // nobody reads the regions any more
   char* const st = lds + w * epilogue_bytes(TQ);
   bf16_t* const C = (bf16_t*)d.out;
   const int p = j.p0 + wp * 16 * TP, q = j.q0 + wq * (j.gated ? 8 * TQ : 16 * TQ);
-  if (j.gated) {
-    store_tiles<2>(acc, st, C, j.P, j.Q, p, q, lane, nullptr);
-  } else if (d.p.mode == 1) {
-    const bf16_t* R = (const bf16_t*)sload_ptr(t.ptrs + __builtin_amdgcn_readfirstlane(d.ptr0 + 2 * j.nk));
-    store_tiles<1>(acc, st, C, j.P, j.Q, p, q, lane, R);
-  } else {
-    store_tiles<0>(acc, st, C, j.P, j.Q, p, q, lane, nullptr);
-  }
+  const int mode = __builtin_amdgcn_readfirstlane(d.p.mode);
+  const bf16_t* const R = mode == 1 ? (const bf16_t*)sload_ptr(t.ptrs + __builtin_amdgcn_readfirstlane(d.ptr0 + 2 * j.nk)) : nullptr;
+  // (modes outermost: what a short product takes is the way of its instructions from memory as much as anything, and those that are
+  // run lie next to each other)
+  auto store = [&](auto v) __attribute__((always_inline)) {
+    constexpr int V = decltype(v)::value;
+    if (mode == 0) store_tiles<TQ == 4 ? kRounded : 0, TQ, TP, V>(acc, st, C, j.P, j.Q, p, q, lane, R);
+    else if (mode == 1) store_tiles<1, TQ, TP, V>(acc, st, C, j.P, j.Q, p, q, lane, R);
+    else store_tiles<2, TQ, TP, V>(acc, st, C, j.P, j.Q, p, q, lane, R);
+  };
+  if ((j.Q & 7) == 0) store(std::integral_constant<int, 8>());
+  else if ((j.Q & 3) == 0) store(std::integral_constant<int, 4>());
+  else store(std::integral_constant<int, 1>());
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -404,10 +417,23 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_256_kernel(DeviceTables t, B
       TN_QUARTER(1, 0, fp[0], base_p, true, 3);
       TN_QUARTER(1, 1, fq[0], base_q, false, 0);
     };
+    // (the loops end in the wait: where paths meet, the compiler moves accumulators)
     int r = 0;
-    for (; r + 8 + NS < total; r += 8) two_chunks(std::integral_constant<bool, true>());
-    mfma_drain();
-    for (; r < total; r += 8) two_chunks(std::integral_constant<bool, false>());
+    if (8 + NS < total)
+      for (;;) {
+        two_chunks(std::integral_constant<bool, true>());
+        r += 8;
+        if (r + 8 + NS < total) continue;
+        mfma_drain(acc);
+        break;
+      }
+    for (;;) {
+      two_chunks(std::integral_constant<bool, false>());
+      r += 8;
+      if (r < total) continue;
+      mfma_drain(acc);
+      break;
+    }
   }
 #undef TN_QUARTER
 #undef TN_READ_REGION
@@ -522,14 +548,22 @@ __global__ void __launch_bounds__(256, NC == 2 ? 2 : 1) gemm_bf16_128_kernel(Dev
       if (more) next_chunk();
     };
     int c = 0;
-    for (; c + 2 + NC <= total; c += 2) {
-      chunk(std::integral_constant<bool, true>(), xp, xq, yp, yq);
-      chunk(std::integral_constant<bool, true>(), yp, yq, xp, xq);
-    }
-    mfma_drain();
-    for (; c < total; c += 2) {
+    if (2 + NC <= total)
+      for (;;) {
+        chunk(std::integral_constant<bool, true>(), xp, xq, yp, yq);
+        chunk(std::integral_constant<bool, true>(), yp, yq, xp, xq);
+        c += 2;
+        if (c + 2 + NC <= total) continue;
+        mfma_drain(acc);
+        break;
+      }
+    for (;;) {  // (at least two chunks are left: the ring holds as many)
       chunk(std::integral_constant<bool, false>(), xp, xq, yp, yq);
       chunk(std::integral_constant<bool, false>(), yp, yq, xp, xq);
+      c += 2;
+      if (c < total) continue;
+      mfma_drain(acc);
+      break;
     }
   }
 #undef TN_PIECE
