@@ -41,6 +41,7 @@ struct VInfo {
   int8_t cls = -1;  // LaunchClass, or -1 for non-kernel vertices
   int8_t dtype = 0;
   int16_t head_dim = 0;
+  int8_t stages = 0;   // gemm_small_stages
   int8_t depth = 0;    // tile products: class of the summed depth K (see the GEMM case of tn_executor_create)
   int16_t group = -1;  // index of its (cls, dtype, head_dim, depth) combination: vertices of one group can share a launch
   int32_t desc = -1;
@@ -470,6 +471,7 @@ tn_status build_tables(tn_executor& ex) {
     }
     d.nblocks = blocks_for(vi.cls, d, aux.data());
     vi.nblocks = d.nblocks;
+    if (vi.cls == LC_GEMM_F32 || vi.cls == LC_GEMM_BF16_SMALL || vi.cls == LC_GEMM_ROWS) vi.stages = (int8_t)gemm_small_stages(vi.cls, d, aux.data() + d.aux0);
     vi.desc = (int32_t)descs.size();
     descs.push_back(d);
   }
@@ -1584,11 +1586,12 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
       for (int64_t m : same) batch.base = std::min(batch.base, (uint32_t)ex->info[m].desc);
       int32_t max_blocks = 0;
       int64_t n_blocks = 0;
+      batch.stages = 0;
       double flops = 0, bytes = 0;
       bool deep = false;
       if (lead.cls == LC_GEMM_ROWS) {  // rows of one key next to each other: they are formed together, and read B once
         row_list.clear();
-        for (int64_t m : same) row_list.push_back({ex->info[m].row_key, (uint32_t)ex->info[m].desc});
+        for (int64_t m : same) row_list.push_back({ex->info[m].row_key, (uint32_t)ex->info[m].desc, ex->info[m].stages});
         std::sort(row_list.begin(), row_list.end(), [](const RowVertex& a, const RowVertex& b) { return a.key < b.key; });
         for (size_t k = 0; k < row_list.size(); ++k)
           if (k == 0 || row_list[k].key != row_list[k - 1].key) bytes += ex->row_bytes[row_list[k].key];
@@ -1597,6 +1600,7 @@ static tn_status run_memgraph(tn_executor* ex, const void* const* host_inputs, v
         const VInfo& v = ex->info[same[k]];
         batch.idx[k] = (uint16_t)(v.desc - batch.base);
         max_blocks = std::max(max_blocks, v.nblocks);
+        batch.stages = std::max<int32_t>(batch.stages, v.stages);
         n_blocks += v.nblocks;
         flops += v.flops;
         bytes += v.bytes;

@@ -19,6 +19,8 @@
 // registers -> by way of LDS: 256x256 in fp32 with K of 1024, one to four of them, 11.5 -> 9.7 us, twelve 28.9 -> 26.2 (61 TFLOP/s); with K of
 // 2560 22.6 -> 19.1 and 66.4 -> 54.8 (73, of 157); 64x64 with K of 256 5.7 -> 5.4, with 704 in tiles of 64 9.5 -> 9.8 (every piece
 // lies in another tile).  bf16: 32 products of 512x16, K 4096, 28 us; 8 of 16x512, K 16384, 53 us.
+#include <algorithm>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -26,15 +28,13 @@ namespace tn {
 namespace {
 
 constexpr int kTile = kGemmSmallTile;  // 32: output rows and columns of a workgroup
-constexpr int kWaves = 4;
-constexpr int kStages = 4;  // pieces of a wavefront in LDS
+constexpr int kWaves = kGemmSmallWaves, kStages = kGemmSmallStages, kTableTiles = kGemmRowsTable;
 // F: fragments of 16 rows or columns per side of a workgroup's tile; floats per row of a partial in LDS, bytes of a piece and of a ring
 constexpr int pitch(int f) { return 16 * f + 4; }
 constexpr int piece_bytes(int f) { return 2 * 16 * f * 128; }
-constexpr int ring_bytes(int f) { return kWaves * kStages * piece_bytes(f); }
 constexpr int partials_bytes(int f) { return kWaves * 16 * f * pitch(f) * 4; }
-constexpr int kTableTiles = 64;    // gemm_rows: K tiles whose addresses are held in LDS
-static_assert(partials_bytes(2) <= ring_bytes(2) && partials_bytes(1) <= ring_bytes(1), "the partials take the place of the ring");
+// (the partials take the place of the rings)
+constexpr int ring_bytes(int f, int stages) { return std::max(kWaves * stages * piece_bytes(f), partials_bytes(f)); }
 static_assert(kTile == 32, "two 16-row MFMA tiles per side");
 
 __device__ __forceinline__ f32x4 ldg4(const TN_GLOBAL float* p) { return *(const TN_GLOBAL f32x4*)p; }
@@ -122,7 +122,7 @@ struct Sides {
   void* const* px;
   void* const* py;
   const int* ks;
-  int nk, X, Y, x0, y0, w, n, g;
+  int nk, X, Y, x0, y0, w, n, g, stages;
   LaneTable sizes;
   __device__ __forceinline__ int size(int q) const { return sizes.size(ks, q); }
 };
@@ -230,8 +230,8 @@ __device__ __forceinline__ void product(const Sides& s, SX x, SY y, bool vectors
   typename P::Vec fx[STAGED ? 1 : 3][2][F], fy[STAGED ? 1 : 3][2][F];
   auto multiply = [&](int b) __attribute__((always_inline)) { P::template multiply<F>(fx[b], fy[b], acc); };
   if constexpr (STAGED) {
-    const uint32_t ring = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t)lds + s.w * kStages * kPieceBytes);
-    const char* const mem = lds + s.w * kStages * kPieceBytes;
+    const uint32_t ring = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t)lds + s.w * s.stages * kPieceBytes);
+    const char* const mem = lds + s.w * s.stages * kPieceBytes;
     uint32_t put = 0, get = 0;  // stages, in bytes
     int issued = 0;
     uint32_t bytes = 0;  // the next piece's place along K
@@ -368,6 +368,7 @@ __global__ void __launch_bounds__(64 * kWaves) gemm_small_kernel(DeviceTables t,
   Sides s;
   s.ks = t.aux + __builtin_amdgcn_readfirstlane(d.aux0);
   s.nk = nk;
+  s.stages = b.stages;
   s.sizes = read_sizes(s.ks, nk);
   s.X = tc ? cols : rows;
   s.Y = tc ? rows : cols;
@@ -500,6 +501,7 @@ __global__ void __launch_bounds__(64 * kWaves) gemm_rows_kernel(DeviceTables t, 
   Sides s;
   s.ks = t.aux + __builtin_amdgcn_readfirstlane(d.aux0);
   s.nk = nk;
+  s.stages = b.stages;
   s.sizes = read_sizes(s.ks, nk);
   s.X = count;
   s.Y = __builtin_amdgcn_readfirstlane(d.cols);
@@ -509,7 +511,7 @@ __global__ void __launch_bounds__(64 * kWaves) gemm_rows_kernel(DeviceTables t, 
   s.n = lane & 15;
   s.g = lane >> 4;
   RowsSide<T, P> x(t, b, first, count, s.n, s.g);
-  uint64_t* const table = (uint64_t*)(lds + ring_bytes(2));
+  uint64_t* const table = (uint64_t*)(lds + ring_bytes(2, b.stages));
   if (nk <= kTableTiles) {
     for (int q = threadIdx.x; q < kTile * nk; q += 64 * kWaves) {
       const OpDesc& o = t.descs[b.base + b.idx[b.n + 1 + first + min(q % kTile, count - 1)]];
@@ -555,9 +557,9 @@ __global__ void __launch_bounds__(64 * kWaves) gemm_rows_kernel(DeviceTables t, 
 
 #define TN_LAUNCH_SMALL(KERNEL, LDS)                                                                                              \
   do {                                                                                                                            \
-    static const hipError_t attr = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, (LDS));   \
+    static const hipError_t attr = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, LDS(kStages)); \
     if (attr != hipSuccess) return attr;                                                                                          \
-    hipLaunchKernelGGL(KERNEL, grid, wg, (LDS), s, t, b);                                                                         \
+    hipLaunchKernelGGL(KERNEL, grid, wg, LDS(b.stages), s, t, b);                                                                         \
   } while (0)
 
 hipError_t launch_gemm_small(bool bf16_products, int dtype, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t s) {
@@ -566,10 +568,12 @@ hipError_t launch_gemm_small(bool bf16_products, int dtype, const DeviceTables& 
   // (128 workgroups) 18.9 -> 14.1, four 18.9 -> 26.2.
   const bool tiny = !bf16_products && dtype == TN_F32 && (int64_t)max_blocks * b.n <= 128;
   const dim3 grid((unsigned)max_blocks * (tiny ? 4 : 1), (unsigned)b.n), wg(64 * kWaves);
-  if (bf16_products) TN_LAUNCH_SMALL((gemm_small_kernel<bf16_t, true, 2>), ring_bytes(2));
-  else if (dtype == TN_BF16) TN_LAUNCH_SMALL((gemm_small_kernel<bf16_t, false, 2>), partials_bytes(2));
-  else if (tiny) TN_LAUNCH_SMALL((gemm_small_kernel<float, false, 1>), ring_bytes(1));
-  else TN_LAUNCH_SMALL((gemm_small_kernel<float, false, 2>), ring_bytes(2));
+  auto lds = [](int stages) { return ring_bytes(2, stages); };
+  auto lds_tiny = [](int stages) { return ring_bytes(1, stages); };
+  if (bf16_products) TN_LAUNCH_SMALL((gemm_small_kernel<bf16_t, true, 2>), lds);
+  else if (dtype == TN_BF16) TN_LAUNCH_SMALL((gemm_small_kernel<bf16_t, false, 2>), lds);
+  else if (tiny) TN_LAUNCH_SMALL((gemm_small_kernel<float, false, 1>), lds_tiny);
+  else TN_LAUNCH_SMALL((gemm_small_kernel<float, false, 2>), lds);
   return hipGetLastError();
 }
 
@@ -577,6 +581,9 @@ hipError_t launch_gemm_rows(int dtype, const DeviceTables& t, uint32_t base, con
                             hipStream_t s) {
   Batch b;
   b.base = base;
+  b.stages = 0;
+  for (int k = 0; k < n; ++k) b.stages = std::max(b.stages, rows[k].stages);
+  auto lds = [](int stages) { return ring_bytes(2, stages) + kTableTiles * kTile * 8; };
   for (int at = 0; at < n;) {
     // as many groups of up to kTile vertices with one key as the list holds: a start per group, the last one's
     // end, and the vertices
@@ -594,9 +601,8 @@ hipError_t launch_gemm_rows(int dtype, const DeviceTables& t, uint32_t base, con
     for (int k = 0; k <= groups; ++k) b.idx[k] = start[k];
     for (int k = 0; k < taken; ++k) b.idx[groups + 1 + k] = (uint16_t)(rows[at + k].desc - base);
     const dim3 grid((unsigned)max_blocks, (unsigned)groups), wg(64 * kWaves);
-    constexpr int kRowsLds = ring_bytes(2) + kTableTiles * kTile * 8;
-    if (dtype == TN_BF16) TN_LAUNCH_SMALL((gemm_rows_kernel<bf16_t, Bf16Products>), kRowsLds);
-    else TN_LAUNCH_SMALL((gemm_rows_kernel<float, Fp32Products<float>>), kRowsLds);
+    if (dtype == TN_BF16) TN_LAUNCH_SMALL((gemm_rows_kernel<bf16_t, Bf16Products>), lds);
+    else TN_LAUNCH_SMALL((gemm_rows_kernel<float, Fp32Products<float>>), lds);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     at += taken;

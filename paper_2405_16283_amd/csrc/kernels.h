@@ -67,6 +67,7 @@ constexpr uint32_t kMaxBatchSpan = 65535;  // largest descriptor index distance 
 struct Batch {
   int32_t n;
   uint32_t base;            // smallest descriptor index of the group
+  int32_t stages;           // products of gemm_small.hip: pieces along K that a wavefront holds in LDS
   uint16_t idx[kMaxBatch];  // descriptor index minus base
   __host__ __device__ uint32_t at(uint32_t i) const { return base + idx[i]; }
 };
@@ -130,6 +131,24 @@ hipError_t launch_gemm_bf16(int form, const DeviceTables& t, const Batch& b, int
 
 // LC_GEMM_F32 and LC_GEMM_BF16_SMALL: gemm_small.hip.
 constexpr int kGemmSmallTile = 32;  // output rows and columns per workgroup
+constexpr int kGemmSmallWaves = 4;  // wavefronts per workgroup, which share its pieces along K
+constexpr int kGemmSmallStages = 4; // pieces of a wavefront in LDS, at most
+constexpr int kGemmRowsTable = 64;  // LC_GEMM_ROWS: K tiles whose addresses are held in LDS
+// The stages a vertex of these classes or of LC_GEMM_ROWS uses (ksz: the depths of its K tiles); a launch takes its largest.  What a
+// short product has no use for would only keep other workgroups off the CU: fp32, 64 of 256x256 with K of 128 53 -> 36 us; bf16, 256 of 64x64
+// with K of 256 14.1 -> 8.4; single rows, 4 against each of 64 B tiles of 512 with K of 512 20.8 -> 14.4; rows not aligned to four elements
+// (no stages), 64 of 128x128 with K of 1022 110 -> 96.
+// The layouts that go by registers hold no stages but are given their room: two workgroups on a CU push one another's
+// lines out of L1 (fp32, B stored [K, N], 192 of 64x64 with K of 704 26.8 us, 33.4 without the room; 64 of 256x256 with K of 1024 147 and 132).
+inline int32_t gemm_small_stages(int cls, const OpDesc& d, const int32_t* ksz) {
+  const bool b16 = cls == LC_GEMM_BF16_SMALL || (cls == LC_GEMM_ROWS && d.dtype == TN_BF16);
+  if (cls == LC_GEMM_ROWS ? d.p.nk > kGemmRowsTable : !b16 && d.dtype != TN_F32) return 0;
+  const int vec = b16 ? 8 : 4;
+  const bool vectors = b16 || !d.p.trans_a || d.trans_b;  // as `pieces` in `product` counts them
+  int64_t pieces = 0;
+  for (int k = 0; k < d.p.nk; ++k) pieces += vectors && ksz[k] % vec ? 0 : ksz[k] / (8 * vec);
+  return (int32_t)(pieces < kGemmSmallWaves * kGemmSmallStages ? (pieces + kGemmSmallWaves - 1) / kGemmSmallWaves : kGemmSmallStages);
+}
 hipError_t launch_gemm_small(bool bf16_products, int dtype, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t stream);
 
 // LC_GEMM_ROWS: products of a single row whose B tiles are stored [cols, K], with rows along K aligned to 16 bytes.
@@ -138,6 +157,7 @@ hipError_t launch_gemm_small(bool bf16_products, int dtype, const DeviceTables& 
 struct RowVertex {
   int32_t key;
   uint32_t desc;
+  int32_t stages;
 };
 hipError_t launch_gemm_rows(int dtype, const DeviceTables& t, uint32_t base, const RowVertex* rows, int n, int32_t max_blocks,
                             hipStream_t stream);

@@ -6,6 +6,7 @@
 //
 // A kernel vertex writes one 32-bit word, a mix of the first words of its operands (additions: their sum, so that
 // increments commute); a graph's results depend on every vertex and on nothing else.
+#include <algorithm>
 #include <cstring>
 #include <deque>
 #include <functional>
@@ -31,6 +32,7 @@ struct Entry { int32_t kind, stream, n, detail, kernels_before, to_gpu; };
 std::map<int, Stream> streams;
 std::map<const char*, std::pair<size_t, hipMemoryType>> memory;  // start -> size, kind
 std::vector<Entry> entries;
+std::vector<int32_t> stages;  // of the launches of small products
 uint64_t rng = 1, serial = 0, idle_asks = 0;
 int64_t calls_until_failure = -1, enqueued_after_failure = -1;  // -1: no failure yet
 
@@ -138,6 +140,7 @@ void* fake_alloc(uint64_t bytes, int gpu) { return allocate(bytes, gpu ? hipMemo
 void fake_reset(uint64_t seed) {  // forgets streams and the log, frees nothing
   streams.clear();
   entries.clear();
+  stages.clear();
   rng = mix(seed + 1);
   idle_asks = 0;
   calls_until_failure = enqueued_after_failure = -1;
@@ -148,6 +151,11 @@ int64_t fake_pending() { return pending(); }
 int64_t fake_log(int32_t* out, int64_t cap) {
   for (int64_t i = 0; i < (int64_t)entries.size() && i < cap; ++i) memcpy(out + 6 * i, &entries[i], sizeof(Entry));
   return (int64_t)entries.size();
+}
+
+int64_t fake_stages(int32_t* out, int64_t cap) {
+  for (int64_t i = 0; i < (int64_t)stages.size() && i < cap; ++i) out[i] = stages[i];
+  return (int64_t)stages.size();
 }
 
 // ---- the runtime ----------------------------------------------------------------------------
@@ -226,6 +234,7 @@ hipError_t launch_device_copies(const CopyBatch& b, hipStream_t s) { return copi
 hipError_t launch_batch(int cls, int, int, const DeviceTables& t, const Batch& b, int32_t, hipStream_t s) {
   if (fails()) return hipErrorLaunchFailure;
   log(0, s, b.n, cls, nullptr);
+  if (cls == LC_GEMM_F32 || cls == LC_GEMM_BF16_SMALL) stages.push_back(b.stages);
   for (int k = 0; k < b.n; ++k) {
     const uint32_t i = b.at(k);
     push(s, [=] { vertex(cls, t, i); }, true);
@@ -235,6 +244,8 @@ hipError_t launch_batch(int cls, int, int, const DeviceTables& t, const Batch& b
 hipError_t launch_gemm_rows(int, const DeviceTables& t, uint32_t, const RowVertex* rows, int n, int32_t, hipStream_t s) {
   if (fails()) return hipErrorLaunchFailure;
   log(0, s, n, LC_GEMM_ROWS, nullptr);
+  stages.push_back(0);
+  for (int k = 0; k < n; ++k) stages.back() = std::max(stages.back(), rows[k].stages);
   for (int k = 0; k < n; ++k) {
     const uint32_t i = rows[k].desc;
     push(s, [=] { vertex(LC_GEMM_ROWS, t, i); }, true);

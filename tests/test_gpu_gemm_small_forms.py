@@ -51,6 +51,29 @@ def test_few_and_many_workgroups(dtype, shape, kw):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m", [1, 40])
+def test_products_of_any_depth_share_a_launch(dtype, m):
+    """A launch's rings have as many stages as its deepest vertex uses, one to four: results are those of the vertices alone."""
+    print(f"[case] gemm {dtype} {m}x48 of mixed depth", flush=True)
+    piece = 32 if dtype == "f32" else 64
+    alone, shared = [], []
+    for together in ([0], [1], [2], [3], [4], [0, 1, 2], [0, 1, 2, 3, 4]):
+        rng = np.random.default_rng(7)
+        g = Graph(dtype)
+        outs, refs = [], []
+        for d, k in enumerate([piece // 2, 4 * piece, 5 * piece, 9 * piece + 8, 40 * piece]):
+            a, b = g.inp(rng.standard_normal((m, k))), g.inp(rng.standard_normal((48, k)) / np.sqrt(k))
+            if d in together:
+                outs.append(g.op(B.TN_OP_GEMM, [a[0], b[0]], m, 48, nk=1, trans_b=1))
+                refs.append((d, k, T._eval_vertex("gemm", dict(nk=1, trans_a=0, trans_b=1, trans_c=0, mode=0), [a[1], b[1]])))
+        for got, (d, k, ref) in zip(g.run(outs), refs):
+            assert R.rel_err(got, ref) < k * 2.0 ** -24 + (2.0 ** -8 if dtype == "bf16" else 0.0)
+            (alone if len(together) == 1 else shared).append((d, got))
+    for d, got in shared:
+        assert np.array_equal(got, dict(alone)[d])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("nk", [64, 65])
 def test_single_rows_with_many_tiles_along_k(dtype, nk):
     """The addresses of the rows' tiles lie in LDS up to 64 tiles along K."""
