@@ -297,7 +297,7 @@ tn_status build_tables(tn_executor& ex) {
     switch (x.op_kind) {
       case TN_OP_GEMM: {
         if (x.p.trans_c) std::swap(d.rows, d.cols);  // the kernels work on the logical [rows, cols] product
-        bool mfma = d.dtype == TN_BF16 && d.trans_b && (!x.p.trans_a || d.rows == 1), k4 = true, too_deep = false;
+        bool mfma = d.dtype == TN_BF16 && d.trans_b && (!x.p.trans_a || d.rows == 1), k4 = true, k32 = true, too_deep = false;
         double K = 0;
         for (int k = 0; k < x.p.nk; ++k) {
           const int32_t kk = x.p.trans_a ? odesc(k).rows : odesc(k).cols;
@@ -305,14 +305,20 @@ tn_status build_tables(tn_executor& ex) {
           K += kk;
           if (kk % 8) mfma = false;
           if (kk % 4) k4 = false;
+          if (kk % 32) k32 = false;
           if (kk > kGemmBf16MaxK) too_deep = true;
         }
         // Small outputs leave a 128x128 workgroup mostly empty and alone with its walk along K.  Measured at K of 4096,
-        // 32x32 tiles against 128x128 ones: 32 products of 512x16, 28 against 59 us, two of them 15 against 56; 8 of
-        // 16x512 with K of 16384, 53 against 223; 64x64 with K of 512, 64 of them, 5.7 against 13.  From 128x128 up the
-        // larger tile's reuse wins once a launch holds more than 64 (256 of them: 120 against 43).
+        // 32x32 tiles against 128x128 ones: 32 products of 512x16, 18 against 28 us, two of them 10 against 26; 8 of 16x512 with K
+        // of 16384, 24 against 83; 64x64 with K of 512, 64 of them, 6.8 against 10, 256 11.6 against 11.0; 64x128, four of them 11 against
+        // 26, 64 20 against 27, 256 68 against 35.  From 128x128 up the larger tile's reuse wins in launches of any size that fills the
+        // chip (two 11 against 27, 64 34 against 29, 256 123 against 36).
         // Tiles too deep for the offsets of the larger form go to the small one as well, which addresses any.
-        const bool small = too_deep || std::min(d.rows, d.cols) <= 32 || (int64_t)d.rows * d.cols <= 64 * 128;
+        // Products with a residual come a row of tiles at a time, a dozen to a launch (the last rows of a prompt): 8 of 48x512 12 us
+        // against 29, with K of 11008 23 against 60, 8 of 63x512 with K of 512 7 against 12 (but 64 of 48x512 68 against 45, and 8 of
+        // 40x4096 95 against 63); rows that share lines of memory with their neighbours, 8 of 96x512 with K of 4104, 26 against 41.
+        const bool thin = x.p.mode == 1 && d.rows < (k32 ? 64 : 128) && d.cols <= 1024;
+        const bool small = too_deep || thin || std::min(d.rows, d.cols) <= 32 || (int64_t)d.rows * d.cols <= 64 * 128;
         vi.cls = !mfma ? LC_GEMM_F32 : small ? LC_GEMM_BF16_SMALL : d.rows >= 256 && d.cols >= 256 ? LC_GEMM_BF16 : LC_GEMM_BF16_128;
         vi.nblocks128 = gemm_blocks(128, d);
         // Single rows against the same B tiles are formed together (32 rows against 24 tiles of 512 with K of 4096: 486
