@@ -544,8 +544,8 @@ constexpr int bwd_lds(int hd) { return 4 * (2 * kRows * (hd + 4) + 2 * kRows); }
 
 template <auto kernel>
 hipError_t launch(int lds, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t s) {
-  static const hipError_t attr = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (attr != hipSuccess) return attr;
+  static std::atomic<uint64_t> allowed{0};
+  if (const hipError_t e = allow_lds(allowed, (const void*)kernel, lds); e != hipSuccess) return e;
   hipLaunchKernelGGL(kernel, dim3((unsigned)max_blocks, (unsigned)b.n), dim3(256), lds, s, t, b);
   return hipGetLastError();
 }

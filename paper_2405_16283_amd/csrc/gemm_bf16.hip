@@ -577,8 +577,8 @@ hipError_t launch_gemm_bf16(int form, const DeviceTables& t, const Batch& b, int
   const dim3 grid((unsigned)max_blocks, (unsigned)b.n), wg(256);
 #define TN_LAUNCH_GEMM(KERNEL, LDS)                                                                                             \
   do {                                                                                                                          \
-    static const hipError_t attr = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, (LDS)); \
-    if (attr != hipSuccess) return attr;                                                                                        \
+    static std::atomic<uint64_t> allowed{0};                                                                                    \
+    if (const hipError_t e = allow_lds(allowed, (const void*)KERNEL, (LDS)); e != hipSuccess) return e;                         \
     hipLaunchKernelGGL(KERNEL, grid, wg, (LDS), s, t, b);                                                                       \
   } while (0)
   switch (form) {

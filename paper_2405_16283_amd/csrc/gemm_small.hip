@@ -557,9 +557,9 @@ __global__ void __launch_bounds__(64 * kWaves) gemm_rows_kernel(DeviceTables t, 
 
 #define TN_LAUNCH_SMALL(KERNEL, LDS)                                                                                              \
   do {                                                                                                                            \
-    static const hipError_t attr = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, LDS(kStages)); \
-    if (attr != hipSuccess) return attr;                                                                                          \
-    hipLaunchKernelGGL(KERNEL, grid, wg, LDS(b.stages), s, t, b);                                                                         \
+    static std::atomic<uint64_t> allowed{0};                                                                                      \
+    if (const hipError_t e = allow_lds(allowed, (const void*)KERNEL, LDS(kStages)); e != hipSuccess) return e;                    \
+    hipLaunchKernelGGL(KERNEL, grid, wg, LDS(b.stages), s, t, b);                                                                 \
   } while (0)
 
 hipError_t launch_gemm_small(bool bf16_products, int dtype, const DeviceTables& t, const Batch& b, int32_t max_blocks, hipStream_t s) {

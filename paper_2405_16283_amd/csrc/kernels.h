@@ -8,6 +8,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 
 #include "turnip.h"
@@ -26,6 +27,18 @@ struct OpDesc {
   int32_t trans_b;  // gemm: B tiles are stored [cols, K]
   tn_op_params p;
 };
+
+// Lets `kernel` be launched with `bytes` of dynamic LDS on the current GPU, where that is more than 64 KiB: a GPU is told of it
+// once per kernel (done: a bit for each GPU).
+inline hipError_t allow_lds(std::atomic<uint64_t>& done, const void* kernel, int bytes) {
+  int dev = -1;
+  if (const hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+  const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+  if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+  return e;
+}
 
 // Launch classes: vertices of one class can share a launch.
 enum LaunchClass {

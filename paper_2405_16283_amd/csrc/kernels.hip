@@ -1390,9 +1390,8 @@ hipError_t launch_batch(int cls, int dtype, int head_dim, const DeviceTables& t,
     if (head_dim == 64) {                                                                                         \
       hipLaunchKernelGGL((attn_bwd_bf16_kernel<64, MODE>), grid, dim3(kAttnBwdThreads), attn_bwd_lds(64), s, t, b); \
     } else if (head_dim == 128) {                                                                                 \
-      static const hipError_t attr = hipFuncSetAttribute((const void*)attn_bwd_bf16_kernel<128, MODE>,            \
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, attn_bwd_lds(128)); \
-      if (attr != hipSuccess) return attr;                                                                        \
+      static std::atomic<uint64_t> allowed{0};                                                                    \
+      if (const hipError_t e = allow_lds(allowed, (const void*)attn_bwd_bf16_kernel<128, MODE>, attn_bwd_lds(128)); e != hipSuccess) return e; \
       hipLaunchKernelGGL((attn_bwd_bf16_kernel<128, MODE>), grid, dim3(kAttnBwdThreads), attn_bwd_lds(128), s, t, b); \
     } else {                                                                                                      \
       return hipErrorInvalidValue;                                                                                \
@@ -1409,9 +1408,8 @@ hipError_t launch_batch(int cls, int dtype, int head_dim, const DeviceTables& t,
       if (head_dim == 64) {
         hipLaunchKernelGGL(attn_bf16_kernel<64>, grid, wg, 4 * 64 * 64 * 2, s, t, b);
       } else if (head_dim == 128) {
-        static const hipError_t attr = hipFuncSetAttribute((const void*)attn_bf16_kernel<128>,
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 64 * 128 * 2);
-        if (attr != hipSuccess) return attr;
+        static std::atomic<uint64_t> allowed{0};
+        if (const hipError_t e = allow_lds(allowed, (const void*)attn_bf16_kernel<128>, 4 * 64 * 128 * 2); e != hipSuccess) return e;
         hipLaunchKernelGGL(attn_bf16_kernel<128>, grid, wg, 4 * 64 * 128 * 2, s, t, b);
       } else {
         return hipErrorInvalidValue;
