@@ -64,6 +64,35 @@ __device__ __forceinline__ const T* tile_elem_t(void* const* tiles, int nc, int 
   return (const T*)tiles[rt * nc + ct] + (size_t)(col - ct * t_cols) * pitch + (row - rt * t_rows);
 }
 
+// 16 bytes per lane from global memory straight into LDS at lds_addr + imm + 16 * lane.  In assembly, so that the compiler does
+// not wait for them: kernels keep several in flight across barriers and count them themselves.  (M0 has to be written one
+// instruction ahead of the load that uses it.)
+typedef __attribute__((address_space(3))) void* lptr_t;
+typedef __attribute__((ext_vector_type(4))) uint32_t rsrc_t;
+// from a 32-bit byte offset per lane and a uniform one
+__device__ __forceinline__ void load_lds(uint32_t voff, rsrc_t r, uint32_t soff, uint32_t lds_addr, int imm) {
+  asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               ::"v"(voff), "s"(r), "s"(soff), "s"(lds_addr), "n"(imm) : "memory", "scc");
+}
+__device__ __forceinline__ void load_lds(uint64_t addr, uint32_t lds_addr, int imm) {
+  asm volatile("s_add_u32 m0, %1, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(addr), "s"(lds_addr), "n"(imm) : "memory", "scc");
+}
+__device__ __forceinline__ void load_lds(const void* addr, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(addr), "s"(lds_addr) : "memory");
+}
+// Reads of the (read-only, wavefront-uniform) operand tables through the scalar unit, so that
+// they are counted by lgkmcnt and never force a wait on the vector loads in flight.
+__device__ __forceinline__ const void* sload_ptr(const void* const* addr) {
+  const void* v;
+  asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(addr) : "memory");
+  return v;
+}
+__device__ __forceinline__ int sload_int(const int* addr) {
+  int v;
+  asm volatile("s_load_dword %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(addr) : "memory");
+  return v;
+}
+
 // Workgroups are handed to the 8 XCDs round-robin in launch order, and each XCD has its own L2.
 // This turns the launch position into a position in which each XCD gets a contiguous run of
 // (vertex, tile) pairs, so that the workgroups sharing an L2 work on neighbouring tiles -- the

@@ -28,33 +28,12 @@
 namespace tn {
 namespace {
 
-typedef __attribute__((address_space(3))) void* lptr_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t rsrc_t;
-
 constexpr int kChunk = 64;               // of K
 constexpr int kRegionRows = 128;
 constexpr uint32_t kRegionBytes = kRegionRows * kChunk * 2;
 constexpr int kPieceLoads = 4;           // load instructions per wavefront and region
 constexpr uint32_t kNoOffset = 0xFFFFFFFFu;  // outside every buffer resource: the lane's bytes in LDS become zero
 
-__device__ __forceinline__ const void* sload_ptr(const void* const* addr) {
-  const void* v;
-  asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(addr) : "memory");
-  return v;
-}
-__device__ __forceinline__ int sload_int(const int* addr) {
-  int v;
-  asm volatile("s_load_dword %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(addr) : "memory");
-  return v;
-}
-
-// 16 bytes per lane from global memory straight into LDS at lds_addr + imm + 16 * lane, from a 32-bit byte offset per lane and a
-// uniform one.  In assembly, so that the compiler does not wait for them: the loops count their own loads.  (M0 has to be
-// written one instruction ahead of the load that uses it.)
-__device__ __forceinline__ void load_lds(uint32_t voff, rsrc_t r, uint32_t soff, uint32_t lds_addr, int imm) {
-  asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               ::"v"(voff), "s"(r), "s"(soff), "s"(lds_addr), "n"(imm) : "memory", "scc");
-}
 // The accumulators stay in the accumulation registers and each is updated in place: left to itself the compiler gives the
 // result other registers than the summand, and the 256 of a wavefront do not fit twice.  It does not know that these
 // are MFMAs, so whatever else reads accumulators comes after mfma_drain(), through which they pass.

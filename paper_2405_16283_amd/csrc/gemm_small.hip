@@ -47,17 +47,6 @@ __device__ __forceinline__ f32x4 ldg4(const TN_GLOBAL bf16_t* p) {
 __device__ __forceinline__ float ldg(const TN_GLOBAL float* p) { return *p; }
 __device__ __forceinline__ float ldg(const TN_GLOBAL bf16_t* p) { return bf2f(*p); }
 
-typedef __attribute__((ext_vector_type(4))) uint32_t rsrc_t;
-typedef __attribute__((address_space(3))) void* lptr_t;
-// 16 bytes per lane from global memory straight into LDS at lds_addr + 16 * lane, not tracked by the compiler.  (M0 has to be
-// written one instruction ahead.)
-__device__ __forceinline__ void load_lds(uint32_t voff, rsrc_t r, uint32_t soff, uint32_t lds_addr, int imm) {
-  asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(r), "s"(soff), "s"(lds_addr), "n"(imm) : "memory", "scc");
-}
-__device__ __forceinline__ void load_lds(uint64_t addr, uint32_t lds_addr, int imm) {
-  asm volatile("s_add_u32 m0, %1, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(addr), "s"(lds_addr), "n"(imm) : "memory", "scc");
-}
-
 __device__ __forceinline__ uint64_t uniform(uint64_t v) {
   return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }

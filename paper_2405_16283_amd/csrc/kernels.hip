@@ -647,22 +647,6 @@ __global__ void __launch_bounds__(256) transpose_kernel(DeviceTables t, Batch b)
     if (c0 + i < C && r0 + tx < R) o[(size_t)(c0 + i) * R + r0 + tx] = tile[tx][i];
 }
 
-typedef __attribute__((address_space(3))) void* lptr_t;
-
-// 16 bytes per lane from global memory straight into LDS at lds_addr + 16 * lane.  Issued as
-// inline assembly so that the compiler does not track it: the kernel keeps several such loads
-// in flight across barriers and waits for them with explicit vmcnt values.
-__device__ __forceinline__ void load_lds16(const void* gsrc, uint32_t lds_addr) {
-  // m0 is read one wait state after it is written at the earliest
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gsrc), "s"(lds_addr) : "memory");
-}
-// Reads of the (read-only, wavefront-uniform) operand tables through the scalar unit, so that
-// they are counted by lgkmcnt and never force a wait on the vector loads in flight.
-__device__ __forceinline__ const void* sload_ptr(const void* const* addr) {
-  const void* v;
-  asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(addr) : "memory");
-  return v;
-}
 // The idea of xcd_remap for kernels whose workgroups of one vertex share operands (the query blocks of an
 // attention head all read that head's keys and values): vertex by goes to XCD by % 8 as a whole,
 // and vertices that differ in cost (blocks on and off the diagonal) stay spread over the XCDs.
@@ -779,15 +763,15 @@ __global__ void __launch_bounds__(kAttnBwdThreads) attn_bwd_bf16_kernel(DeviceTa
       const int p = i * kAttnBwdThreads + threadIdx.x, r = p / CPR;
       const int col = cin0 + (((p % CPR) ^ (CPR == 16 ? (r & 15) : ((r >> 1) & 7))) * 8);
       const int gr = min(rin + r, trows - 1);  // rows past the end: any valid row, their weights are zero
-      load_lds16(At + (size_t)gr * tc + col, dst + i * (kAttnBwdThreads * 16));
-      if (mode != 3) load_lds16(Bt + (size_t)gr * tc + col, dst + ABYTES + i * (kAttnBwdThreads * 16));
+      load_lds(At + (size_t)gr * tc + col, dst + i * (kAttnBwdThreads * 16));
+      if (mode != 3) load_lds(Bt + (size_t)gr * tc + col, dst + ABYTES + i * (kAttnBwdThreads * 16));
     }
     if (mode >= 1) {
 #pragma unroll
       for (int i = 0; i < HD * (CH / 8) / kAttnBwdThreads; ++i) {
         const int p = i * kAttnBwdThreads + threadIdx.x, dd = p / 8;
         const int r8 = min(rin + ((p % 8) ^ ((dd >> 1) & 7)) * 8, trows - 8);  // 8 rows at once
-        load_lds16(Tp + (size_t)(cin0 + dd) * trows + r8, dst + 2 * ABYTES + i * (kAttnBwdThreads * 16));
+        load_lds(Tp + (size_t)(cin0 + dd) * trows + r8, dst + 2 * ABYTES + i * (kAttnBwdThreads * 16));
       }
     }
   };
@@ -1074,10 +1058,10 @@ __global__ void __launch_bounds__(256, 2) attn_bf16_kernel(DeviceTables t, Batch
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
       const int krow = min(kin + kr_[i], trows - 1);  // rows past the end: any valid row, masked later
-      load_lds16(Kt + (size_t)krow * tc + kcol_[i], dst + i * 4096);
+      load_lds(Kt + (size_t)krow * tc + kcol_[i], dst + i * 4096);
       int kv = kin + vkv_[i];
       if (kv >= trows) kv = 0;  // multiplied by zero probabilities; any valid data will do
-      load_lds16(Vt + (size_t)vrow_[i] * trows + kv, dst + KBYTES + i * 4096);
+      load_lds(Vt + (size_t)vrow_[i] * trows + kv, dst + KBYTES + i * 4096);
     }
   };
 

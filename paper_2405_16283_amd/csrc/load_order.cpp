@@ -27,6 +27,7 @@ constexpr uint64_t kMaxSetBytes = 64ull << 20, kMaxSteps = 50ull << 20;
 constexpr double kWorthwhile = 0.04;
 constexpr double kLinkBytes = 54e9;  // per second
 
+// (the multipliers are those of splitmix64, whose last steps `mix` is)
 uint64_t hash_words(const uint64_t* w, size_t n) {
   uint64_t h = 0x9E3779B97F4A7C15ull;
   for (size_t i = 0; i < n; ++i) {
