@@ -7,12 +7,15 @@
 // and 2070, and 2130 when neighbouring instructions share an operand both ways (rows of tiles walked to and fro).  Hence:
 //   - MFMA 16x16x32 (the sums come out bit by bit as those of 32x32x16);
 //   - four wavefronts, one per SIMD, with 128x128 of the 256x256 tile each: eight with 128x64 read half as much again from LDS;
-//   - K in chunks of 64, so that the eight lanes of a row fetch a whole 128-byte line; with 32 each line was fetched twice;
+//   - K in chunks of 64, so that the eight lanes of a row fetch a whole 128-byte line once (counted: 256 workgroups with K of 4096 read
+//     1074 MB into LDS, their operands and no more); of a chunk of 32 a line is two, half of it used by each;
 //   - one wavefront per SIMD has nothing beside it to hide its other instructions, so these are placed one by one into
 //     the 16 cycles of an MFMA, and the position in LDS of a load is set ahead of the MFMA before it.
-// The loop of the 256x256 form takes 2380 cycles per chunk, 2048 of them MFMAs, at 1.64 to 1.79 GHz.  Against the kernel it replaces
-// (32x32x16, eight wavefronts, K in steps of 32), launches of 512x512 vertices one behind the other: 4096 x 12288 with K of 4096 367 -> 327
-// us, 4096 x 4096 133 -> 119, with K of 11008 315 -> 276, 8192 x 8192 x 8192 877 -> 762 (1443 TFLOP/s).
+// The loop of the 256x256 form takes 2250 cycles per chunk, 2048 of them MFMAs, at 1.72 GHz (256 workgroups, K of 4096 and 8192: 174 and
+// 319 thousand cycles); what does not depend on K, the first operands and the stores, takes 30 thousand.  Against the kernel it replaced
+// (32x32x16, eight wavefronts, K in steps of 32), launches of 512x512 vertices one behind the other, when it came: 4096 x 12288 with
+// K of 4096 367 -> 327 us, 4096 x 4096 133 -> 119, with K of 11008 315 -> 276, 8192 x 8192 x 8192 877 -> 762.  With the present epilogue, twelve
+// launches in a row: 289, 100, 242 and 743 us (1480 TFLOP/s).
 //
 // Operands lie in LDS in regions of 128 rows x 64 of K (16 KiB), a ring of them that `buffer_load ... lds` fills directly, 64 lanes
 // x 16 bytes per instruction, unpadded: piece c of row r lies at position c ^ (r & 7) of its row, so that the 16 lanes
@@ -428,12 +431,13 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_256_kernel(DeviceTables t, B
 
 // ---------------------------------------------------------------------------------------------
 // 128x128 per workgroup: every wavefront has 64x64.  A chunk's fragments are read while the chunk before is multiplied, into a second
-// set of registers, with one barrier per chunk and a ring of NC chunks.  What bounds it is LDS: 96 KiB read and written per chunk, 768
-// cycles at 128 bytes, 512 of MFMAs.
-// NC = 4: 128 KiB, one workgroup per CU, for launches of at most 256 workgroups: loads have three chunks to arrive, 820 cycles
-// each.  (320 rows x 4096 with K of 11008, 96 workgroups: 65 us; the register-staged 128x128 kernel it replaces 93.)
-// NC = 2: 64 KiB, two workgroups per CU hide each other's waits, for larger launches (1371 x 4096 with K of 11008, 352 workgroups:
-// 138 us, 153 with NC = 4; 688 workgroups with K of 2048: 57 and 67; but 96 workgroups with K of 11008: 100 and 65).
+// set of registers, with one barrier per chunk and a ring of NC chunks.  96 KiB go through LDS per chunk and 512 cycles of MFMAs: twice
+// the bytes per product of the larger form.
+// NC = 4: 128 KiB, one workgroup per CU, for launches of at most 256 workgroups: loads have three chunks to arrive, 680 cycles
+// each (256 workgroups, K of 4096 and 8192: 60 and 103 thousand cycles).  (320 rows x 4096 with K of 11008, 96 workgroups: 65 to 68 us; the
+// register-staged 128x128 kernel it replaced 93.)
+// NC = 2: 64 KiB, two workgroups per CU hide each other's waits, 580 cycles per chunk, for larger launches (1371 x 4096 with K of 11008, 352
+// workgroups: 138 us, 153 with NC = 4; 688 workgroups with K of 2048: 57 and 67; but 96 workgroups with K of 11008: 100 and 65).
 // A form with 256x128 per workgroup measured within 3 % of NC = 2 wherever that is the fastest and is not kept.
 // ---------------------------------------------------------------------------------------------
 constexpr uint32_t kChunkBytes = 2 * kRegionBytes;  // P region, then the Q region

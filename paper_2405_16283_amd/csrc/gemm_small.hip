@@ -8,8 +8,8 @@
 // One workgroup = 32x32 elements of the output; its four wavefronts form the same 32x32 each over a quarter of
 // K (pieces of 128 bytes per row, dealt out in turn) and add up through LDS.  K is summed in a permuted but fixed order.
 // Where both operands are stored along K, pieces come by `buffer_load ... lds` into a ring of the wavefront's own in LDS (no barrier),
-// three of them in flight, eight lanes to a row; fragments are read from there.  Other layouts, and tiles whose rows are not aligned,
-// go from memory straight into the registers that feed the MFMAs: lane (n = lane & 15, g = lane >> 4) reads 16 bytes
+// three of them in flight, eight lanes to a row; fragments are read from there (how much LDS that is: gemm_small_stages).  Other
+// layouts, and tiles whose rows are not aligned, go from memory straight into the registers that feed the MFMAs: lane (n = lane & 15, g = lane >> 4) reads 16 bytes
 // along K of row n.  That way a load instruction touches 16 rows out of order, and a wavefront spends more time on issuing its
 // eight loads per piece than on its 32 MFMAs.
 //
@@ -18,7 +18,7 @@
 // the way to its first operands (about 4 us with launch and end) and the number of workgroups.  Per launch, straight into
 // registers -> by way of LDS: 256x256 in fp32 with K of 1024, one to four of them, 11.5 -> 9.7 us, twelve 28.9 -> 26.2 (61 TFLOP/s); with K of
 // 2560 22.6 -> 19.1 and 66.4 -> 54.8 (73, of 157); 64x64 with K of 256 5.7 -> 5.4, with 704 in tiles of 64 9.5 -> 9.8 (every piece
-// lies in another tile).  bf16: 32 products of 512x16, K 4096, 28 us; 8 of 16x512, K 16384, 53 us.
+// lies in another tile).  bf16: 32 products of 512x16, K 4096, 30 -> 18 us; 8 of 16x512, K 16384, 52 -> 24.
 #include <algorithm>
 
 #include "device.h"
